@@ -172,3 +172,44 @@ def tolerance(case):
     if case["op"] in ("nt", "nn", "splitk"):
         return {"rel": 6.6e-3, "max": 1.6e-2}
     return {"rel": 1e-2, "max": 0.3 if case["op"] == "bwd" else 0.15}
+
+
+def exact(case, seed):
+    # what run() returns, in float64 by plain torch: the definition, one query head at a time
+    s = prepare(case, seed)
+    if case["op"] in ("nt", "nn", "splitk"):
+        return s["a"].double() @ (s["b"].double() if case["op"] == "nn" else s["b"].double().t())
+    B, Hq, Hkv, N, d = (case[k] for k in ("B", "Hq", "Hkv", "N", "d"))
+
+    def real(nm, b, h):
+        x = s[nm][b, h]
+        return x.view(torch.float8_e4m3fn).float().double() * s["s" + nm] if case["dtype"] == "fp8" else x.double()
+
+    def zeros(*shape):
+        return torch.zeros(shape, device="cuda", dtype=torch.float64)
+
+    hidden = torch.ones(N, N, device="cuda", dtype=torch.bool).triu_(1) if case["causal"] else None
+    bwd = case["op"] == "bwd"
+    if bwd:
+        dq, dk, dv = zeros(B, Hq, N, d), zeros(B, Hkv, N, d), zeros(B, Hkv, N, d)
+    else:
+        o, lse = zeros(B, Hq, N, d), zeros(B, Hq, N)
+    for b in range(B):
+        for h in range(Hq):
+            g = h // (Hq // Hkv)
+            q, k, v = real("q", b, h), real("k", b, g), real("v", b, g)
+            sc = (q @ k.t()).mul_(s["scale"])
+            if hidden is not None:
+                sc.masked_fill_(hidden, -math.inf)
+            row = torch.logsumexp(sc, 1)
+            p = sc.sub_(row[:, None]).exp_()
+            if not bwd:
+                o[b, h], lse[b, h] = p @ v, row
+                continue
+            g_out = s["dout"][b, h].double()
+            dv[b, g] += p.t() @ g_out
+            dp = g_out @ v.t()
+            ds = dp.sub_((p * dp).sum(1, keepdim=True)).mul_(p).mul_(s["scale"])
+            dq[b, h] = ds @ k
+            dk[b, g] += ds.t() @ q
+    return (dq, dk, dv) if bwd else (o, lse)
