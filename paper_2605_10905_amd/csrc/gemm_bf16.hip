@@ -45,6 +45,64 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, t);
 }
 
+// The last step of every tile: the finished bf16 tile lies row-major in LDS (row pitch BN * 2 + 16
+// bytes) and goes to C in 16-byte pieces at 16-byte aligned addresses, consecutive lanes on
+// consecutive pieces of a row.  The accumulator layout gives a lane 8 columns of a row of its own,
+// i.e. a store instruction that touches 32 rows with 32 bytes each, and with N not a multiple of 8
+// even that splits into 2-byte stores because the rows start at any multiple of 2 bytes.  Here the
+// odd start costs a shift: the piece that begins s = (row start mod 8) elements earlier is put
+// together from five LDS words by a funnel shift, and only the up to seven elements in front of the
+// first and behind the last whole piece of a row are stored one by one.  Bound by memory writes for
+// short contractions; measured, stores from the accumulator layout -> staged: 442368 x 448 x 192
+// 165.6 -> 145.9 us (3.4 -> 3.9 TB/s), 5329 x 3495 x 160 79.5 -> 26.2 us, 27854 x 4910 x 960 457 -> 303 us,
+// 794 x 58579 x 4576 601 -> 485 us, 8192 x 8192 x 4096 unchanged (457 / 458 us).
+template <int BM, int BN>
+__device__ __forceinline__ void gemm_store_staged(LDS_AS const char* tile, const GemmParams& p, int m0, int n0, int tid) {
+  constexpr int PITCH = BN * 2 + 16, CPR = BN / 8, RPI = 256 / CPR;
+  static_assert(256 % CPR == 0 && BM % RPI == 0, "whole rows per pass");
+  const int rows = min(BM, p.M - m0), nv = min(BN, p.N - n0);
+  const int c = tid % CPR, r0 = tid / CPR;
+  __bf16* const ctile = (__bf16*)p.c + (size_t)m0 * p.N + n0;
+  if ((p.N & 7) == 0) {
+#pragma unroll 8
+    for (int i = 0; i < BM / RPI; ++i) {
+      const int r = i * RPI + r0;
+      if (r < rows && c * 8 < nv) {
+        const u32x4 out = *(LDS_AS const u32x4*)(tile + r * PITCH + c * 16);
+        GEMM_STORE_C(out, (u32x4*)(ctile + (size_t)r * p.N + c * 8));
+      }
+    }
+    return;
+  }
+#pragma unroll 4
+  for (int i = 0; i < BM / RPI; ++i) {
+    const int r = i * RPI + r0;
+    const int s = (int)(((size_t)(m0 + r) * p.N + n0) & 7);
+    const int e = 8 * (c + (s ? 1 : 0)) - s;  // first element of this lane's piece
+    if (r < rows && e + 8 <= nv) {
+      LDS_AS const uint32_t* const w = (LDS_AS const uint32_t*)(tile + r * PITCH) + (e >> 1);
+      uint32_t d[5];
+#pragma unroll
+      for (int j = 0; j < 5; ++j) d[j] = w[j];  // (the fifth word of a row's last piece is row padding)
+      const uint32_t sh = (e & 1) * 16;
+      u32x4 out;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) out[j] = __builtin_amdgcn_alignbit(d[j + 1], d[j], sh);
+      GEMM_STORE_C(out, (u32x4*)(ctile + (size_t)r * p.N + e));
+    }
+  }
+  // row ends: eight lanes for the elements in front of the first whole piece, eight for those behind the last
+  const int j = tid & 15;
+#pragma unroll 4
+  for (int i = 0; i < BM / 16; ++i) {
+    const int r = i * 16 + (tid >> 4);
+    const int s = (int)(((size_t)(m0 + r) * p.N + n0) & 7);
+    const int head = min((8 - s) & 7, nv);
+    const int e = j < 8 ? j : head + ((nv - head) & ~7) + (j - 8);
+    if (r < rows && e < (j < 8 ? head : nv)) ((uint16_t*)ctile)[(size_t)r * p.N + e] = *(LDS_AS const uint16_t*)(tile + r * PITCH + e * 2);
+  }
+}
+
 // WM x WN 32x32 blocks per wave, 2 x 2 waves: the workgroup tile is 64 WM x 64 WN.
 template <int WM, int WN, int BK, int NSTAGE>
 struct GemmCfg {
@@ -56,7 +114,8 @@ struct GemmCfg {
   static constexpr int LPS = NLDA + NLDB;
   static constexpr int NKK = BK / 16;
   static constexpr int LPP = LPS / NKK;  // loads issued per k-step
-  static constexpr int LDS_BYTES = NSTAGE * STAGEB;
+  static constexpr int PITCH = BN * 2 + 16;  // bytes per row of the finished tile staged in LDS (gemm_store_staged)
+  static constexpr int LDS_BYTES = NSTAGE * STAGEB > BM * PITCH ? NSTAGE * STAGEB : BM * PITCH;
   static_assert(LDS_BYTES <= 160 * 1024, "ring does not fit the LDS");
   static_assert((NSTAGE - 1) * LPS <= 63, "vmcnt field");
   static_assert(NSTAGE >= 2 && NKK % 2 == 0 && LPS % NKK == 0 && NLDA >= 1 && NLDB >= 1, "pipeline shape");
@@ -249,11 +308,10 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
   }
 
   // ---- epilogue: lane (li, h) holds, for row m, the columns n = 32 nb + 8 a + 4 h + (0..3) ---------
-  const bool vec_ok = (N & 7) == 0;
+  __syncthreads();  // no wave reads the ring any more
 #pragma unroll
   for (int mb = 0; mb < WM; ++mb) {
-    const int m = m0 + wm * 32 * WM + mb * 32 + li;
-    __bf16* const crow = (__bf16*)p.c + (size_t)min(m, M - 1) * N;
+    const uint32_t row = (wm * 32 * WM + mb * 32 + li) * C::PITCH + (wn * 32 * WN + h * 8) * 2;
 #pragma unroll
     for (int nb = 0; nb < WN; ++nb)
 #pragma unroll
@@ -267,22 +325,12 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
           x[r] = sw[0];
           y[r] = sw[1];
         }
-        const int n = n0 + wn * 32 * WN + nb * 32 + a * 16 + h * 8;  // this lane's 8 consecutive columns
-        if (m < M) {
-          if (vec_ok && n + 8 <= N) {
-            u32x4 out = {x[0], x[1], y[0], y[1]};
-            GEMM_STORE_C(out, (u32x4*)(crow + n));
-          } else {
-            const uint32_t v[4] = {x[0], x[1], y[0], y[1]};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (n + e < N) ((uint16_t*)crow)[n + e] = (uint16_t)(v[e >> 1] >> ((e & 1) * 16));
-          }
-        }
+        *(LDS_AS u32x4*)(smem + row + (nb * 32 + a * 16) * 2) = u32x4{x[0], x[1], y[0], y[1]};  // this lane's 8 consecutive columns
       }
   }
+  __syncthreads();
+  gemm_store_staged<C::BM, C::BN>(smem, p, m0, n0, tid);
 }
-
 
 // The 256 x 256 tile on the 16x16x32 MFMA: each wave's 128 x 128 quarter is 8 x 8 blocks of 16 x 16
 // (64 accumulators of 4 registers), a k-step is 32 wide, a fragment (16 rows x 32 k: 16 bytes per
@@ -464,11 +512,10 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
     }
     return;
   }
-  const bool vec_ok = (N & 7) == 0;
+  __syncthreads();  // no wave reads the ring any more
 #pragma unroll
   for (int mb = 0; mb < 8; ++mb) {
-    const int m = m0 + wm * 128 + mb * 16 + lj;
-    __bf16* const crow = (__bf16*)p.c + (size_t)min(m, M - 1) * N;
+    const uint32_t row = (wm * 128 + mb * 16 + lj) * C::PITCH;
 #pragma unroll
     for (int nb = 0; nb < 8; nb += 2) {
       uint32_t x[2], y[2];
@@ -481,20 +528,12 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
         y[r] = sw[1];
       }
       // even lane groups: own block nb, columns 4g .. 4g+7; odd ones: block nb+1, columns 4(g-1) .. 4(g-1)+7
-      const int n = n0 + wn * 128 + (nb + (g & 1)) * 16 + 4 * (g & ~1);
-      if (m < M) {
-        if (vec_ok && n + 8 <= N) {
-          u32x4 out = {x[0], x[1], y[0], y[1]};
-          GEMM_STORE_C(out, (u32x4*)(crow + n));
-        } else {
-          const uint32_t v[4] = {x[0], x[1], y[0], y[1]};
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (n + e < N) ((uint16_t*)crow)[n + e] = (uint16_t)(v[e >> 1] >> ((e & 1) * 16));
-        }
-      }
+      const int n = wn * 128 + (nb + (g & 1)) * 16 + 4 * (g & ~1);
+      *(LDS_AS u32x4*)(smem + row + n * 2) = u32x4{x[0], x[1], y[0], y[1]};
     }
   }
+  __syncthreads();
+  gemm_store_staged<C::BM, C::BN>(smem, p, m0, n0, tid);
 }
 
 template <int BK, int NSTAGE>

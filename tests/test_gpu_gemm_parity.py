@@ -75,6 +75,29 @@ def test_gemm_small_shapes_all_variants(M, N, K):
         check(c, a, b, f"gemm {M}x{N}x{K} variant {var}")
 
 
+@pytest.mark.parametrize("N", [1, 2, 7, 9, 63, 65, 120, 129, 255, 257, 263, 511])
+def test_gemm_row_starts_at_every_alignment(N):
+    """C's rows start at any multiple of two bytes when N is not a multiple of 8: whole 16-byte pieces,
+    the elements in front of and behind them, and nothing outside C."""
+    import paper_2605_10905_amd as A
+
+    M, K, guard = 261, 64, 64
+    a, b = wl.make_gemm_inputs(1300 + N, M, N, K)
+    ad, bd = gu.bf16_to_device(a), gu.bf16_to_device(b)
+    for var in _variants(K):
+        print(f"gemm row starts N {N} variant {var}", flush=True)
+        buf = torch.full((M * N + 2 * guard,), 7.0, dtype=torch.bfloat16, device="cuda")
+        c = buf[guard:guard + M * N].view(M, N)
+        c.fill_(float("nan"))
+        if var is None:
+            A.gemm_bf16_nt(ad, bd, c, M, N, K)
+        else:
+            A.gemm_bf16_nt_variant(ad, bd, c, M, N, K, var)
+        torch.cuda.synchronize()
+        check(c, a, b, f"gemm row starts N {N} variant {var}")
+        assert bool((buf[:guard] == 7.0).all()) and bool((buf[guard + M * N:] == 7.0).all())
+
+
 def test_gemm_structured_inputs():
     """Operands that expose a wrong row/column or k mapping: one-hot rows select single entries."""
     M, N, K = 384, 320, 128
