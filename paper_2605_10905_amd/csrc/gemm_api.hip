@@ -10,59 +10,90 @@ namespace {
 
 bool misaligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) != 0; }
 
-// Kernel choice, from measurements on the paper's shapes: the 256 x 256 tile (best rate per CU)
-// when it gives most of the 256 CUs a tile; the 128 x 128 tile with a deep ring when that yields
-// at least 100 tiles (it then beats both the half-empty chip of the large tile and the operand
-// re-reads of the small one); else 64 x 64.
-int find(const GemmVariant* table, int count, int tile, int bk, int nth) {
-  for (int i = 0; i < count; ++i)
-    if (table[i].bm == tile && table[i].bk == bk && nth-- == 0) return i;
-  return -1;
+// Tile choice: the estimated time of a launch, smallest wins.  A tile's workgroup takes
+// fixed + steps * step_us microseconds (GemmTile: measured, the rates hold the LDS staging, the
+// matrix work and the tile's start and end); with one workgroup per CU the launch takes whole
+// rounds over the 256 CUs, with several the rounds blur (half a round is lost at the end).
+// Operands and result at tb_s are the other bound, and 0.3 of the smaller of the two is not
+// hidden behind the larger.  Against the best tile of an exhaustive run over those shapes the choice
+// loses 2.6 % on average; against the rule it replaces (256 / 128 / 64 squares by number of
+// tiles) it is 1.8 x faster on the nt shapes (half of it from the staged stores) and 1.5 x on nn.
+double tile_cost(const GemmTile& t, int M, int N, long long K, long long splits, double bytes) {
+  const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
+  if (tiles * 512 > 0x7fffffffll) return -1.0;  // beyond what a grid holds
+  double rounds = (double)((tiles + 255) / 256);
+  if (t.per_cu > 1 && tiles >= 256ll * t.per_cu) rounds = (double)tiles / 256.0 + 0.5;
+  const double work = rounds * (t.fixed_us + (double)((K + t.step - 1) / t.step) * t.step_us);
+  const double mem = bytes / (t.tb_s * 1e6);
+  return work > mem ? work + 0.3 * mem : mem + 0.3 * work;
 }
 
-int choose(int M, int N, int K, const GemmVariant* table, int count) {
-  auto tiles = [&](int t) { return (long long)((M + t - 1) / t) * ((N + t - 1) / t); };
-  int v = -1;
-  // (256 tile: the 16x16x32 MFMA form is 2-4 % faster at the same power; it runs its stages in pairs)
-  // (with at most four of its k-stages the ring of two 64-column stages starts and drains faster
-  // than the ring of four 32-column ones: 8-12 % on the K <= 256 shapes of the paper's tables)
-  if (tiles(256) >= 200) v = K % 64 == 0 && K <= 256 ? find(table, count, 256, 64, 1) : find(table, count, 256, 32, K % 64 == 0 ? 1 : 0);
-  else if (tiles(128) >= 100 && K % 64 == 0) v = find(table, count, 128, 64, 1);
-  if (v < 0) v = find(table, count, 64, 32, 0);
-  return v;
+const GemmTile* cheapest(const GemmTile* best, double* cost, const GemmTile* table, int count, int M, int N, long long K, long long splits, double bytes) {
+  for (int i = 0; i < count; ++i) {
+    const double c = tile_cost(table[i], M, N, K, splits, bytes);
+    if (c >= 0.0 && (!best || c < *cost)) {
+      best = &table[i];
+      *cost = c;
+    }
+  }
+  return best;
 }
 
-// Non-temporal stores of C in gemm_bf16_nt, measured on the paper's shapes (interleaved, one
-// process): they pay where C's rows are short and the product is bound by memory traffic (442368 x
-// 448 x 192: +11 %, 589824 x 256 x 128: +3 %) and where a long contraction makes C a small part of
-// the traffic that should not displace operand panels in the L2 (8192 x 8192 x 8192 / 16384: +3 %);
-// elsewhere they cost (8192 x 8192 x 1024: -8 %, 2048 x 64512 x 256: -9 %, 589824 x 512 x 2048:
-// -5 %), and in gemm_bf16_nn they cost at every size tried (-2 .. -3 %), so that entry keeps plain stores.
-int stream_c_pays(int M, int N, int K) {
-  (void)M;
-  return ((N <= 512 && K <= 256) || K >= 8192) ? 1 : 0;
+double gemm_bytes(int M, int N, int K) { return 2.0 * ((double)M * K + (double)N * K + (double)M * N); }
+
+const GemmTile* choose_nt(int M, int N, int K, double* cost) {
+  int n1 = 0, n2 = 0;
+  const GemmTile* t1 = gemm_bf16_nt_tiles(&n1);
+  const GemmTile* t2 = gemm_wavek_nt_tiles(&n2);
+  const GemmTile* best = cheapest(nullptr, cost, t1, n1, M, N, K, 1, gemm_bytes(M, N, K));
+  return cheapest(best, cost, t2, n2, M, N, K, 1, gemm_bytes(M, N, K));
+}
+
+const GemmTile* choose_nn(int M, int N, int K, double* cost) {
+  int n1 = 0, n2 = 0;
+  const GemmTile* t1 = gemm_bf16_nn_tiles(&n1);
+  const GemmTile* t2 = gemm_wavek_nn_tiles(&n2);
+  const GemmTile* best = cheapest(nullptr, cost, t1, n1, M, N, K, 1, gemm_bytes(M, N, K));
+  return cheapest(best, cost, t2, n2, M, N, K, 1, gemm_bytes(M, N, K));
+}
+
+// Non-temporal stores of C from 96 MB on: C then does not stay in the caches and should not displace
+// the operands in them.  Measured plain -> non-temporal with the tile chosen here: 442368 x 448 x 192
+// 161.6 -> 128.0 us, 2048 x 64512 x 256 113.2 -> 89.8, 46207 x 1250 x 384 (116 MB) 73.3 -> 60.4, 8192 x 8192 x
+// 1024 140 -> 133, nn 200336 x 1432 x 256 242 -> 198; below the line 5329 x 3495 x 160 (37 MB) 16.9 -> 18.7,
+// 300000 x 100 x 512 (60 MB) 83.5 -> 85.8, nn 2763 x 9272 x 128 (51 MB) 17.3 -> 19.2.
+int stream_c_pays(int M, int N) { return 2.0 * M * N >= 96e6 ? 1 : 0; }
+
+int launch_tile(const GemmTile* t, GemmParams& p, void* stream) {
+  if (!t) return ATTN_ERR_UNSUPPORTED;
+  p.tiles_m = (p.M + t->bm - 1) / t->bm;
+  p.tiles_n = (p.N + t->bn - 1) / t->bn;
+  return t->launch(p, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
 int run(const void* a, const void* b, void* c, int M, int N, int K, int variant, void* stream) {
   if (!a || !b || !c) return ATTN_ERR_NULL;
   if (M <= 0 || N <= 0 || K <= 0) return ATTN_ERR_SHAPE;
   if (misaligned(a, 16) || misaligned(b, 16) || misaligned(c, 16)) return ATTN_ERR_SHAPE;
+  if (K % 32 != 0) return ATTN_ERR_UNSUPPORTED;
   int count = 0;
   const GemmVariant* table = gemm_bf16_nt_variants(&count);
-  if (K % 32 != 0) return ATTN_ERR_UNSUPPORTED;
-  if (variant == -1) variant = choose(M, N, K, table, count);
-  if (variant < 0 || variant >= count) return ATTN_ERR_UNSUPPORTED;
-  const GemmVariant& v = table[variant];
-  if (K % v.bk != 0 || K % v.kmult != 0) return ATTN_ERR_UNSUPPORTED;
+  if (variant < -1 || variant >= count) return ATTN_ERR_UNSUPPORTED;
   // per-lane offsets inside an operand panel are 32-bit: 256 rows of K bf16
   if ((long long)K * 2 * 256 >= (1ll << 31)) return ATTN_ERR_UNSUPPORTED;
   GemmParams p;
   p.a = a; p.b = b; p.c = c;
   p.M = M; p.N = N; p.K = K;
+  p.stream_c = stream_c_pays(M, N);
+  if (variant < 0) {
+    double cost = 0.0;
+    return launch_tile(choose_nt(M, N, K, &cost), p, stream);
+  }
+  const GemmVariant& v = table[variant];
+  if (K % v.bk != 0 || K % v.kmult != 0) return ATTN_ERR_UNSUPPORTED;
   p.tiles_m = (M + v.bm - 1) / v.bm;
   p.tiles_n = (N + v.bn - 1) / v.bn;
   if ((long long)p.tiles_m * p.tiles_n > 0x7fffffffll) return ATTN_ERR_UNSUPPORTED;
-  p.stream_c = stream_c_pays(M, N, K);
   return v.launch(p, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
@@ -72,17 +103,12 @@ int run_nn(const void* a, const void* b, void* c, int M, int N, int K, void* str
   if (misaligned(a, 16) || misaligned(b, 16) || misaligned(c, 16)) return ATTN_ERR_SHAPE;
   if (K % 32 != 0 || N % 8 != 0) return ATTN_ERR_UNSUPPORTED;
   if ((long long)K * 2 * 256 >= (1ll << 31) || (long long)N * 2 * 64 >= (1ll << 31)) return ATTN_ERR_UNSUPPORTED;
-  int count = 0;
-  const GemmVariant* table = gemm_bf16_nn_variants(&count);
-  const long long tiles256 = (long long)((M + 255) / 256) * ((N + 255) / 256);
-  const GemmVariant& v = table[tiles256 >= 200 ? 0 : 1];
   GemmParams p;
   p.a = a; p.b = b; p.c = c;
   p.M = M; p.N = N; p.K = K;
-  p.tiles_m = (M + v.bm - 1) / v.bm;
-  p.tiles_n = (N + v.bn - 1) / v.bn;
-  if ((long long)p.tiles_m * p.tiles_n > 0x7fffffffll) return ATTN_ERR_UNSUPPORTED;
-  return v.launch(p, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
+  p.stream_c = stream_c_pays(M, N);
+  double cost = 0.0;
+  return launch_tile(choose_nn(M, N, K, &cost), p, stream);
 }
 
 int run_splitk(const void* a, const void* b, void* c, int M, int N, int K, int splits, float* workspace, void* stream) {

@@ -113,12 +113,12 @@ struct GemmCfg {
   static constexpr int NLDA = BM * NCH / NT, NLDB = BN * NCH / NT;  // direct-to-LDS loads per thread and stage
   static constexpr int LPS = NLDA + NLDB;
   static constexpr int NKK = BK / 16;
-  static constexpr int LPP = LPS / NKK;  // loads issued per k-step
+  static constexpr int LPP = (LPS + NKK - 1) / NKK;  // loads issued per k-step, at most
   static constexpr int PITCH = BN * 2 + 16;  // bytes per row of the finished tile staged in LDS (gemm_store_staged)
   static constexpr int LDS_BYTES = NSTAGE * STAGEB > BM * PITCH ? NSTAGE * STAGEB : BM * PITCH;
   static_assert(LDS_BYTES <= 160 * 1024, "ring does not fit the LDS");
   static_assert((NSTAGE - 1) * LPS <= 63, "vmcnt field");
-  static_assert(NSTAGE >= 2 && NKK % 2 == 0 && LPS % NKK == 0 && NLDA >= 1 && NLDB >= 1, "pipeline shape");
+  static_assert(NSTAGE >= 2 && NKK % 2 == 0 && NLDA >= 1 && NLDB >= 1, "pipeline shape");
 };
 
 // BKN: the second operand is stored [K, N] (row-major, N contiguous) instead of [N, K].  Its tile is
@@ -128,6 +128,9 @@ template <int WM, int WN, int BK, int NSTAGE, int MINW, bool BKN>
 __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p) {
   using C = GemmCfg<WM, WN, BK, NSTAGE>;
   constexpr int ROWBB = C::BN * 2, NCHB = ROWBB / 16;  // [K,N] layout: bytes and 16-byte chunks per tile row
+  // the four k rows that the transposing read takes together land in different 64-byte groups of the
+  // 256-byte bank line (128-byte rows: two rows share a line)
+  auto swz_b = [](int r) __attribute__((always_inline)) { return NCHB >= 16 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; };
   constexpr int ROWB = C::ROWB, NCH = C::NCH, TILEA = C::TILEA, STAGEB = C::STAGEB, NKK = C::NKK;
   constexpr int NLDA = C::NLDA, NLDB = C::NLDB, LPS = C::LPS, LPP = C::LPP;
 
@@ -156,10 +159,9 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
       const int row = is_a ? min(m0 + r, M - 1) - m0 : min(n0 + r, N - 1) - n0;
       g_off[it] = (uint32_t)row * (uint32_t)rowbytes + c * 16;
     } else {
-      // [K,N] tile: k row r, LDS chunk s % NCHB holds the row's chunk XOR ((r & 3) << 2) (rows that the
-      // transposing read takes together land in different 64-byte groups); columns past N re-read
+      // [K,N] tile: k row r, LDS chunk s % NCHB holds the row's chunk XOR swz_b(r); columns past N re-read
       // the row's last 8 (N is a multiple of 8)
-      const int r = s / NCHB, c = (s % NCHB) ^ ((r & 3) << 2);
+      const int r = s / NCHB, c = (s % NCHB) ^ swz_b(r);
       const int col = min(n0 + c * 8, N - 8) - n0;
       g_off[it] = (uint32_t)r * (uint32_t)(N * 2) + col * 2;
     }
@@ -174,12 +176,26 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
     else attn_lds_dma16(b_tile + (size_t)ks * b_step, g_off[it], lds_wave + slot * STAGEB + TILEA + (it - NLDA) * C::NT * 16);
   };
 
-  const int nk = K / BK;
+  // K may leave half a stage of 64 (TAIL): the upper half of its rows' 128 bytes re-reads the lower one
+  // and is not contracted
+  constexpr bool TAIL = BK == 64 && !BKN;
+  const int nfull = K / BK;                      // whole stages
+  const int nk = TAIL ? (K + BK - 1) / BK : nfull;
+  auto issue_any = [&](int ks, int slot, int it) __attribute__((always_inline)) {
+    if (TAIL && ks == nfull) {
+      const int s = (it < NLDA ? it : it - NLDA) * C::NT + tid;
+      const int c = (s % NCH) ^ attn_swz_k<ROWB>(s / NCH);
+      attn_lds_dma16((it < NLDA ? a_tile : b_tile) + (size_t)ks * ROWB, g_off[it] - (c >= 4 ? 64 : 0),
+                     lds_wave + slot * STAGEB + (it < NLDA ? it * C::NT * 16 : TILEA + (it - NLDA) * C::NT * 16));
+    } else {
+      issue_load(ks, slot, it);
+    }
+  };
 #pragma unroll
   for (int s = 0; s < NSTAGE; ++s)
     if (s < nk) {
 #pragma unroll
-      for (int it = 0; it < LPS; ++it) issue_load(s, s, it);
+      for (int it = 0; it < LPS; ++it) issue_any(s, s, it);
     }
 
   // ---- consumer role: fragment addresses inside a stage (row block 0 of this wave's quarter)
@@ -201,7 +217,7 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
       for (int e = 0; e < 2; ++e) {
         const int krow = 8 * h + 4 * e + (s16 >> 2);
         const int chunk = (wn * 32 * WN + nb * 32) / 8 + chalf * 2 + ((s16 & 3) >> 1);
-        tb[nb][e] = TILEA + krow * ROWBB + ((chunk ^ ((krow & 3) << 2)) << 4) + ((s16 & 1) << 3);
+        tb[nb][e] = TILEA + krow * ROWBB + ((chunk ^ swz_b(krow)) << 4) + ((s16 & 1) << 3);
       }
   }
 
@@ -274,7 +290,11 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
         read_frags(nxt, base, kk + 1);
         if (STEADY || (ks >= 1 && ks - 1 + NSTAGE < nk)) {
 #pragma unroll
-          for (int i = 0; i < LPP; ++i) issue_load(ks - 1 + NSTAGE, pslot, (kk + 1) * LPP + i);
+          for (int i = 0; i < LPP; ++i)
+            if ((kk + 1) * LPP + i < LPS) {
+              if constexpr (STEADY) issue_load(ks - 1 + NSTAGE, pslot, (kk + 1) * LPP + i);
+              else issue_any(ks - 1 + NSTAGE, pslot, (kk + 1) * LPP + i);
+            }
         }
       } else if (STEADY || ks + 1 < nk) {
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of the slot about to be refilled are done
@@ -284,11 +304,16 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
         read_frags(nxt, nslot * STAGEB, 0);
         if (STEADY || ks + NSTAGE < nk) {
 #pragma unroll
-          for (int i = 0; i < LPP; ++i) issue_load(ks + NSTAGE, slot, i);
+          for (int i = 0; i < LPP; ++i) {
+            if constexpr (STEADY) issue_load(ks + NSTAGE, slot, i);
+            else issue_any(ks + NSTAGE, slot, i);
+          }
         }
       }
-      mfmas(cur);
-      interleave();
+      if (STEADY || !TAIL || kk < NKK / 2 || ks < nfull) {
+        mfmas(cur);
+        interleave();
+      }
     }
   };
 
@@ -298,7 +323,7 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
     ks = 1;
     slot = NSTAGE > 1 ? 1 : 0;
   }
-  for (; ks + NSTAGE < nk; ++ks) {
+  for (; ks + NSTAGE < nfull; ++ks) {  // (what a steady stage requests is a whole stage)
     stage(ks, slot, std::true_type{});
     slot = slot == NSTAGE - 1 ? 0 : slot + 1;
   }
@@ -593,10 +618,31 @@ const GemmVariant* gemm_bf16_nt_variants(int* count) {
   return table;
 }
 
-const GemmVariant* gemm_bf16_nn_variants(int* count) {
-  static const GemmVariant table[] = {
-      {"bf16 nn 256x256x32 ring4", 256, 256, 32, 32, launch<4, 4, 32, 4, 1, true>},
-      {"bf16 nn 128x128x32 ring4", 128, 128, 32, 32, launch<2, 2, 32, 4, 2, true>},
+// The rates (GemmTile) are a fit to about 70 shapes per layout, M 1 .. 590000, N 32 .. 65536, K 64 .. 16384.
+const GemmTile* gemm_bf16_nt_tiles(int* count) {
+  static const GemmTile table[] = {
+      {256, 256, 32, 1, 6.1f, 0.58f, 5.5f, launch<4, 4, 32, 4, 1>},
+      {256, 128, 64, 1, 4.4f, 0.62f, 5.5f, launch<4, 2, 64, 3, 1>},
+      {128, 256, 64, 1, 4.1f, 0.65f, 5.5f, launch<2, 4, 64, 3, 1>},
+      {128, 256, 32, 2, 1.8f, 0.42f, 5.5f, launch<2, 4, 32, 3, 2>},
+      {128, 128, 64, 1, 2.7f, 0.39f, 5.5f, launch<2, 2, 64, 4, 1>},
+      {64, 128, 64, 2, 0.7f, 0.30f, 5.5f, launch<1, 2, 64, 3, 2>},
+      {64, 128, 64, 3, 0.1f, 0.42f, 5.5f, launch<1, 2, 64, 2, 3>},
+      {64, 128, 32, 3, 0.3f, 0.20f, 5.5f, launch<1, 2, 32, 4, 3>},
+      {64, 64, 32, 5, 0.0f, 0.14f, 5.5f, launch<1, 1, 32, 4, 4>},
+  };
+  *count = (int)(sizeof(table) / sizeof(table[0]));
+  return table;
+}
+
+const GemmTile* gemm_bf16_nn_tiles(int* count) {
+  static const GemmTile table[] = {
+      {256, 256, 32, 1, 5.0f, 0.55f, 5.5f, launch<4, 4, 32, 4, 1, true>},
+      {256, 128, 32, 2, 2.4f, 0.35f, 5.5f, launch<4, 2, 32, 3, 2, true>},
+      {128, 256, 32, 2, 1.9f, 0.34f, 5.5f, launch<2, 4, 32, 3, 2, true>},
+      {128, 128, 32, 2, 1.1f, 0.22f, 5.5f, launch<2, 2, 32, 4, 2, true>},
+      {64, 256, 32, 2, 0.9f, 0.25f, 5.5f, launch<1, 4, 32, 4, 2, true>},
+      {64, 128, 32, 3, 0.3f, 0.16f, 5.5f, launch<1, 2, 32, 4, 3, true>},
   };
   *count = (int)(sizeof(table) / sizeof(table[0]));
   return table;

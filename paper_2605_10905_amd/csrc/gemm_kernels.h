@@ -23,7 +23,19 @@ struct GemmVariant {
   int (*launch)(const GemmParams& p, hipStream_t stream);
 };
 
-const GemmVariant* gemm_bf16_nt_variants(int* count);
-const GemmVariant* gemm_bf16_nn_variants(int* count);  // second operand stored [K, N]
+const GemmVariant* gemm_bf16_nt_variants(int* count);  // what gemm_bf16_nt_variant offers
+// A tile of the library's own choice (gemm_api.hip): one workgroup of it takes about
+// fixed_us + ceil(K / step) * step_us, `per_cu` of them share a CU.
+struct GemmTile {
+  int bm, bn, step, per_cu;
+  float fixed_us, step_us;
+  float tb_s;  // rate at which it moves operands and result when they are the bound
+  int (*launch)(const GemmParams& p, hipStream_t stream);
+};
+const GemmTile* gemm_bf16_nt_tiles(int* count);   // ring in LDS, shared by the waves of a workgroup
+const GemmTile* gemm_bf16_nn_tiles(int* count);
+const GemmTile* gemm_wavek_nt_tiles(int* count);  // waves split k; also writes split-K partial tiles
+const GemmTile* gemm_wavek_nn_tiles(int* count);
+
 // 256 x 256 tiles, K split over p.splits workgroups per tile (p.klen a multiple of 64), then the sum
 int gemm_bf16_nt_splitk_launch(const GemmParams& p, hipStream_t stream);

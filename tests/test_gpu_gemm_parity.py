@@ -142,6 +142,18 @@ def test_gemm_full_size_sampled(name):
     print(check(c, a, b, f"gemm {name}", rows=rows), flush=True)
 
 
+# outputs of a few tiles: edges of the 16-, 32- and 64-row tiles whose waves split k, k shorter than one
+# chunk per wave, a last half chunk (K = 32 mod 64), many chunks per wave; and one shape per ring tile
+@pytest.mark.parametrize("M,N,K", [(1, 16, 32), (15, 17, 96), (33, 15, 160), (17, 33, 4128), (65, 64, 9952), (63, 300, 2080), (200, 1, 8224),
+                                   (300, 328, 2016), (1030, 1000, 1056), (129, 4104, 224), (2050, 1992, 352), (5000, 72, 544)])
+def test_gemm_tile_choice_edges(M, N, K):
+    a, b = wl.make_gemm_inputs(1500 + M + N + K, M, N, K)
+    print(f"gemm tile choice {M}x{N}x{K}", flush=True)
+    check(run_gemm(a, b), a, b, f"gemm tile choice {M}x{N}x{K}")
+    if N % 8 == 0:
+        check(run_gemm_nn(a, np.ascontiguousarray(b.T)), a, b, f"gemm nn tile choice {M}x{N}x{K}")
+
+
 # ---- split-K ------------------------------------------------------------------------------------------
 def run_gemm_splitk(a_bits, b_bits, splits, poison=float("nan")):
     import paper_2605_10905_amd as A
