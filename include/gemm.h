@@ -48,14 +48,15 @@ int gemm_bf16_nn(const void* a, const void* b, void* c, int M, int N, int K, voi
 /*
  * gemm_bf16_nt_splitk -- gemm_bf16_nt for outputs with too few 256 x 256 tiles to occupy the
  * chip while K is long (the large-K rows of the paper's appendix A GEMM shape table): every
- * output tile is computed by `splits` workgroups, each contracting one slice of k in fp32, and a
- * second kernel adds the slices in index order and rounds to bfloat16.  Deterministic.
- *   splits     1 .. 64 slices per tile; slices are whole multiples of 64 in k, so fewer may be
- *              used than asked for (a slice is never empty)
+ * output tile is computed by up to `splits` workgroups, each contracting one slice of k in fp32, and
+ * a second kernel adds the slices in index order and rounds to bfloat16.  Deterministic.
+ *   splits     1 .. 64 slices per tile, what the workspace holds; slices are whole multiples of 64 in
+ *              k and never empty, and the library uses fewer (or none: one kernel, the workspace is
+ *              not touched) where it expects that to be faster
  *   workspace  device, gemm_splitk_workspace_bytes(M, N, splits) bytes, 16-byte aligned, owned by
  *              the caller; contents on entry are irrelevant, contents on return unspecified
  *   K          positive multiple of 64 (ATTN_ERR_UNSUPPORTED otherwise)
- * Everything else, and the error behaviour, as for gemm_bf16_nt.  Two kernels are enqueued.
+ * Everything else, and the error behaviour, as for gemm_bf16_nt.  At most two kernels are enqueued.
  */
 int gemm_bf16_nt_splitk(const void* a, const void* b, void* c, int M, int N, int K, int splits,
                         float* workspace, void* stream);

@@ -120,15 +120,43 @@ int run_splitk(const void* a, const void* b, void* c, int M, int N, int K, int s
   GemmParams p;
   p.a = a; p.b = b; p.c = c;
   p.M = M; p.N = N; p.K = K;
-  p.tiles_m = (M + 255) / 256;
-  p.tiles_n = (N + 255) / 256;
-  // slices of whole 64-column steps, none empty
+  // `splits` is what the workspace holds, so any smaller number may be used: the waves of the small
+  // tiles split k among themselves already, and a slice more costs its partial tile twice over the
+  // memory.  The same estimate as above, plus the partial tiles (written and read at 4 TB/s) and the
+  // second launch (3 us), over 1, 2, 3, 4, 6, 9, ... slices and `splits` itself.  Measured, always 256 x 256
+  // tiles and `splits` slices -> this: 234 x 74 x 21504 67 -> 8.1 us, 896 x 761 x 12288 72 -> 35, 84 x 3775 x 40000
+  // 110 -> 79, 64 x 64 x 65536 57 -> 10; where the large tile stays, its XCD map (gemm_map.h): 2304 x 1024 x 65536
+  // 357 -> 335 us with the sum kernel.
   const int steps = K / 64;
-  p.klen = ((steps + splits - 1) / splits) * 64;
+  auto slice = [&](int s) { return ((steps + s - 1) / s) * 64; };  // whole 64-column steps, none empty
+  const GemmTile large = {256, 256, 32, 1, 6.1f, 0.58f, 5.5f, gemm_bf16_nt_splitk_launch};
+  int nwave = 0;
+  const GemmTile* const wave = gemm_wavek_nt_tiles(&nwave);
+  double best_cost = 0.0;
+  const GemmTile* best = choose_nt(M, N, K, &best_cost);
+  int best_splits = 1;
+  for (int s = 2; s <= splits; s = s == splits ? s + 1 : s + s / 2 < splits ? s + s / 2 : splits) {
+    const int used = (K + slice(s) - 1) / slice(s);
+    const double extra = 3.0 + 8.0 * used * M * N / 4e6;
+    double cost = 0.0;
+    const GemmTile* t = cheapest(nullptr, &cost, &large, 1, M, N, slice(s), used, gemm_bytes(M, N, K));
+    t = cheapest(t, &cost, wave, nwave, M, N, slice(s), used, gemm_bytes(M, N, K));
+    if (t && (!best || cost + extra < best_cost)) {
+      best_cost = cost + extra;
+      best = t;
+      best_splits = s;
+    }
+  }
+  if (best_splits == 1) {
+    p.stream_c = stream_c_pays(M, N);
+    return launch_tile(best, p, stream);
+  }
+  p.klen = slice(best_splits);
   p.splits = (K + p.klen - 1) / p.klen;
   p.partial = workspace;
-  if ((long long)p.tiles_m * p.tiles_n * p.splits > 0x7fffffffll) return ATTN_ERR_UNSUPPORTED;
-  return gemm_bf16_nt_splitk_launch(p, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
+  const int st = launch_tile(best, p, stream);
+  if (st != ATTN_OK) return st;
+  return gemm_splitk_sum_launch(p, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
 }  // namespace

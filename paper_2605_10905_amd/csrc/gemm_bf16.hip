@@ -381,9 +381,9 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
   const int lj = lane & 15, g = lane >> 4;
   const int wm = w >> 1, wn = w & 1;
 
-  const int ntile = p.tiles_m * p.tiles_n;
-  const int split = SPLITK ? (int)blockIdx.x / ntile : 0;
-  const GemmTileCoord tc = gemm_tile_coord_impl(SPLITK ? (int)blockIdx.x - split * ntile : (int)blockIdx.x, p.tiles_m, p.tiles_n);
+  int split = 0;
+  const GemmTileCoord tc = SPLITK ? gemm_tile_coord_split(blockIdx.x, p.tiles_m, p.tiles_n, p.splits, &split)
+                                  : gemm_tile_coord_impl(blockIdx.x, p.tiles_m, p.tiles_n);
   const int m0 = tc.tm * C::BM, n0 = tc.tn * C::BN;
   const int M = p.M, N = p.N, K = p.K;
   const size_t rowbytes = (size_t)K * 2;
@@ -567,24 +567,38 @@ int launch_m16(const GemmParams& p, hipStream_t stream) {
   return (int)hipGetLastError();
 }
 
-// c[i] = bf16(sum over splits of partial[s][i]), splits added in index order; 8 elements per thread
-__global__ void __launch_bounds__(256) gemm_splitk_sum_kernel(const float* __restrict__ partial, void* c, size_t total, int splits) {
-  const size_t i8 = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;
-  if (i8 >= total) return;
-  if ((total & 7) == 0) {
-    f32x4 lo = *(const f32x4*)(partial + i8), hi = *(const f32x4*)(partial + i8 + 4);
-    for (int s = 1; s < splits; ++s) {
-      lo += *(const f32x4*)(partial + (size_t)s * total + i8);
-      hi += *(const f32x4*)(partial + (size_t)s * total + i8 + 4);
+// c[i] = bf16(sum over splits of partial[s][i]), splits added in index order.  VEC: four consecutive
+// elements per thread (total a multiple of 4: every slice starts 16-byte aligned), else four
+// elements 256 apart, so that a wave reads whole lines either way; the loads of four slices are in
+// flight at a time.
+template <bool VEC>
+__global__ void __launch_bounds__(256) gemm_splitk_sum_kernel(const float* __restrict__ partial, __bf16* __restrict__ c, size_t total, int splits) {
+  const size_t i0 = (size_t)blockIdx.x * 1024 + (VEC ? threadIdx.x * 4 : threadIdx.x);
+  auto load = [&](int s) __attribute__((always_inline)) {
+    const float* const src = partial + (size_t)s * total;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (VEC) {
+      if (i0 < total) v = *(const f32x4*)(src + i0);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (i0 + 256 * t < total) v[t] = src[i0 + 256 * t];
     }
-    u32x4 out = {pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]), pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3])};
-    *(u32x4*)((__bf16*)c + i8) = out;
+    return v;
+  };
+  f32x4 sum = load(0);
+  int s = 1;
+  for (; s + 4 <= splits; s += 4) {
+    const f32x4 a = load(s), b = load(s + 1), d = load(s + 2), e = load(s + 3);
+    sum = (((sum + a) + b) + d) + e;
+  }
+  for (; s < splits; ++s) sum += load(s);
+  if constexpr (VEC) {
+    if (i0 < total) *(u32x2*)(c + i0) = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
   } else {
-    for (size_t i = i8; i < i8 + 8 && i < total; ++i) {
-      float v = partial[i];
-      for (int s = 1; s < splits; ++s) v += partial[(size_t)s * total + i];
-      ((__bf16*)c)[i] = (__bf16)v;
-    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (i0 + 256 * t < total) c[i0 + 256 * t] = (__bf16)sum[t];
   }
 }
 
@@ -598,8 +612,14 @@ int launch(const GemmParams& p, hipStream_t stream) {
 
 int gemm_bf16_nt_splitk_launch(const GemmParams& p, hipStream_t stream) {
   hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<32, 4, true>), dim3(p.tiles_m * p.tiles_n * p.splits), dim3(256), 0, stream, p);
+  return (int)hipGetLastError();
+}
+
+int gemm_splitk_sum_launch(const GemmParams& p, hipStream_t stream) {
   const size_t total = (size_t)p.M * p.N;
-  hipLaunchKernelGGL(gemm_splitk_sum_kernel, dim3((unsigned)((total + 2047) / 2048)), dim3(256), 0, stream, p.partial, p.c, total, p.splits);
+  const dim3 grid((unsigned)((total + 1023) / 1024));
+  if ((total & 3) == 0) hipLaunchKernelGGL(gemm_splitk_sum_kernel<true>, grid, dim3(256), 0, stream, p.partial, (__bf16*)p.c, total, p.splits);
+  else hipLaunchKernelGGL(gemm_splitk_sum_kernel<false>, grid, dim3(256), 0, stream, p.partial, (__bf16*)p.c, total, p.splits);
   return (int)hipGetLastError();
 }
 

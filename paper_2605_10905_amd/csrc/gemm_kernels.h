@@ -37,5 +37,7 @@ const GemmTile* gemm_bf16_nn_tiles(int* count);
 const GemmTile* gemm_wavek_nt_tiles(int* count);  // waves split k; also writes split-K partial tiles
 const GemmTile* gemm_wavek_nn_tiles(int* count);
 
-// 256 x 256 tiles, K split over p.splits workgroups per tile (p.klen a multiple of 64), then the sum
+// 256 x 256 tiles, K split over p.splits workgroups per tile (p.klen a multiple of 64), without the sum
 int gemm_bf16_nt_splitk_launch(const GemmParams& p, hipStream_t stream);
+// c = bf16(sum of the p.splits partial tiles)
+int gemm_splitk_sum_launch(const GemmParams& p, hipStream_t stream);

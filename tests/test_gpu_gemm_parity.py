@@ -174,6 +174,11 @@ SPLITK = [(256, 256, 512, 2), (300, 520, 4032, 4), (513, 257, 1024, 8), (64, 7, 
           (512, 384, 8192, 16), (33, 1001, 4096, 5)]
 
 
+# outputs of a few small tiles (waves split a slice's k further), the sum over an element count that is
+# not a multiple of four, more slices than are worth using
+SPLITK += [(16, 16, 2304, 5), (33, 65, 2112, 7), (100, 300, 8192, 16), (77, 1031, 20032, 15), (700, 900, 4096, 4)]
+
+
 @pytest.mark.parametrize("M,N,K,splits", SPLITK)
 def test_gemm_splitk_shapes(M, N, K, splits):
     a, b = wl.make_gemm_inputs(700 + M + N + K, M, N, K)
