@@ -117,7 +117,6 @@ int bwd_run(const void* q, const void* k, const void* v, const void* o, const vo
   p.q = q; p.k = k; p.v = v; p.o = o; p.dout = dout; p.lse = lse;
   p.dq = dq; p.dk = dk; p.dv = dv; p.ws = workspace;
   p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.N = N;
-  p.T = (N + 255) / 256;
   p.Npad = (N + 63) / 64 * 64;
   p.causal = causal ? 1 : 0;
   p.scale_log2 = scale * kLog2e;

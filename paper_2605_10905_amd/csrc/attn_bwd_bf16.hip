@@ -11,11 +11,11 @@
 // Two kernels, neither of which uses atomics or a reduction across workgroups, so the result is
 // deterministic and no gradient needs an fp32 accumulation buffer in memory:
 //
-//   * attn_bwd_dq_kernel: a workgroup owns 256 query rows (Q and dO rows stationary in registers
+//   * attn_bwd_dq_kernel: a workgroup owns 256 query rows (128 when the launch is small; Q and dO rows stationary in registers
 //     as MFMA B operands, one query per lane, exactly the forward layout) and streams K/V tiles:
 //     S^T = K Q^T, dP^T = V dO^T, dS^T in registers, dQ^T += K^T dS^T.  It also writes the two
 //     per-row vectors the other kernel needs, delta and lse * log2(e), into the workspace.
-//   * attn_bwd_dkv_pipe_kernel: a workgroup owns 128 keys (K and V rows stationary, one key per
+//   * attn_bwd_dkv_pipe_kernel: a workgroup owns 128 keys (64 when the launch is small; K and V rows stationary, one key per
 //     lane) and streams Q/dO tiles of every query head of its group: S = Q K^T, dP = dO V^T, P,
 //     dS = P * (dP - delta), dV^T += dO^T P, dK^T += Q^T dS.
 //   S and dP are therefore computed twice, 7 matrix products per tile pair instead of the minimal
@@ -105,11 +105,16 @@ __device__ __forceinline__ void store_transposed(const f32x16 (&acc)[NCB], float
 // =====================================================================================================
 // dQ (and the workspace vectors)
 // =====================================================================================================
-template <int D, bool CAUSAL>
+// KS = 1: the 8 waves own 32 queries each and compute both 32-key blocks of every tile.
+// KS = 2, for launches that leave CUs idle: a workgroup owns 128 queries; waves w and w + 4 share 32
+// of them, one takes the first key block of every tile, the other the second, and the two partial
+// dQ are added through LDS at the end: twice the workgroups, half the serial chain.
+template <int D, bool CAUSAL, int KS>
 __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams p) {
   using C = BwdCommon<D>;
   constexpr int NKK = C::NKK, NCB = C::NCB, ROWB = C::ROWB, NCH = C::NCH, TILEB = C::TILEB, SUBB = C::SUBB, NSLOT = C::NSLOT;
-  constexpr int NLD = C::NLD, NT = C::NT, BN = C::BN, BM = C::BM;
+  constexpr int NLD = C::NLD, NT = C::NT, BN = C::BN, NQW = C::NWAVES / KS, BM = NQW * 32;
+  static_assert(KS == 1 || (KS == 2 && NQW * NCB * 2048 <= 2 * NSLOT * TILEB), "the exchanged halves of dQ fit the ring");
 
   __shared__ __attribute__((aligned(1024))) char smem_raw[2 * NSLOT * TILEB];
   LDS_AS char* const smem = (LDS_AS char*)smem_raw;
@@ -122,7 +127,8 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
   const int N = p.N;
   const int hk = tc.hq / (p.Hq / p.Hkv);
   const int q0 = tc.t * BM;
-  const int wq0 = q0 + w * 32;
+  const int kg = KS == 1 ? 0 : w / NQW;  // which key block of a tile this wave computes (KS = 2)
+  const int wq0 = q0 + (KS == 1 ? w : w % NQW) * 32;
   const bool wave_valid = wq0 < N;
   const int qrow = wq0 + qi;
 
@@ -178,7 +184,7 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
   const float lse2 = p.lse[(size_t)(tc.b * p.Hq + tc.hq) * N + min(qrow, N - 1)] * kLog2e;
   // workspace for the key-side kernels, padded to whole 64-row tiles: rows past N get a
   // statistic of +inf (their probabilities come out as zero) and delta = 0
-  if (h == 0 && qrow < p.Npad) {
+  if (kg == 0 && h == 0 && qrow < p.Npad) {
     float* const wsrow = p.ws + (size_t)(tc.b * p.Hq + tc.hq) * 2 * p.Npad;
     wsrow[qrow] = qrow < N ? lse2 : INFINITY;
     wsrow[p.Npad + qrow] = qrow < N ? delta : 0.f;
@@ -267,7 +273,8 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
     const int pslot = slot == 0 ? NSLOT - 1 : slot - 1;  // slot of tile j+2 = slot of tile j-1
     if (j + 2 < nt) issue_tile(j + 2, pslot);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int i = 0; i < 2 / KS; ++i) {
+      const int kb = KS == 1 ? i : kg;
       const int key0 = j * BN + kb * 32;
       if (wave_valid && key0 < kv_end && (!CAUSAL || key0 <= wlast)) block(key0, slot * TILEB + kb * SUBB);
     }
@@ -277,7 +284,34 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
     slot = slot == NSLOT - 1 ? 0 : slot + 1;
   }
 
-  store_transposed<NCB>(acc, p.scale, (char*)p.dq + qoff + (size_t)min(qrow, N - 1) * ROWB, h, qrow < N);
+  char* const dq_row = (char*)p.dq + qoff + (size_t)min(qrow, N - 1) * ROWB;
+  if constexpr (KS == 1) {
+    store_transposed<NCB>(acc, p.scale, dq_row, h, qrow < N);
+  } else {
+    // every wave is past the loop's last barrier, so the ring is free: the two waves of a query block
+    // exchange halves of their partial dQ (each gives away the columns the other one finishes)
+    constexpr int NH = NCB / 2;
+    LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((kg ^ 1) * NQW + w % NQW) * (NH * 4) * 64 + lane;
+    LDS_AS const f32x4* const take = (LDS_AS const f32x4*)smem + (kg * NQW + w % NQW) * (NH * 4) * 64 + lane;
+    f32x16 mine[NH];
+#pragma unroll
+    for (int cb = 0; cb < NH; ++cb) {
+      const f32x16 other = kg ? acc[cb] : acc[NH + cb];
+      mine[cb] = kg ? acc[NH + cb] : acc[cb];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) give[(cb * 4 + a) * 64] = f32x4{other[4 * a], other[4 * a + 1], other[4 * a + 2], other[4 * a + 3]};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int cb = 0; cb < NH; ++cb)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 o = take[(cb * 4 + a) * 64];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[cb][4 * a + r] += o[r];
+      }
+    store_transposed<NH>(mine, p.scale, dq_row + kg * NH * 64, h, qrow < N);
+  }
 }
 
 // =====================================================================================================
@@ -336,11 +370,17 @@ struct BwdPipe {
   static constexpr int aslot(int a) { return vslot(4 * a) - 6 > 0 ? vslot(4 * a) - 6 : 0; }  // slot that reads the statistics of rows 4a..4a+3
 };
 
-template <int D, bool CAUSAL>
+// QS = 1: each wave owns 32 of the workgroup's 128 keys and takes both 32-query blocks of every tile.
+// QS = 2, for launches that leave CUs idle: a workgroup owns 64 keys; waves w and w + 2 share 32 of
+// them, one takes the first query block of every tile, the other the second (its "previous" and
+// "next" blocks are those of the neighbouring tiles), and at the end one finishes dV and the other
+// dK with the partner's partial sum, exchanged through LDS.
+template <int D, bool CAUSAL, int QS>
 __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwdParams p) {
   using C = BwdPipe<D>;
   constexpr int NKK = C::NKK, NCB = C::NCB, ROWB = C::ROWB, NCH = C::NCH, TILEB = C::TILEB, SUBB = C::SUBB, NSLOT = C::NSLOT;
-  constexpr int NLD = C::NLD, NT = C::NT, BN = C::BN, BM = C::BM, NM = C::NM, RA = C::RA;
+  constexpr int NLD = C::NLD, NT = C::NT, BN = C::BN, NKW = C::NWAVES / QS, BM = NKW * 32, NM = C::NM, RA = C::RA;
+  static_assert(QS == 1 || QS == 2, "a tile has two query blocks");
 
   __shared__ __attribute__((aligned(1024))) char smem_raw[C::LDS_BYTES];
   LDS_AS char* const smem = (LDS_AS char*)smem_raw;
@@ -349,14 +389,15 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int ki = lane & 31, h = lane >> 5;
 
-  const int T128 = (p.N + BM - 1) / BM;
-  AttnTileCoord tc = attn_tile_coord_impl(blockIdx.x, p.B, p.Hkv, p.Hkv, T128, CAUSAL ? 1 : 0);
-  if (CAUSAL) tc.t = T128 - 1 - tc.t;  // key tile 0 is the heaviest: first
+  const int T = (p.N + BM - 1) / BM;
+  AttnTileCoord tc = attn_tile_coord_impl(blockIdx.x, p.B, p.Hkv, p.Hkv, T, CAUSAL ? 1 : 0);
+  if (CAUSAL) tc.t = T - 1 - tc.t;  // key tile 0 is the heaviest: first
   const int N = p.N;
   const int G = p.Hq / p.Hkv;
   const int g = tc.hq;
   const int k0 = tc.t * BM;
-  const int wk0 = k0 + w * 32;  // first key of this wave
+  const int qg = QS == 1 ? 0 : w / NKW;                   // which query block of a tile this wave computes (QS = 2)
+  const int wk0 = k0 + (QS == 1 ? w : w % NKW) * 32;  // first key of this wave
   const int krow = wk0 + ki;
 
   const size_t koff = ((size_t)(tc.b * p.Hkv + g) * N) * ROWB;
@@ -440,7 +481,7 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   uint32_t raddr[2][NKK];
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) {
-    raddr[0][kk] = ki * ROWB + (((2 * kk + h) ^ swz_rt<ROWB>(ki)) << 4);
+    raddr[0][kk] = qg * SUBB + ki * ROWB + (((2 * kk + h) ^ swz_rt<ROWB>(ki)) << 4);
     raddr[1][kk] = raddr[0][kk] + C::T2BASE;
   }
   uint32_t taddr[2][NCB][2];
@@ -452,11 +493,11 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
       for (int e = 0; e < 2; ++e) {
         const int row = 8 * e + 4 * h + (s >> 2);
         const int chunk = cb * 4 + chalf * 2 + ((s & 3) >> 1);
-        taddr[0][cb][e] = row * ROWB + ((chunk ^ swz_rt<ROWB>(row)) << 4) + ((s & 1) << 3);
+        taddr[0][cb][e] = qg * SUBB + row * ROWB + ((chunk ^ swz_rt<ROWB>(row)) << 4) + ((s & 1) << 3);
         taddr[1][cb][e] = taddr[0][cb][e] + C::T2BASE;
       }
   }
-  const uint32_t auxaddr = C::AUXBASE + 16 * h;
+  const uint32_t auxaddr = C::AUXBASE + qg * 128 + 16 * h;
   // `t2` selects the tensor (0: Q slots, 1: dO slots), `off` is the block's offset inside them
   auto row_operand = [&](int t2, int off, int kk) __attribute__((always_inline)) { return *(LDS_AS u32x4*)(smem + raddr[t2][kk] + off); };
   auto tr_operand = [&](int t2, int off, int cb, int kc) __attribute__((always_inline)) {
@@ -544,14 +585,15 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
     }
   };
 
-  // the block "before the first" lives in the last half of slot 3: zeros, so that its gradient
-  // products (with P = dS = 0) add exact zeros
+  // the block "before the first" lives in the last half of slot 3 (QS = 2: a wave's half of it):
+  // zeros, so that its gradient products (with P = dS = 0) add exact zeros
+  constexpr int BEFORE = 3 * TILEB + (QS == 1 ? SUBB : 0);
   {
     const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < SUBB / (NT * 16); ++i) {
-      *(LDS_AS u32x4*)(smem + 3 * TILEB + SUBB + (i * NT + tid) * 16) = z;
-      *(LDS_AS u32x4*)(smem + C::T2BASE + 3 * TILEB + SUBB + (i * NT + tid) * 16) = z;
+    for (int i = 0; i < (4 * TILEB - BEFORE) / (NT * 16); ++i) {
+      *(LDS_AS u32x4*)(smem + BEFORE + (i * NT + tid) * 16) = z;
+      *(LDS_AS u32x4*)(smem + C::T2BASE + BEFORE + (i * NT + tid) * 16) = z;
     }
   }
   if (nt > 2) ATTN_WAIT_VMCNT(2 * LPT);
@@ -575,12 +617,25 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
 #pragma unroll
   for (int t = 0; t < 2; ++t) ppb[t] = pdb[t] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int m = 0; m < RA; ++m) pre[m] = grad_operand(3 * TILEB + SUBB, m);
+  for (int m = 0; m < RA; ++m) pre[m] = grad_operand(BEFORE, m);
 
   int qt = qt0;
   // tile j lives in slot j % 4 = S
   auto tile = [&](auto S, int j) __attribute__((always_inline)) {
     constexpr int s = decltype(S)::value;
+    if constexpr (QS == 2) {
+      // one step per tile; in front of it: tile j+1 has landed, every wave is done with tile j-2
+      // (tiles 0, 1 and 2 are requested by the prologue, later ones one step ahead)
+      ATTN_WAIT_VMCNT(0);
+      attn_wg_barrier();
+      if (j >= 1 && j + 2 < nt) issue_next((s + 2) & 3);
+      constexpr int o = s * TILEB, op = ((s + 3) & 3) * TILEB, on = ((s + 1) & 3) * TILEB;
+      const int q0b = qt * BN + qg * 32;
+      if constexpr (s & 1) step(sb, dpb, sa, dpa, ppb, pdb, ppa, pda, ic<op>{}, ic<o>{}, ic<on>{}, ic<s * 512>{}, q0b);
+      else step(sa, dpa, sb, dpb, ppa, pda, ppb, pdb, ic<op>{}, ic<o>{}, ic<on>{}, ic<s * 512>{}, q0b);
+      if (++qt == nqt_all) qt = qt0;
+      return;
+    }
     constexpr int b0 = s * TILEB, b1 = b0 + SUBB, bp = ((s + 3) & 3) * TILEB + SUBB, bn = ((s + 1) & 3) * TILEB;
     const int q0b = qt * BN;
     step(sa, dpa, sb, dpb, ppa, pda, ppb, pdb, ic<bp>{}, ic<b0>{}, ic<b1>{}, ic<s * 512>{}, q0b);
@@ -607,37 +662,83 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
     }
   }
   // epilogue: the gradient products of the last block (its first RA operands are already here)
-  {
+  if constexpr (QS == 1) {
     const int last = ((nt - 1) & 3) * TILEB + SUBB;
 #pragma unroll
     for (int i = RA; i < C::NG; ++i) grad_mfma(i, grad_operand(last, i), ppb, pdb);
 #pragma unroll
     for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], ppb, pdb);
+    const size_t roff = koff + (size_t)min(krow, N - 1) * ROWB;
+    store_transposed<NCB>(acc_dv, 1.0f, (char*)p.dv + roff, h, krow < N);
+    store_transposed<NCB>(acc_dk, p.scale, (char*)p.dk + roff, h, krow < N);
+  } else {
+    const int last = ((nt - 1) & 3) * TILEB;
+    const bool odd = ((nt - 1) & 1) != 0;  // (the parity of the last step says which registers hold P and dS)
+    if (!odd) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        ppb[t] = ppa[t];
+        pdb[t] = pda[t];
+      }
+    }
+#pragma unroll
+    for (int i = RA; i < C::NG; ++i) grad_mfma(i, grad_operand(last, i), ppb, pdb);
+#pragma unroll
+    for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], ppb, pdb);
+    const size_t roff = koff + (size_t)min(krow, N - 1) * ROWB;
+    __syncthreads();  // no wave reads the ring any more
+    LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((qg ^ 1) * NKW + w % NKW) * (NCB * 4) * 64 + lane;
+    LDS_AS const f32x4* const take = (LDS_AS const f32x4*)smem + (qg * NKW + w % NKW) * (NCB * 4) * 64 + lane;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      const f32x16 other = qg ? acc_dv[cb] : acc_dk[cb];
+      if (qg) acc_dv[cb] = acc_dk[cb];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) give[(cb * 4 + a) * 64] = f32x4{other[4 * a], other[4 * a + 1], other[4 * a + 2], other[4 * a + 3]};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 o = take[(cb * 4 + a) * 64];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc_dv[cb][4 * a + r] += o[r];
+      }
+    store_transposed<NCB>(acc_dv, qg ? p.scale : 1.0f, (char*)(qg ? p.dk : p.dv) + roff, h, krow < N);
   }
-
-
-  const size_t roff = koff + (size_t)min(krow, N - 1) * ROWB;
-  store_transposed<NCB>(acc_dv, 1.0f, (char*)p.dv + roff, h, krow < N);
-  store_transposed<NCB>(acc_dk, p.scale, (char*)p.dk + roff, h, krow < N);
 }
 
 }  // namespace
 
+// Both kernels split where the launch has few tiles.  Whole backward passes in which only that
+// kernel changes, us, unsplit -> split, d = 128 (d = 64 behaves alike):
+//   dQ     non-causal 128 tiles, N = 4096 264 -> 227; 320, 2048 358 -> 344; 192, 2048 204 -> 224; 384, 512 126 -> 131
+//          causal     128 tiles, N = 8192 491 -> 384; 192, 4096 264 -> 217; 320, 4000 394 -> 428
+//   dK/dV  non-causal 64 tiles, 4 heads of N = 1000 155 -> 110; 384, 4096 386 -> 368; 256, 2048 142 -> 153; 640, 2048 358 -> 361
+//          causal     256 tiles, N = 8192 491 -> 417; 256, 1000 81 -> 75; 384, 4096 264 -> 291
 int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
-  const int grid_q = p.B * p.Hq * p.T;
-  const int grid_f = p.B * p.Hkv * ((p.N + 127) / 128);
-  auto launch = [&](auto dtag) {
+  auto launch = [&](auto dtag, auto causal_tag) {
     constexpr int D = decltype(dtag)::value;
-    if (p.causal) {
-      hipLaunchKernelGGL((attn_bwd_dq_kernel<D, true>), dim3(grid_q), dim3(512), 0, stream, p);
-      hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, true>), dim3(grid_f), dim3(256), 0, stream, p);
-    } else {
-      hipLaunchKernelGGL((attn_bwd_dq_kernel<D, false>), dim3(grid_q), dim3(512), 0, stream, p);
-      hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, false>), dim3(grid_f), dim3(256), 0, stream, p);
-    }
+    constexpr bool CAUSAL = decltype(causal_tag)::value;
+    const double blocks = (p.N + 31) / 32;  // 32-row blocks of a head
+    AttnBwdParams q = p;
+    const bool split_q = attn_split_pays(CAUSAL, (long long)p.B * p.Hq * ((p.N + 255) / 256), (p.N + 127) / 128, blocks, 12.0, 1.0);
+    q.T = split_q ? (p.N + 127) / 128 : (p.N + 255) / 256;
+    const dim3 grid_q(p.B * p.Hq * q.T);
+    if (split_q) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 2>), grid_q, dim3(512), 0, stream, q);
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 1>), grid_q, dim3(512), 0, stream, q);
+    const bool split_k = attn_split_pays(CAUSAL, (long long)p.B * p.Hkv * ((p.N + 127) / 128), (p.N + 63) / 64, blocks * (p.Hq / p.Hkv), 11.0, 1.1);
+    const dim3 grid_k(p.B * p.Hkv * (split_k ? (p.N + 63) / 64 : (p.N + 127) / 128));
+    if (split_k) hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 2>), grid_k, dim3(256), 0, stream, q);
+    else hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 1>), grid_k, dim3(256), 0, stream, q);
   };
-  if (d == 128) launch(ic<128>{});
-  else if (d == 64) launch(ic<64>{});
+  auto by_causal = [&](auto dtag) {
+    if (p.causal) launch(dtag, std::true_type{});
+    else launch(dtag, std::false_type{});
+  };
+  if (d == 128) by_causal(ic<128>{});
+  else if (d == 64) by_causal(ic<64>{});
   else return -1;
   return (int)hipGetLastError();
 }

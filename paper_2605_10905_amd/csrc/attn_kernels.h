@@ -20,6 +20,24 @@ struct AttnParams {
   AttnTileMap map;       // attn_tile_map_make(B, Hq, Hkv, T, causal): workgroup id -> (batch, head, tile)
 };
 
+// Whether a launch of `tiles` workgroups, the longest `steps` serial 32-row block steps each, is better
+// run as twice as many that take half as many steps each, on 256 CUs with one workgroup each.
+// A workgroup costs `fixed` steps beside its chain (first loads, merge, stores), a step of the split form
+// `slower` times one of the whole; `per_head` is the number of split tiles per head.
+//   equal tiles: whole rounds over the CUs;
+//   causal: more tiles than CUs fill each other's gaps, so only up to 256 tiles, where the longest one
+//     sets the time, against the mean length of the split tiles over the CUs.
+// The kernels' callers quote what was measured on both sides.
+inline bool attn_split_pays(bool causal, long long tiles, int per_head, double steps, double fixed, double slower) {
+  if (causal) {
+    const double mean = 0.5 * (1.0 + 1.0 / per_head) * 0.5 * steps * slower + fixed;
+    const double rounds = 2.0 * (double)tiles / 256.0;
+    return tiles <= 256 && rounds * mean < steps + fixed;
+  }
+  if (tiles > 65536) return false;  // (nothing to gain after hundreds of rounds, and the doubled grid stays in range)
+  return (double)((2 * tiles + 255) / 256) * (0.5 * steps * slower + fixed) < (double)((tiles + 255) / 256) * (steps + fixed);
+}
+
 // persistent bf16 forward (d = 64 or 128): `workgroups` resident workgroups drain the tile queue
 int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int workgroups, hipStream_t stream);
 
@@ -36,7 +54,7 @@ struct AttnBwdParams {
   void* dv;
   float* ws;         // [B, Hq, 2, Npad] floats: lse * log2(e) and delta, rows padded to whole 64-row tiles
   int B, Hq, Hkv, N;
-  int T;             // 256-row tiles per head = ceil(N / 256)
+  int T = 0;         // query tiles per head of the dQ kernel, set by the launch (256 rows each, 128 when it splits the keys)
   int Npad;          // ceil(N / 64) * 64
   int causal;
   float scale_log2;  // scale * log2(e)

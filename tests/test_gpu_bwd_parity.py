@@ -74,6 +74,19 @@ def test_bwd_d64_reduced_configs(ci, B, Hq, Hkv, N):
     print(gu.check_bwd_full(inp, dob, dq, dk, dv, f"bwd d64 cfg{ci + 1} N={N}"), flush=True)
 
 
+# The cases above are few workgroups, which the launch splits: two waves share 32 rows and add their
+# partial gradients.  Here both sides of that rule: more tiles than CUs (260 heads: one tile a head, neither
+# kernel splits, or dK/dV alone does), and long enough that non-causal dQ alone (75 heads x 4 tiles, three half
+# rounds against two) or non-causal dK/dV alone (48 heads x 8 tiles) splits.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Hkv,N,causal", [(260, 260, 33, False), (260, 260, 97, True), (260, 130, 65, True), (75, 75, 799, False), (48, 48, 1000, False)])
+def test_bwd_split_rule(H, Hkv, N, causal, d):
+    cfg, inp, dob = _case(1, 1, H, Hkv, N, causal=causal, seed=431 + N, d=d)
+    print(f"bwd split rule H={H} Hkv={Hkv} N={N} causal={causal} d={d}", flush=True)
+    dq, dk, dv, _, _ = gu.run_gpu_bwd(inp, dob)
+    gu.check_bwd_full(inp, dob, dq, dk, dv, f"bwd split rule H={H} N={N}")
+
+
 def _bits(x):
     return wl.f32_to_bf16_bits(np.asarray(x, dtype=np.float32))
 
