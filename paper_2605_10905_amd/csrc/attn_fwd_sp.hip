@@ -56,6 +56,8 @@
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) int i32x8;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr float kTau = 8.0f;
 constexpr float kSumLimit = 65536.0f;  // a lane's 16-term partial sum above this redoes the block with a raised reference
@@ -98,10 +100,20 @@ __device__ __forceinline__ void step_pipeline() {
 // is packed, and the packed output is stored only when the next tile's loads have been waited
 // for (loads and stores share one counter per wave, so a store in between would be waited for
 // as well).
-template <int D, bool CAUSAL, int MODE, bool FP8>
+//
+// KS = 2 (bf16, MODE 0), for launches that leave CUs idle: a workgroup owns 128 queries, and the waves
+// w and w + 4 share 32 of them: one takes the first 32-key block of every 64-key tile, the other the
+// second, each with a streaming softmax of its own, merged through LDS at the end.  Twice the
+// workgroups, half the serial chain.  An iteration is then ONE step: bundle b holds key tile b+2 and
+// value tile b, the barrier that publishes bundle b+1 and frees the slot of bundle b-1 sits in front of
+// the step, and the ring has four slots so that a bundle is requested three steps ahead.  Q travels
+// through LDS as well: with no load the compiler knows of, the waits are exact, and the first scores
+// need only Q and key tiles 0 and 1 to have arrived, not bundles 0 and 1 requested behind them.
+template <int D, bool CAUSAL, int MODE, bool FP8, int KS = 1>
 __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p) {
   static_assert(!FP8 || (D == 128 && MODE != 1), "fp8 inputs: head dimension 128, no queue launch");
-  constexpr int BN = 64, NWAVES = 8, BM = NWAVES * 32, NT = NWAVES * 64;
+  static_assert(KS == 1 || (KS == 2 && MODE == 0 && !FP8), "split keys: bf16, one tile per workgroup");
+  constexpr int BN = 64, NWAVES = 8, NQW = NWAVES / KS, BM = NQW * 32, NT = NWAVES * 64;
   constexpr int NCB = D / 32;                // 32-row blocks of O^T
   constexpr int ROWB = D * 2;                // bytes per bf16 row: V in the ring, O
   constexpr int INB = FP8 ? D : 2 * D;       // bytes per input row (q, k, v in memory; K rows in the ring)
@@ -110,7 +122,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   constexpr int KSUBB = 32 * INB;            // bytes per 32-key block of it
   constexpr int TILEB = BN * ROWB;           // bytes per bf16 V tile in the ring
   constexpr int SUBB = 32 * ROWB;            // bytes per 32-key block of it
-  constexpr int NSLOT = 3;                   // ring depth: bundles are requested NSLOT-1 ahead
+  constexpr int NSLOT = KS == 1 ? 3 : 4;     // ring depth: bundles are requested NSLOT-1 ahead
   constexpr int VBASE = NSLOT * KTILEB;      // K parts of the slots first, then the V parts
   constexpr int STGBASE = VBASE + NSLOT * TILEB;  // fp8: two staging slots of one e4m3 V tile each
   constexpr int STGTILE = BN * INB;
@@ -136,6 +148,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int qi = lane & 31;  // query column within the wave's 32-query block
   const int h = lane >> 5;   // which half of the k-slots / accumulator rows this lane holds
+  const int kg = KS == 1 ? 0 : w / NQW;  // KS = 2: which key block of a tile this wave takes
 
   // ---- the tile this workgroup works on (re-assigned at every seam in modes 1 and 2) ------------
   const int N = p.N;
@@ -152,7 +165,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     tile_hq = tc.hq;
     const int hk = tc.hq / G;
     q0 = tc.t * BM;
-    wq0 = q0 + w * 32;
+    wq0 = q0 + (KS == 1 ? w : w % NQW) * 32;
     wave_valid = wq0 < N;
     qhead = (const char*)p.q + ((size_t)(tc.b * p.Hq + tc.hq) * N) * INB;
     khead = (const char*)p.k + ((size_t)(tc.b * p.Hkv + hk) * N) * INB;
@@ -295,7 +308,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
 #pragma unroll
   for (int kk = 0; kk < NKQ; ++kk)
 #pragma unroll
-    for (int e = 0; e < QKR; ++e) kaddr[kk][e] = qi * INB + (((QKR * (2 * kk + h) + e) ^ attn_swz_k<INB>(qi)) << 4);
+    for (int e = 0; e < QKR; ++e) kaddr[kk][e] = kg * KSUBB + qi * INB + (((QKR * (2 * kk + h) + e) ^ attn_swz_k<INB>(qi)) << 4);
   // V through the transposing load: in a group of 16 lanes, lane s reads the four columns
   // 4*(s%4).. of key row s/4 and the hardware hands lane t the four keys of column t.
   uint32_t vaddr[NCB][2];
@@ -307,7 +320,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       for (int e = 0; e < 2; ++e) {
         const int key = 8 * e + 4 * h + (s >> 2);
         const int chunk = cb * 4 + chalf * 2 + ((s & 3) >> 1);
-        vaddr[cb][e] = VBASE + key * ROWB + (v_chunk(key, chunk) << 4) + ((s & 1) << 3);
+        vaddr[cb][e] = VBASE + kg * SUBB + key * ROWB + (v_chunk(key, chunk) << 4) + ((s & 1) << 3);
       }
   }
   // A block id names a 32-key block of the ring: 2 * slot + (which half of the slot's tiles)
@@ -584,6 +597,146 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     step_any(is_active(k2), k2, is_active(k1), s_b, s_a, p_b, p_a, slot * KTILEB + KSUBB, slot * TILEB + SUBB);
   };
 
+  // KS = 2: iteration b exponentiates this wave's block of tile b+1, computes its scores of tile b+2,
+  // accumulates its block of tile b; every wave issues the loads of bundle b+3 in every iteration
+  // (past the end the last tiles again, never read), so the loads in flight are always the same.
+  auto split_mid = [&]() __attribute__((always_inline)) {
+    ATTN_WAIT_VMCNT(2 * NLD);  // bundle b+1 has landed, bundle b+2 stays in flight
+    attn_wg_barrier();
+  };
+  auto split_hot = [&](int b, auto slot_tag) __attribute__((always_inline)) {
+    constexpr int SLOT = decltype(slot_tag)::value, FREE = (SLOT + 3) & 3, NSEG = 2 * NLD < 2 ? 2 : 2 * NLD;
+    const int kt = min(b + 5, nt - 1), vt = min(b + 3, nt - 1);
+    auto producer = [&](int sg) __attribute__((always_inline)) {
+      if (sg == 0) split_mid();
+#pragma unroll
+      for (int j = 0; j < 2 * NLD; ++j) {
+        if (j != sg) continue;
+        if (j < NLD) load_k(kt, FREE, j);
+        else load_v(vt, FREE, j - NLD);
+      }
+    };
+    if constexpr (SLOT & 1) step_hot(s_b, s_a, p_b, p_a, ic<2 * SLOT>{}, ic<2 * ((SLOT + 1) & 3)>{}, ic<NSEG>{}, producer);
+    else step_hot(s_a, s_b, p_a, p_b, ic<2 * SLOT>{}, ic<2 * ((SLOT + 1) & 3)>{}, ic<NSEG>{}, producer);
+  };
+  auto hand_on = [&]() __attribute__((always_inline)) {  // what an even step leaves becomes the next even step's input
+    s_a = s_b;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) p_b[i] = p_a[i];
+  };
+  auto split_any = [&](int b) __attribute__((always_inline)) {
+    const int slot = b & 3, k1 = (b + 1) * BN + kg * 32;
+    split_mid();
+    issue_k(min(b + 5, nt - 1), (slot + 3) & 3);
+    issue_v(min(b + 3, nt - 1), (slot + 3) & 3);
+    step_any(is_active(k1), k1, is_active(k1 - BN), s_a, s_b, p_a, p_b, slot * KTILEB, slot * TILEB);
+    hand_on();
+  };
+  if constexpr (KS == 2) {
+    set_tile((int)blockIdx.x);
+    // Q (128 rows, swizzled like a K tile) borrows the V parts of slots 2 and 3, key tiles 0 and 1 the K
+    // parts of slots 3 and 2
+    constexpr int QBASE = VBASE + 2 * TILEB;
+#pragma unroll
+    for (int it = 0; it < 2 * NLD; ++it) {
+      const int s = it * NT + tid, r = s / NCHI, ch = (s % NCHI) ^ attn_swz_k<INB>(r);
+      attn_lds_dma16(qhead, (uint32_t)min(q0 + r, N - 1) * INB + (ch << 4), lds_wave + QBASE + it * NT * 16);
+    }
+    issue_k(0, 3);
+    issue_k(min(1, nt - 1), 2);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      issue_k(min(b + 2, nt - 1), b);
+      issue_v(min(b, nt - 1), b);
+    }
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
+    m_ref = -INFINITY;
+    l_run = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};
+    ATTN_WAIT_VMCNT(4 * NLD);  // Q and key tiles 0 and 1 have landed
+    attn_wg_barrier();
+    const int qr = (w % NQW) * 32 + qi;
+#pragma unroll
+    for (int kk = 0; kk < NKQ; ++kk) {
+      // (kaddr's row qi and this row agree in the bits the swizzle uses)
+      const u32x4 x = *(LDS_AS const u32x4*)(smem + QBASE + qr * INB + (((2 * kk + h) ^ attn_swz_k<INB>(qr)) << 4));
+      if constexpr (!FP8) qf[kk] = __builtin_bit_cast(bf16x8, x);
+    }
+    // (a wave whose first block is invisible sees no key at all: m stays -inf, l and O zero)
+    if (is_active(kg * 32)) {
+      qk_block(s_b, 3 * KTILEB);
+      softmax_block(s_b, p_b, p_a, kg * 32, needs_mask(kg * 32));
+      qk_block(s_a, 2 * KTILEB);
+    }
+#pragma unroll
+    for (int kk = 0; kk < NKQ; ++kk) asm volatile("" ::"v"(qf[kk]));  // (read by every wave before the barrier, too)
+    lds_ops_done();
+    ATTN_WAIT_VMCNT(2 * NLD);
+    attn_wg_barrier();  // bundle 0 is full; slots 2 and 3 are free
+    issue_k(min(4, nt - 1), 2);
+    issue_v(min(2, nt - 1), 2);
+#pragma unroll
+    for (int m = 0; m < RA; ++m) pre[m] = step_operand(ic<0>{}, m);
+    const int vis = (CAUSAL ? min(wq0, N - 1) : N - 1) - kg * 32;
+    const int n_hot = (wave_valid && vis >= 95) ? (vis - 95) / 64 + 1 : 0;  // bundles whose block of tile b+1 every query sees in full
+    int b = 0;
+    for (; b < (n_hot & ~3); b += 4) {
+      split_hot(b, ic<0>{});
+      split_hot(b + 1, ic<1>{});
+      split_hot(b + 2, ic<2>{});
+      split_hot(b + 3, ic<3>{});
+    }
+    if (b < n_hot) { split_hot(b, ic<0>{}); ++b; }
+    if (b < n_hot) { split_hot(b, ic<1>{}); ++b; }
+    if (b < n_hot) { split_hot(b, ic<2>{}); ++b; }
+    if (b & 1) hand_on();
+    for (; b < nt; ++b) split_any(b);
+
+    // ---- merge: each of the two waves gives away the columns the other one finishes ------------------
+    const float l = attn_sum_halves(l_run);
+    ATTN_WAIT_VMCNT(0);
+    attn_wg_barrier();  // no load is in flight and no wave reads the ring any more
+    constexpr int NH = NCB / 2, MLBASE = NWAVES * NH * 4096;
+    static_assert(MLBASE + NWAVES * 512 <= STGBASE, "the exchanged halves fit the ring");
+    const int wq = w % NQW;
+    LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((kg ^ 1) * NQW + wq) * NH * 256 + lane;
+    LDS_AS const f32x4* const take = (LDS_AS const f32x4*)smem + w * NH * 256 + lane;
+    f32x16 mine[NH];
+#pragma unroll
+    for (int cb = 0; cb < NH; ++cb) {
+      const f32x16 other = kg ? oacc[cb] : oacc[NH + cb];
+      mine[cb] = kg ? oacc[NH + cb] : oacc[cb];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) give[(cb * 4 + a) * 64] = f32x4{other[4 * a], other[4 * a + 1], other[4 * a + 2], other[4 * a + 3]};
+    }
+    ((LDS_AS f32x2*)(smem + MLBASE))[((kg ^ 1) * NQW + wq) * 64 + lane] = f32x2{m_ref, l};
+    __syncthreads();
+    const f32x2 ml = ((LDS_AS const f32x2*)(smem + MLBASE))[w * 64 + lane];
+    const float m = fmaxf(m_ref, ml[0]);
+    const float a_mine = __builtin_amdgcn_exp2f(m_ref - m), a_other = __builtin_amdgcn_exp2f(ml[0] - m);
+    const float l_all = l * a_mine + ml[1] * a_other;
+#pragma unroll
+    for (int cb = 0; cb < NH; ++cb)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 o = take[(cb * 4 + a) * 64];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mine[cb][4 * a + r] = mine[cb][4 * a + r] * a_mine + o[r] * a_other;
+      }
+    u32x4 out[2 * NH];
+    attn_pack_o_rows<NH>(mine, p.out_scale / l_all, out);
+    if (qrow < N) {
+      const size_t row = (size_t)(tile_b * p.Hq + tile_hq) * N + qrow;
+      if (kg == 0 && h == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f;
+      attn_store_packed_o<NH>(out, (char*)p.o + row * ROWB + kg * NH * 64 + h * 16);
+    }
+    return;
+  }
+
   // ---- the tiles of this workgroup -----------------------------------------------------------------
   int wg = (int)blockIdx.x;
   if constexpr (MODE != 0) {
@@ -734,8 +887,32 @@ int resident_workgroups() {
 // (measured: +0.5 .. +4.5 %; with two tiles per CU the plain launch is 1 % faster).  Non-causal
 // launches run one tile per workgroup: in the list-walking instantiation the compiler's greedy
 // scheduling-group solver interleaves the pipelined step less well (5 % more cycles).
+// bf16 launches of few tiles (`tiles` of 256 queries) split the keys (KS = 2); the plain and the queue
+// launch follow the same rule, so that both give the same bytes.  us, unsplit -> split, d = 128:
+//   non-causal  64 tiles, N = 1000 26.6 -> 18.3; 128, 2048 45.0 -> 35.9; 320, 2048 101.6 -> 94.3; 320, 8192 366 -> 328;
+//               192, 2048 52.0 -> 59.4; 256, 4096 118 -> 129; 320, 512 38.8 -> 39.9; 384, 2048 102.9 -> 103.5
+//   causal      128 tiles, N = 1000 26.6 -> 19.2; 192, 1024 27.1 -> 25.5; 256, 2048 48.4 -> 42.1; 256, 8192 163 -> 133;
+//               256, 256 17.2 -> 24.2; 256, 1024 30.4 -> 30.1; 320, 2048 52.6 -> 65.9; 320, 8192 183 -> 210
+// and d = 64: non-causal 128, 2048 32.9 -> 23.0; 384, 4096 128 -> 120; causal 256, 4096 60.4 -> 45.6; 320, 8192 123 -> 144.
+bool split_pays(const AttnParams& p, long long tiles) {
+  return attn_split_pays(p.causal != 0, tiles, (p.N + 127) / 128, (p.N + 31) / 32, 11.0, p.causal ? 1.3 : 1.07);
+}
+
+template <int D>
+int launch_split(const AttnParams& p, hipStream_t stream) {
+  AttnParams q = p;
+  q.T = (p.N + 127) / 128;
+  q.map = attn_tile_map_make(p.B, p.Hq, p.Hkv, q.T, p.causal);
+  const dim3 grid(p.B * p.Hq * q.T);
+  if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 0, false, 2>), grid, dim3(512), 0, stream, q);
+  else hipLaunchKernelGGL((attn_fwd_sp_kernel<D, false, 0, false, 2>), grid, dim3(512), 0, stream, q);
+  return (int)hipGetLastError();
+}
+
 template <int D, bool FP8>
 int launch_sp(const AttnParams& p, int grid, hipStream_t stream) {
+  if constexpr (!FP8)
+    if (split_pays(p, grid)) return launch_split<D>(p, stream);
   const int resident = p.causal ? resident_workgroups() : 0;
   if (p.causal && resident >= 8 && grid >= 3 * resident) {
     AttnParams q = p;
@@ -758,6 +935,7 @@ __global__ void attn_queue_reset_kernel(int* queue) {
 
 int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int workgroups, hipStream_t stream) {
   if (!p.queue || p.total <= 0 || workgroups <= 0) return -1;
+  if (split_pays(p, p.total)) return d == 128 ? launch_split<128>(p, stream) : d == 64 ? launch_split<64>(p, stream) : -1;
   hipLaunchKernelGGL(attn_queue_reset_kernel, dim3(1), dim3(64), 0, stream, p.queue);
   const dim3 grid(workgroups < p.total ? workgroups : p.total);
   if (d == 128) {

@@ -263,6 +263,23 @@ def test_paper_grid_shapes_sampled(N, causal):
         print(f"paper grid N={N} causal={causal}: whole head {mh}", flush=True)
 
 
+# The cases above are few workgroups, which bf16 launches split over the keys (two waves share 32
+# queries and merge their softmax states).  Here both sides of that rule at the edges of its tiles:
+# 75 heads x 4 tiles non-causal, 50 x 4 and 60 x 4 causal split, 260 heads of one tile do not; the queue launch
+# follows the same rule and gives the same bytes.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Hkv,N,causal", [(75, 25, 897, False), (50, 50, 897, True), (60, 30, 1024, True), (260, 130, 33, False), (260, 260, 97, True), (260, 260, 256, True)])
+def test_split_rule(H, Hkv, N, causal, d):
+    cfg = dict(wl.CONFIGS[0], causal=causal, d=d, scale=1.0 / float(np.sqrt(d)), seed=5000 + N)
+    inp = wl.make_inputs(cfg, B=1, Hq=H, Hkv=Hkv, N=N)
+    print(f"split rule H={H} Hkv={Hkv} N={N} causal={causal} d={d}", flush=True)
+    dev = gu.to_device(inp)
+    o, lse = gu.run_gpu(inp, dev)
+    gu.check_full(inp, o, lse, f"split rule H={H} N={N}")
+    o2, lse2 = _run_persistent(inp, dev)
+    assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
+
+
 # ---- persistent launch with the dynamic tile queue ------------------------------------------------
 def _run_persistent(inp, dev, queue_fill=0x7F):
     import paper_2605_10905_amd as A
