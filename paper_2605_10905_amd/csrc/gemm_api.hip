@@ -19,6 +19,7 @@ bool misaligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) !=
 // loses 2.6 % on average; against the rule it replaces (256 / 128 / 64 squares by number of
 // tiles) it is 1.8 x faster on the nt shapes (half of it from the staged stores) and 1.5 x on nn.
 double tile_cost(const GemmTile& t, int M, int N, long long K, long long splits, double bytes) {
+  if (K % t.kmult != 0) return -1.0;
   const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
   if (tiles * 512 > 0x7fffffffll) return -1.0;  // beyond what a grid holds
   double rounds = (double)((tiles + 255) / 256);
@@ -129,7 +130,7 @@ int run_splitk(const void* a, const void* b, void* c, int M, int N, int K, int s
   // 357 -> 335 us with the sum kernel.
   const int steps = K / 64;
   auto slice = [&](int s) { return ((steps + s - 1) / s) * 64; };  // whole 64-column steps, none empty
-  const GemmTile large = {256, 256, 32, 1, 6.1f, 0.58f, 5.5f, gemm_bf16_nt_splitk_launch};
+  const GemmTile large = {256, 256, 64, 1, 5.9f, 0.985f, 5.5f, gemm_bf16_nt_splitk_launch, 64};
   int nwave = 0;
   const GemmTile* const wave = gemm_wavek_nt_tiles(&nwave);
   double best_cost = 0.0;

@@ -359,7 +359,11 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
 
 // The 256 x 256 tile on the 16x16x32 MFMA: each wave's 128 x 128 quarter is 8 x 8 blocks of 16 x 16
 // (64 accumulators of 4 registers), a k-step is 32 wide, a fragment (16 rows x 32 k: 16 bytes per
-// lane, lane (j, g) = row j, k 8g .. 8g+7) feeds eight MFMAs.  Same ring, same barrier placement.
+// lane, lane (j, g) = row j, k 8g .. 8g+7) feeds eight MFMAs.  It is what large outputs run on where K is
+// a multiple of 64: stages of 64 k, so that a load covers whole 128-byte lines (half the L2 requests
+// of 32-wide stages), in two slots.  Bound by the board's power limit, then by the matrix pipe; the
+// 32x32x16 kernel with four 32-wide stages -> this one, us: 8192 x 8192 x 1024 134 -> 119, x 4096 427 -> 370,
+// x 8192 822 -> 702, x 16384 1866 -> 1530 (1437 TFLOP/s), 4096^3 108.6 -> 94, 16384 x 4096 x 2048 229 -> 200.
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // SPLITK: the grid holds p.splits workgroups per tile; workgroup (split, tile) contracts its slice
@@ -370,8 +374,7 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
   constexpr int ROWB = C::ROWB, NCH = C::NCH, TILEA = C::TILEA, STAGEB = C::STAGEB;
   constexpr int NLDA = C::NLDA, LPS = C::LPS;
   constexpr int NPH = BK / 32;       // k-steps per stage
-  constexpr int LPP = LPS / NPH;     // loads issued per k-step
-  static_assert(BK % 32 == 0 && LPS % NPH == 0, "k-step of 32");
+  static_assert(BK % 32 == 0 && LPS % (8 * NPH) == 0, "k-step of 32, whole loads per row");
 
   __shared__ __attribute__((aligned(1024))) char smem_raw[C::LDS_BYTES];
   LDS_AS char* const smem = (LDS_AS char*)smem_raw;
@@ -433,61 +436,69 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
       for (int r = 0; r < 4; ++r) acc[nb][mb][r] = 0.f;
 
   bf16x8 fa[2][8], fb[2][8];
-  auto read_frags = [&](int buf, int base, int ph) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) fa[buf][i] = *(LDS_AS bf16x8*)(smem + ra[ph] + base + i * 16 * ROWB);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) fb[buf][i] = *(LDS_AS bf16x8*)(smem + rb[ph] + base + i * 16 * ROWB);
-  };
-  auto mfmas = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int nb = 0; nb < 8; ++nb)
-#pragma unroll
-      for (int mb = 0; mb < 8; ++mb)
-        acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[buf][nb], fa[buf][mb], acc[nb][mb], 0, 0, 0);
-  };
-  auto interleave = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    }
+  // fragment r of a k-step in the order of first use: the first n block, the eight m blocks, the other n blocks
+  auto read_frag = [&](int buf, int base, int ph, int r) __attribute__((always_inline)) {
+    if (r >= 1 && r <= 8) fa[buf][r - 1] = *(LDS_AS bf16x8*)(smem + ra[ph] + base + (r - 1) * 16 * ROWB);
+    else fb[buf][r ? r - 8 : 0] = *(LDS_AS bf16x8*)(smem + rb[ph] + base + (r ? r - 8 : 0) * 16 * ROWB);
   };
 
   if (NSTAGE <= nk) ATTN_WAIT_VMCNT((NSTAGE - 1) * LPS);
   else ATTN_WAIT_VMCNT(0);
   attn_wg_barrier();
-  read_frags(0, 0, 0);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) read_frag(0, 0, 0, r);
 
-  // one k-stage; PAR: which fragment buffer its first k-step uses (stages of one k-step alternate)
+  // One k-stage; PAR: which fragment buffer its first k-step uses (stages of one k-step alternate).
+  // A k-step is eight rows of eight MFMAs (one n block each), fenced one by one: every row carries two
+  // or three fragment reads of the next k-step and DPR direct-to-LDS loads, each behind an MFMA of its own.
+  // (All loads of a stage in one go behind the barrier kept the waves from issuing MFMAs until the
+  // address unit had taken them: 1.61 M cycles at 8192^3 where the matrix pipe needs 1.05 M.)  The stage
+  // boundary sits behind the first row of a stage's last k-step: that k-step's fragments, requested one
+  // k-step ago, have arrived by then, and the slot of the stage is free for stage ks+NSTAGE.
   auto stage = [&](int ks, int slot, auto steady, auto par) __attribute__((always_inline)) {
     constexpr bool STEADY = decltype(steady)::value;
     constexpr int PAR = decltype(par)::value;
+    constexpr int DPR = NSTAGE > 2 ? LPS / (8 * NPH) : 2 * LPS / (8 * NPH);  // (two slots: early enough to arrive)
+    static_assert(DPR >= 1 && DPR <= 2, "loads per row");
     const int base = slot * STAGEB;
     const int nslot = slot == NSTAGE - 1 ? 0 : slot + 1;
     const int pslot = slot == 0 ? NSTAGE - 1 : slot - 1;
+    const bool more = STEADY || ks + 1 < nk;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ph = 0; ph < NPH; ++ph) {
       const int cur = (PAR + ph) & 1, nxt = cur ^ 1;
-      if (ph + 1 < NPH) {
-        read_frags(nxt, base, ph + 1);
-        if (STEADY || (ks >= 1 && ks - 1 + NSTAGE < nk)) {
+      const bool last = ph == NPH - 1;
 #pragma unroll
-          for (int i = 0; i < LPP; ++i) issue_load(ks - 1 + NSTAGE, pslot, (ph + 1) * LPP + i);
+      for (int row = 0; row < 8; ++row) {
+        if (last && row == 1 && more) {
+          __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of the slot about to be refilled are done
+          if (STEADY || ks + NSTAGE - 1 < nk) ATTN_WAIT_VMCNT((NSTAGE - 2) * LPS);
+          else ATTN_WAIT_VMCNT(0);
+          attn_wg_barrier();
         }
-      } else if (STEADY || ks + 1 < nk) {
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of the slot about to be refilled are done
-        if (STEADY || ks + NSTAGE - 1 < nk) ATTN_WAIT_VMCNT((NSTAGE - 2) * LPS);
-        else ATTN_WAIT_VMCNT(0);
-        attn_wg_barrier();
-        read_frags(nxt, nslot * STAGEB, 0);
-        if (STEADY || ks + NSTAGE < nk) {
+        // reads of this row: first .. first + count - 1
+        const int count = !last ? 2 : row == 0 ? 0 : row < 3 ? 3 : 2;
+        const int first = !last ? 2 * row : row == 0 ? 0 : row < 3 ? 3 * (row - 1) : 2 * row;
+        // rows since the barrier that freed the slot: behind it the loads of stage ks+NSTAGE, before it those left of the one before
+        const bool behind = last && row >= 1;
+        const int q = behind ? row - 1 : 7 + 8 * ph + row;
+        const int dks = behind ? ks + NSTAGE : ks - 1 + NSTAGE;
+        const bool load = STEADY || (dks < nk && (behind || ks >= 1));
 #pragma unroll
-          for (int i = 0; i < LPP; ++i) issue_load(ks + NSTAGE, slot, i);
+        for (int mb = 0; mb < 8; ++mb) {
+          acc[row][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][row], fa[cur][mb], acc[row][mb], 0, 0, 0);
+          if ((mb & 1) == 0 && mb / 2 < count) {
+            if (!last) read_frag(nxt, base, ph + 1, first + mb / 2);
+            else if (more) read_frag(nxt, nslot * STAGEB, 0, first + mb / 2);
+          }
+          if ((mb == 5 || (mb == 7 && DPR > 1)) && load) {
+            const int it = q * DPR + (mb == 7 ? 1 : 0);
+            if (it < LPS) issue_load(dks, behind ? slot : pslot, it);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-      mfmas(cur);
-      interleave();
     }
   };
 
@@ -611,7 +622,7 @@ int launch(const GemmParams& p, hipStream_t stream) {
 }  // namespace
 
 int gemm_bf16_nt_splitk_launch(const GemmParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<32, 4, true>), dim3(p.tiles_m * p.tiles_n * p.splits), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true>), dim3(p.tiles_m * p.tiles_n * p.splits), dim3(256), 0, stream, p);
   return (int)hipGetLastError();
 }
 
@@ -641,6 +652,7 @@ const GemmVariant* gemm_bf16_nt_variants(int* count) {
 // The rates (GemmTile) are a fit to about 70 shapes per layout, M 1 .. 590000, N 32 .. 65536, K 64 .. 16384.
 const GemmTile* gemm_bf16_nt_tiles(int* count) {
   static const GemmTile table[] = {
+      {256, 256, 64, 1, 5.9f, 0.985f, 5.5f, launch_m16<64, 2>, 64},
       {256, 256, 32, 1, 6.1f, 0.58f, 5.5f, launch<4, 4, 32, 4, 1>},
       {256, 128, 64, 1, 4.4f, 0.62f, 5.5f, launch<4, 2, 64, 3, 1>},
       {128, 256, 64, 1, 4.1f, 0.65f, 5.5f, launch<2, 4, 64, 3, 1>},

@@ -75,6 +75,20 @@ def test_gemm_small_shapes_all_variants(M, N, K):
         check(c, a, b, f"gemm {M}x{N}x{K} variant {var}")
 
 
+# the 16x16x32 kernels at the edges of their pipeline (fewer stages than ring slots, one more, odd and even)
+# and of their tiles
+@pytest.mark.parametrize("M,N,K", [(256, 256, 64), (257, 255, 128), (300, 270, 192), (1, 513, 256), (511, 40, 320), (130, 258, 704)])
+def test_gemm_m16_stages(M, N, K):
+    import paper_2605_10905_amd as A
+
+    a, b = wl.make_gemm_inputs(640 + K, M, N, K)
+    for var in _variants(K):
+        if var is not None and "16x16x32" in A.gemm_variant_name(var):
+            print(f"gemm m16 {M}x{N}x{K} variant {var}", flush=True)
+            check(run_gemm(a, b, var), a, b, f"gemm m16 {M}x{N}x{K} variant {var}")
+    check(run_gemm_splitk(a, b, 2), a, b, f"gemm m16 split-K {M}x{N}x{K}")
+
+
 @pytest.mark.parametrize("N", [1, 2, 7, 9, 63, 65, 120, 129, 255, 257, 263, 511])
 def test_gemm_row_starts_at_every_alignment(N):
     """C's rows start at any multiple of two bytes when N is not a multiple of 8: whole 16-byte pieces,
