@@ -62,9 +62,8 @@ int validate(const void* q, const void* k, const void* v, void* o, float* lse, i
   return ATTN_OK;
 }
 
-// Default choice: the first listed variant for (dtype, d).  The smaller query tiles of the first
-// kernel do not pay even when the launch leaves CUs idle: the pipelined kernel on half the chip
-// still beats them (e.g. 128 workgroups at N = 8192: 160 against 228 microseconds).
+// Default choice: the first listed variant for (dtype, d).  (bf16 launches of few tiles are split over the
+// keys by the variant's own launch function.)
 int choose_variant(int dtype, int B, int Hq, int N, int d) {
   (void)B; (void)Hq; (void)N;
   for (int i = 0; i < total_variants(); ++i) {
