@@ -668,6 +668,14 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     }
     // (a wave whose first block is invisible sees no key at all: m stays -inf, l and O zero)
     if (is_active(kg * 32)) {
+      // Both waves start from the reference maximum of keys 0 .. 31, all of which this wave's queries see,
+      // as the unsplit form does: blocks far below it (masked keys, down to -inf) get probabilities of zero
+      // instead of a reference of their own against which they would overflow, and P is rounded as there.
+      // (Measured, without -> with: 2 heads of 256 6.23 -> 6.31 us, 32 of 1000 causal 18.2 -> 18.4.)
+      if (kg) {
+        qk_block(s_b, 3 * KTILEB - KSUBB);
+        m_ref = block_max(s_b);
+      }
       qk_block(s_b, 3 * KTILEB);
       softmax_block(s_b, p_b, p_a, kg * 32, needs_mask(kg * 32));
       qk_block(s_a, 2 * KTILEB);

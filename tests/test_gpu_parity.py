@@ -280,6 +280,31 @@ def test_split_rule(H, Hkv, N, causal, d):
     assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
 
 
+# A key-padding mask carried as an extra feature column: hidden keys get scores from -7e11 to -inf.  The
+# waves that take every second 32-key block must not make such a block their reference: its exponents would
+# overflow (or be -inf + inf) and the merged row be NaN.  Keys 0 .. 31 hold a visible key in every case.
+_HIDDEN = dict(all_after_20=lambda j: j >= 20, all_after_32=lambda j: j >= 32, second_block=lambda j: (j >= 32) & (j < 64),
+               odd_blocks=lambda j: (j // 32) % 2 == 1, block_1_and_5=lambda j: (j // 32 == 1) | (j // 32 == 5))
+
+
+@pytest.mark.parametrize("score", [-7e11, -1e12, -3e30, -3.38e38, -np.inf])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_hidden_keys_far_below_the_visible_ones(d, causal, score):
+    rng = np.random.default_rng(41 + d)
+    N, H = 300, 2
+    q, k, v = (rng.standard_normal((1, H, N, d)).astype(np.float32) for _ in range(3))
+    q[..., 0] = 1.0
+    for name, hidden in _HIDDEN.items():
+        k[..., 0] = np.where(hidden(np.arange(N)), np.float32(score), np.float32(0.0))
+        inp = _custom(q, k, v, causal, 1.0 / d ** 0.5)
+        dev = gu.to_device(inp)
+        for var in [None] + _variants(d):
+            print(f"hidden keys {name} score={score} causal={causal} d={d} variant {var}", flush=True)
+            o, lse = gu.run_gpu(inp, dev, var)
+            gu.check_full(inp, o, lse, f"hidden keys {name} score={score} causal={causal} d={d} variant {var}")
+
+
 # ---- persistent launch with the dynamic tile queue ------------------------------------------------
 def _run_persistent(inp, dev, queue_fill=0x7F):
     import paper_2605_10905_amd as A
