@@ -61,6 +61,10 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr float kTau = 8.0f;
 constexpr float kSumLimit = 65536.0f;  // a lane's 16-term partial sum above this redoes the block with a raised reference
+constexpr float kDeepRef = -134217728.0f;  // -2^27: the unit in the last place is 16 from here down
+// Reference of a row that has seen no key: finite, so that a block whose scores are all -inf gives
+// probabilities of zero (-inf + FLT_MAX) and not NaN, and far enough down that the first real score replaces it.
+constexpr float kNoRef = -3.4028234663852886e38f;
 
 template <int V>
 using ic = std::integral_constant<int, V>;
@@ -359,6 +363,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   // ---- streaming-softmax state ----------------------------------------------------------------
   f32x16 oacc[NCB];
   float m_ref;            // reference maximum, scaled log2 units
+  bool deep = false;      // some row of the wave has a reference below kDeepRef (bf16 inputs)
   float l_run;            // this lane's share of the row sum (halves are added at the end)
   const float c = p.scale_log2;
   f32x16 s_a, s_b;        // S^T of two consecutive blocks (one consumed, one produced)
@@ -374,18 +379,23 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   // raise the reference maximum to cover mx and rescale what is relative to it: l and O
   auto raise_reference = [&](float mx) __attribute__((always_inline)) {
     const float m_new = fmaxf(m_ref, mx);
-    const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);  // exp2(-inf) = 0 on the first block
+    const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);  // 0 on the first block
     m_ref = m_new;
+    if constexpr (!FP8) deep = __builtin_amdgcn_ballot_w64(m_ref < kDeepRef) != 0;
     l_run *= alpha;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) oacc[cb] *= alpha;
     return alpha;
   };
   // exponentials of a whole block against the current reference, packed; returns the lane's sum
-  auto exp_block = [&](const f32x16& s_in, u32x4 (&p_out)[2]) __attribute__((always_inline)) {
+  auto exp_pack = [&](const f32x16& s_in, u32x4 (&p_out)[2], auto bounded) __attribute__((always_inline)) {
     f32x16 e;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s_in[r], c, -m_ref));
+    for (int r = 0; r < 16; ++r) {
+      float x = __builtin_fmaf(s_in[r], c, -m_ref);
+      if constexpr (decltype(bounded)::value) x = x > 16.0f ? 16.0f : x;  // (a NaN stays one)
+      e[r] = __builtin_amdgcn_exp2f(x);
+    }
 #pragma unroll
     for (int u = 0; u < 8; ++u) p_out[u >> 2][u & 3] = attn_pack_bf16(e[2 * u], e[2 * u + 1]);
     float ls0 = e[0], ls1 = e[1];
@@ -395,6 +405,15 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       ls1 += e[2 * u + 1];
     }
     return ls0 + ls1;
+  };
+  // The reference covers the block here, so an exponent exceeds kTau only by what rounding left between
+  // mx * c and the reference: half a unit in the last place, at most 8 down to kDeepRef, more than 128 below
+  // -2^32 (keys hidden by large negative scores).  Bounding it keeps l and O finite until a visible key raises the
+  // reference and drops them; among themselves such scores are a unit apart, so the weights stay what they were.
+  // (2 heads of 256, the smallest launch, pay 0.06 us for it; long ones nothing that can be measured.)
+  auto exp_block = [&](const f32x16& s_in, u32x4 (&p_out)[2]) __attribute__((always_inline)) {
+    if (!FP8 && __builtin_expect(deep, 0)) return exp_pack(s_in, p_out, std::true_type{});
+    return exp_pack(s_in, p_out, std::false_type{});
   };
 
   // ---- boundary-case building blocks (compiler-scheduled, not overlapped) ----------------------
@@ -653,7 +672,8 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
-    m_ref = -INFINITY;
+    m_ref = kNoRef;
+    deep = false;
     l_run = 0.f;
 #pragma unroll
     for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};
@@ -666,7 +686,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       const u32x4 x = *(LDS_AS const u32x4*)(smem + QBASE + qr * INB + (((2 * kk + h) ^ attn_swz_k<INB>(qr)) << 4));
       if constexpr (!FP8) qf[kk] = __builtin_bit_cast(bf16x8, x);
     }
-    // (a wave whose first block is invisible sees no key at all: m stays -inf, l and O zero)
+    // (a wave whose first block is invisible sees no key at all: l and O stay zero)
     if (is_active(kg * 32)) {
       // Both waves start from the reference maximum of keys 0 .. 31, all of which this wave's queries see,
       // as the unsplit form does: blocks far below it (masked keys, down to -inf) get probabilities of zero
@@ -674,7 +694,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       // (Measured, without -> with: 2 heads of 256 6.23 -> 6.31 us, 32 of 1000 causal 18.2 -> 18.4.)
       if (kg) {
         qk_block(s_b, 3 * KTILEB - KSUBB);
-        m_ref = block_max(s_b);
+        raise_reference(block_max(s_b));
       }
       qk_block(s_b, 3 * KTILEB);
       softmax_block(s_b, p_b, p_a, kg * 32, needs_mask(kg * 32));
@@ -765,7 +785,8 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
-    m_ref = -INFINITY;
+    m_ref = kNoRef;
+    deep = false;
     l_run = 0.f;
 #pragma unroll
     for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};

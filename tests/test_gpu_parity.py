@@ -305,6 +305,29 @@ def test_hidden_keys_far_below_the_visible_ones(d, causal, score):
             gu.check_full(inp, o, lse, f"hidden keys {name} score={score} causal={causal} d={d} variant {var}")
 
 
+# The same with keys 0 .. 31 hidden (left padding), where the first reference is that of hidden keys: it is replaced
+# as soon as a visible key is seen, whatever rounding left between it and the scores it was taken from.
+# (The first feature of q varies over the rows, and that remainder with it.)
+_HIDDEN_FIRST = dict(before_40=lambda j: j < 40, before_last_9=lambda j: j < j.size - 9, all_but_block_1=lambda j: j // 32 != 1,
+                     even_blocks=lambda j: (j // 32) % 2 == 0)
+
+
+@pytest.mark.parametrize("N,score", [(300, -1e9), (300, -7e11), (300, -3e30), (300, -3.3e38), (300, -np.inf), (2500, -2.0 ** 34)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_hidden_keys_in_front(d, N, score):
+    rng = np.random.default_rng(43 + d)
+    q, k, v = (rng.standard_normal((1, 1, N, d)).astype(np.float32) for _ in range(3))
+    q[..., 0] = 1.0 - (np.arange(N) % 64) / 128.0
+    for name, hidden in _HIDDEN_FIRST.items():
+        k[..., 0] = np.where(hidden(np.arange(N)), np.float32(score), np.float32(0.0))
+        inp = _custom(q, k, v, False, 1.0 / d ** 0.5)
+        dev = gu.to_device(inp)
+        for var in [None] + _variants(d):
+            print(f"hidden keys in front {name} N={N} score={score} d={d} variant {var}", flush=True)
+            o, lse = gu.run_gpu(inp, dev, var)
+            gu.check_full(inp, o, lse, f"hidden keys in front {name} N={N} score={score} d={d} variant {var}")
+
+
 # ---- persistent launch with the dynamic tile queue ------------------------------------------------
 def _run_persistent(inp, dev, queue_fill=0x7F):
     import paper_2605_10905_amd as A
