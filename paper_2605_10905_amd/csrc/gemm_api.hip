@@ -21,7 +21,7 @@ bool misaligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) !=
 double tile_cost(const GemmTile& t, int M, int N, long long K, long long splits, double bytes) {
   if (K % t.kmult != 0) return -1.0;
   const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
-  if (tiles * 512 > 0x7fffffffll) return -1.0;  // beyond what a grid holds
+  if (tiles * t.threads > 0xffffffffll) return -1.0;  // beyond what a launch holds
   double rounds = (double)((tiles + 255) / 256);
   if (t.per_cu > 1 && tiles >= 256ll * t.per_cu) rounds = (double)tiles / 256.0 + 0.5;
   const double work = rounds * (t.fixed_us + (double)((K + t.step - 1) / t.step) * t.step_us);

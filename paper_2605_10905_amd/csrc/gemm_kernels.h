@@ -32,6 +32,7 @@ struct GemmTile {
   float tb_s;  // rate at which it moves operands and result when they are the bound
   int (*launch)(const GemmParams& p, hipStream_t stream);
   int kmult = 32;  // K must be a multiple of this
+  int threads = 256;
 };
 const GemmTile* gemm_bf16_nt_tiles(int* count);   // ring in LDS, shared by the waves of a workgroup
 const GemmTile* gemm_bf16_nn_tiles(int* count);

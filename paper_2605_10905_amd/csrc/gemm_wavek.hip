@@ -246,7 +246,7 @@ const GemmTile* gemm_wavek_nt_tiles(int* count) {
   static const GemmTile table[] = {
       {16, 16, 256, 2, 0.4f, 0.16f, 5.5f, launch<1, 1, 4, 4>},
       {32, 32, 256, 2, 0.5f, 0.32f, 5.5f, launch<2, 2, 4, 2>},
-      {64, 16, 512, 1, 1.0f, 0.78f, 5.5f, launch<4, 1, 8, 2>},
+      {64, 16, 512, 1, 1.0f, 0.78f, 5.5f, launch<4, 1, 8, 2>, 32, 512},
       {32, 64, 256, 1, 1.5f, 0.52f, 5.5f, launch<2, 4, 4, 3>},
       {64, 64, 256, 1, 2.2f, 0.68f, 5.5f, launch<4, 4, 4, 2>},
   };
@@ -256,9 +256,9 @@ const GemmTile* gemm_wavek_nt_tiles(int* count) {
 
 const GemmTile* gemm_wavek_nn_tiles(int* count) {
   static const GemmTile table[] = {
-      {16, 32, 256, 1, 0.8f, 0.39f, 4.8f, launch<1, 2, 8, 5, true>},
-      {32, 64, 256, 1, 1.3f, 0.50f, 4.8f, launch<2, 4, 8, 3, true>},
-      {64, 32, 256, 1, 1.1f, 0.60f, 4.8f, launch<4, 2, 8, 3, true>},
+      {16, 32, 256, 1, 0.8f, 0.39f, 4.8f, launch<1, 2, 8, 5, true>, 32, 512},
+      {32, 64, 256, 1, 1.3f, 0.50f, 4.8f, launch<2, 4, 8, 3, true>, 32, 512},
+      {64, 32, 256, 1, 1.1f, 0.60f, 4.8f, launch<4, 2, 8, 3, true>, 32, 512},
   };
   *count = (int)(sizeof(table) / sizeof(table[0]));
   return table;
