@@ -138,9 +138,13 @@ def _stream(stream):
     if stream is None:
         import torch
 
-        # the handle alone: building a Stream object for it took a third of a small call's host time
+        # the handle alone: building a Stream object for it took a third of a small call's host time (the two
+        # names are torch's own and not documented: without them the Stream object is built)
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         return torch.cuda.current_stream().cuda_stream
     return getattr(stream, "cuda_stream", stream)
 

@@ -2,6 +2,7 @@
 header declares, rejects bad arguments before touching a device, and its work
 decomposition is a bijection that keeps K/V sharers on one XCD."""
 import ctypes
+import importlib
 import os
 
 import numpy as np
@@ -247,3 +248,22 @@ def test_bench_refuses_more_than_one_gpu():
 
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "--gpus" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torchs_private_names(A, monkeypatch, missing):
+    """The default stream is the current one of the current device, whether or not torch has the names
+    that give its handle directly."""
+    import types
+
+    import torch
+
+    names = dict(_cuda_getCurrentRawStream=lambda device: 100 + device, _cuda_getDevice=lambda: 3)
+    monkeypatch.setattr(torch, "_C", types.SimpleNamespace(**names))
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    stream = importlib.import_module("paper_2605_10905_amd.binding")._stream
+    assert stream(None) == 103
+    monkeypatch.delattr(torch._C, missing)
+    assert stream(None) == 77
+    assert stream(5) == 5 and stream(types.SimpleNamespace(cuda_stream=6)) == 6
