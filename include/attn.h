@@ -96,10 +96,12 @@ int attn_fwd_fp8(const void* q, const void* k, const void* v, void* o, float* ls
  * attn_fwd_persistent -- attn_fwd for bfloat16 as a persistent launch: one workgroup per compute
  * unit, each taking query tiles from a queue in device memory until it is drained (the software
  * form of the paper's dynamic tile assignment by cluster launch control, section 4.2: a kernel
- * that stays resident and balances irregular tile run times).  Same results as attn_fwd.
- *   queue   device, attn_persistent_queue_bytes() bytes, 128-byte aligned, owned by the caller;
- *           contents on entry are irrelevant (the call enqueues a kernel that clears it first),
- *           it must not be shared by calls that can overlap on the device
+ * that stays resident and balances irregular tile run times).  Launches of few tiles, which attn_fwd
+ * splits over the keys, have nothing to balance and run that same kernel here, one workgroup per
+ * 128-row tile; they do not use the queue.  Same results as attn_fwd, bit for bit.
+ *   queue   device, attn_persistent_queue_bytes() bytes, 128-byte aligned, owned by the caller, required
+ *           at every size; contents on entry are irrelevant (a launch that uses it enqueues a kernel
+ *           that clears it first), it must not be shared by calls that can overlap on the device
  * Everything else as attn_fwd; dtype must be ATTN_BF16 (ATTN_ERR_UNSUPPORTED otherwise).
  */
 int attn_fwd_persistent(const void* q, const void* k, const void* v, void* o, float* lse,
@@ -158,6 +160,9 @@ long long attn_bwd_noalloc_max_workspace_bytes(void);
  * attn_fwd_variant -- tuning hook: as attn_fwd, but with the kernel variant
  * forced (see attn_variant_name) instead of chosen by the library.  Returns
  * ATTN_ERR_UNSUPPORTED if the variant does not exist for this d / dtype.
+ * The bf16 variants named "pipelined" are what attn_fwd runs: they choose between
+ * two forms by size, 256-row tiles or, for few tiles, 128-row tiles whose keys are
+ * split between two waves; "whole tiles" and "split keys" are these forms by themselves.
  */
 int attn_fwd_variant(const void* q, const void* k, const void* v, void* o, float* lse,
                      int B, int Hq, int Hkv, int N, int d, int causal, float scale,
@@ -170,14 +175,16 @@ int attn_fwd_fp8_variant(const void* q, const void* k, const void* v, void* o, f
 
 /* Number of kernel variants and a host string describing variant i (NULL if out of range). */
 int attn_num_variants(void);
-/* index of the variant attn_fwd / attn_fwd_fp8 run for this dtype and shape (-1: none) */
+/* index of the variant attn_fwd / attn_fwd_fp8 run for this dtype and shape (-1: none); for bf16 the
+ * "pipelined" one, which chooses its form by itself */
 int attn_default_variant(int dtype, int B, int Hq, int N, int d);
 const char* attn_variant_name(int variant);
 
 /*
  * attn_tile_coord -- host-side copy of the work decomposition the kernels use:
- * workgroup `wg` of a launch of attn_num_workgroups(...) workgroups processes
- * query tile *t (rows t*BM .. t*BM+BM-1) of head *hq in batch *b.  Host
+ * workgroup `wg` of a launch of attn_num_workgroups(...) workgroups with one tile each
+ * processes query tile *t (rows t*BM .. t*BM+BM-1) of head *hq in batch *b (BM = 256,
+ * or 128 where bf16 keys are split; resident workgroups take the same tiles in turn).  Host
  * pointers.  Used to check that the map is a bijection and keeps the
  * workgroups that share a K/V head on one XCD.  Returns an attn_status.
  */
@@ -185,7 +192,8 @@ int attn_tile_coord(int wg, int B, int Hq, int Hkv, int N, int BM, int causal,
                     int* b, int* hq, int* t);
 int attn_num_workgroups(int B, int Hq, int N, int BM);
 
-/* Query-tile height BM (rows per workgroup) of a variant; 0 if out of range. */
+/* Query-tile height BM (rows per workgroup) of a variant; 0 if out of range.  For the bf16 variants named
+ * "pipelined" that of the form for many tiles (256). */
 int attn_variant_bm(int variant);
 
 const char* attn_status_string(int status); /* host string, static storage */

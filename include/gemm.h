@@ -66,8 +66,9 @@ long long gemm_splitk_workspace_bytes(int M, int N, int splits);
  * call (enough tiles, or too little k per slice), more means gemm_bf16_nt_splitk with that many. */
 int gemm_splitk_plan(int M, int N, int K);
 
-/* Tuning hook: the same with kernel variant `variant` (0 .. gemm_num_variants()-1);
- * ATTN_ERR_UNSUPPORTED if K is not a multiple of that variant's K-slice. */
+/* Tuning hook: the same with kernel variant `variant` (0 .. gemm_num_variants()-1), among them every
+ * kernel that gemm_bf16_nt chooses from; ATTN_ERR_UNSUPPORTED if K is not a multiple of
+ * gemm_variant_kmult(variant). */
 int gemm_bf16_nt_variant(const void* a, const void* b, void* c, int M, int N, int K, int variant, void* stream);
 int gemm_num_variants(void);
 const char* gemm_variant_name(int variant); /* NULL if out of range */
@@ -75,7 +76,8 @@ const char* gemm_variant_name(int variant); /* NULL if out of range */
 /*
  * Work decomposition (host-side, for tests): tile (tm, tn) of tile x tile outputs that
  * workgroup `wg` of a launch over an M x N output computes.  Returns ATTN_ERR_SHAPE if wg is
- * out of range.  gemm_variant_tile gives a variant's square tile size (0 if out of range).
+ * out of range.  gemm_variant_tile gives the rows of a variant's tile (0 if out of range; the name
+ * tells rows and columns).
  */
 int gemm_tile_coord(int wg, int M, int N, int tile, int* tm, int* tn);
 int gemm_num_workgroups(int M, int N, int tile);

@@ -22,7 +22,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // all variant tables, concatenated; the first match for (dtype, d) is the default
 typedef const AttnVariant* (*VariantTable)(int*);
-const VariantTable kTables[] = {attn_sp_variants, attn_fp8_variants};
+const VariantTable kTables[] = {attn_sp_variants, attn_fp8_variants, attn_sp_forms};
 
 const AttnVariant* variant_at(int i) {
   if (i < 0) return nullptr;
@@ -62,8 +62,8 @@ int validate(const void* q, const void* k, const void* v, void* o, float* lse, i
   return ATTN_OK;
 }
 
-// Default choice: the first listed variant for (dtype, d).  (bf16 launches of few tiles are split over the
-// keys by the variant's own launch function.)
+// Default choice: the first listed variant for (dtype, d).  (The bf16 defaults choose by themselves between the
+// two forms that attn_sp_forms lists one by one.)
 int choose_variant(int dtype, int B, int Hq, int N, int d) {
   (void)B; (void)Hq; (void)N;
   for (int i = 0; i < total_variants(); ++i) {

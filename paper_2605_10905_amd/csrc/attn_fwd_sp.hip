@@ -928,7 +928,7 @@ bool split_pays(const AttnParams& p, long long tiles) {
 }
 
 template <int D>
-int launch_split(const AttnParams& p, hipStream_t stream) {
+int launch_split(const AttnParams& p, int, hipStream_t stream) {
   AttnParams q = p;
   q.T = (p.N + 127) / 128;
   q.map = attn_tile_map_make(p.B, p.Hq, p.Hkv, q.T, p.causal);
@@ -939,9 +939,7 @@ int launch_split(const AttnParams& p, hipStream_t stream) {
 }
 
 template <int D, bool FP8>
-int launch_sp(const AttnParams& p, int grid, hipStream_t stream) {
-  if constexpr (!FP8)
-    if (split_pays(p, grid)) return launch_split<D>(p, stream);
+int launch_whole(const AttnParams& p, int grid, hipStream_t stream) {
   const int resident = p.causal ? resident_workgroups() : 0;
   if (p.causal && resident >= 8 && grid >= 3 * resident) {
     AttnParams q = p;
@@ -955,6 +953,13 @@ int launch_sp(const AttnParams& p, int grid, hipStream_t stream) {
   return (int)hipGetLastError();
 }
 
+template <int D, bool FP8>
+int launch_sp(const AttnParams& p, int grid, hipStream_t stream) {
+  if constexpr (!FP8)
+    if (split_pays(p, grid)) return launch_split<D>(p, grid, stream);
+  return launch_whole<D, FP8>(p, grid, stream);
+}
+
 // zero the 8 list counters (a kernel, not a memset, so that the pair can be captured in a graph)
 __global__ void attn_queue_reset_kernel(int* queue) {
   if (threadIdx.x < 8) queue[threadIdx.x * 32] = 0;
@@ -964,7 +969,7 @@ __global__ void attn_queue_reset_kernel(int* queue) {
 
 int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int workgroups, hipStream_t stream) {
   if (!p.queue || p.total <= 0 || workgroups <= 0) return -1;
-  if (split_pays(p, p.total)) return d == 128 ? launch_split<128>(p, stream) : d == 64 ? launch_split<64>(p, stream) : -1;
+  if (split_pays(p, p.total)) return d == 128 ? launch_split<128>(p, 0, stream) : d == 64 ? launch_split<64>(p, 0, stream) : -1;
   hipLaunchKernelGGL(attn_queue_reset_kernel, dim3(1), dim3(64), 0, stream, p.queue);
   const dim3 grid(workgroups < p.total ? workgroups : p.total);
   if (d == 128) {
@@ -984,6 +989,17 @@ const AttnVariant* attn_sp_variants(int* count) {
       {"bf16 d128 pipelined BM256 BN64", 0, 128, 256, 64, 512, 2 * 3 * 64 * 128 * 2, launch_sp<128, false>},
       {"bf16 d64 pipelined BM256 BN64", 0, 64, 256, 64, 512, 2 * 3 * 64 * 64 * 2, launch_sp<64, false>},
       {"fp8 d128 fp8-QK bf16-PV pipelined BM256 BN64", 1, 128, 256, 64, 512, 3 * 64 * 128 + 3 * 64 * 256 + 2 * 64 * 128, launch_sp<128, true>},
+  };
+  *count = (int)(sizeof(table) / sizeof(table[0]));
+  return table;
+}
+
+const AttnVariant* attn_sp_forms(int* count) {
+  static const AttnVariant table[] = {
+      {"bf16 d128 whole tiles BM256 BN64", 0, 128, 256, 64, 512, 2 * 3 * 64 * 128 * 2, launch_whole<128, false>},
+      {"bf16 d64 whole tiles BM256 BN64", 0, 64, 256, 64, 512, 2 * 3 * 64 * 64 * 2, launch_whole<64, false>},
+      {"bf16 d128 split keys BM128 BN64", 0, 128, 128, 64, 512, 2 * 4 * 64 * 128 * 2, launch_split<128>},
+      {"bf16 d64 split keys BM128 BN64", 0, 64, 128, 64, 512, 2 * 4 * 64 * 64 * 2, launch_split<64>},
   };
   *count = (int)(sizeof(table) / sizeof(table[0]));
   return table;

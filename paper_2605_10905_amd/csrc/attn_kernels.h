@@ -77,3 +77,4 @@ struct AttnVariant {
 // Variant tables, defined by the kernel translation units (host functions).
 const AttnVariant* attn_sp_variants(int* count);   // pipelined kernel: bf16 d = 128 / 64, fp8 d = 128 (the defaults)
 const AttnVariant* attn_fp8_variants(int* count);  // all products on the fp8 matrix path, P as two e4m3 terms
+const AttnVariant* attn_sp_forms(int* count);      // the two forms between which the bf16 defaults choose, each by itself

@@ -40,6 +40,14 @@ const GemmTile* cheapest(const GemmTile* best, double* cost, const GemmTile* tab
   return best;
 }
 
+// the variant tables, concatenated
+const GemmVariant* variant_at(int i) {
+  int n1 = 0, n2 = 0;
+  const GemmVariant* const t1 = gemm_bf16_nt_variants(&n1);
+  const GemmVariant* const t2 = gemm_wavek_nt_variants(&n2);
+  return i < 0 ? nullptr : i < n1 ? &t1[i] : i < n1 + n2 ? &t2[i - n1] : nullptr;
+}
+
 double gemm_bytes(int M, int N, int K) { return 2.0 * ((double)M * K + (double)N * K + (double)M * N); }
 
 const GemmTile* choose_nt(int M, int N, int K, double* cost) {
@@ -77,25 +85,23 @@ int run(const void* a, const void* b, void* c, int M, int N, int K, int variant,
   if (M <= 0 || N <= 0 || K <= 0) return ATTN_ERR_SHAPE;
   if (misaligned(a, 16) || misaligned(b, 16) || misaligned(c, 16)) return ATTN_ERR_SHAPE;
   if (K % 32 != 0) return ATTN_ERR_UNSUPPORTED;
-  int count = 0;
-  const GemmVariant* table = gemm_bf16_nt_variants(&count);
-  if (variant < -1 || variant >= count) return ATTN_ERR_UNSUPPORTED;
+  const GemmVariant* const v = variant_at(variant);
+  if (!v && variant != -1) return ATTN_ERR_UNSUPPORTED;
   // per-lane offsets inside an operand panel are 32-bit: 256 rows of K bf16
   if ((long long)K * 2 * 256 >= (1ll << 31)) return ATTN_ERR_UNSUPPORTED;
   GemmParams p;
   p.a = a; p.b = b; p.c = c;
   p.M = M; p.N = N; p.K = K;
   p.stream_c = stream_c_pays(M, N);
-  if (variant < 0) {
+  if (!v) {
     double cost = 0.0;
     return launch_tile(choose_nt(M, N, K, &cost), p, stream);
   }
-  const GemmVariant& v = table[variant];
-  if (K % v.bk != 0 || K % v.kmult != 0) return ATTN_ERR_UNSUPPORTED;
-  p.tiles_m = (M + v.bm - 1) / v.bm;
-  p.tiles_n = (N + v.bn - 1) / v.bn;
+  if (K % v->bk != 0 || K % v->kmult != 0) return ATTN_ERR_UNSUPPORTED;
+  p.tiles_m = (M + v->bm - 1) / v->bm;
+  p.tiles_n = (N + v->bn - 1) / v->bn;
   if ((long long)p.tiles_m * p.tiles_n > 0x7fffffffll) return ATTN_ERR_UNSUPPORTED;
-  return v.launch(p, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
+  return v->launch(p, (hipStream_t)stream) == 0 ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
 int run_nn(const void* a, const void* b, void* c, int M, int N, int K, void* stream) {
@@ -200,27 +206,25 @@ int gemm_bf16_nt_variant(const void* a, const void* b, void* c, int M, int N, in
 }
 
 int gemm_num_variants(void) {
-  int count = 0;
-  gemm_bf16_nt_variants(&count);
-  return count;
+  int n1 = 0, n2 = 0;
+  gemm_bf16_nt_variants(&n1);
+  gemm_wavek_nt_variants(&n2);
+  return n1 + n2;
 }
 
 const char* gemm_variant_name(int variant) {
-  int count = 0;
-  const GemmVariant* table = gemm_bf16_nt_variants(&count);
-  return variant >= 0 && variant < count ? table[variant].name : nullptr;
+  const GemmVariant* const v = variant_at(variant);
+  return v ? v->name : nullptr;
 }
 
 int gemm_variant_kmult(int variant) {
-  int count = 0;
-  const GemmVariant* table = gemm_bf16_nt_variants(&count);
-  return variant >= 0 && variant < count ? table[variant].kmult : 0;
+  const GemmVariant* const v = variant_at(variant);
+  return v ? v->kmult : 0;
 }
 
 int gemm_variant_tile(int variant) {
-  int count = 0;
-  const GemmVariant* table = gemm_bf16_nt_variants(&count);
-  return variant >= 0 && variant < count ? table[variant].bm : 0;
+  const GemmVariant* const v = variant_at(variant);
+  return v ? v->bm : 0;
 }
 
 int gemm_num_workgroups(int M, int N, int tile) {

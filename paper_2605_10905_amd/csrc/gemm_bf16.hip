@@ -644,6 +644,14 @@ const GemmVariant* gemm_bf16_nt_variants(int* count) {
       {"bf16 nt 64x64x32 ring4", 64, 64, 32, 32, launch<1, 1, 32, 4, 4>},
       {"bf16 nt 256x256x32 ring4 mfma16x16x32", 256, 256, 32, 64, launch_m16<32, 4>},
       {"bf16 nt 256x256x64 ring2 mfma16x16x32", 256, 256, 64, 64, launch_m16<64, 2>},
+      // (64-wide stages whose last one may be half: K a multiple of 32)
+      {"bf16 nt 256x128x64 ring3", 256, 128, 32, 32, launch<4, 2, 64, 3, 1>},
+      {"bf16 nt 128x256x64 ring3", 128, 256, 32, 32, launch<2, 4, 64, 3, 1>},
+      {"bf16 nt 128x256x32 ring3", 128, 256, 32, 32, launch<2, 4, 32, 3, 2>},
+      {"bf16 nt 128x128x64 ring4 half", 128, 128, 32, 32, launch<2, 2, 64, 4, 1>},
+      {"bf16 nt 64x128x64 ring3", 64, 128, 32, 32, launch<1, 2, 64, 3, 2>},
+      {"bf16 nt 64x128x64 ring2", 64, 128, 32, 32, launch<1, 2, 64, 2, 3>},
+      {"bf16 nt 64x128x32 ring4", 64, 128, 32, 32, launch<1, 2, 32, 4, 3>},
   };
   *count = (int)(sizeof(table) / sizeof(table[0]));
   return table;

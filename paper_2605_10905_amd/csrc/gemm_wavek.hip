@@ -254,6 +254,18 @@ const GemmTile* gemm_wavek_nt_tiles(int* count) {
   return table;
 }
 
+const GemmVariant* gemm_wavek_nt_variants(int* count) {
+  static const GemmVariant table[] = {
+      {"bf16 nt 16x16 waves split k", 16, 16, 32, 32, launch<1, 1, 4, 4>},
+      {"bf16 nt 32x32 waves split k", 32, 32, 32, 32, launch<2, 2, 4, 2>},
+      {"bf16 nt 64x16 waves split k", 64, 16, 32, 32, launch<4, 1, 8, 2>},
+      {"bf16 nt 32x64 waves split k", 32, 64, 32, 32, launch<2, 4, 4, 3>},
+      {"bf16 nt 64x64 waves split k", 64, 64, 32, 32, launch<4, 4, 4, 2>},
+  };
+  *count = (int)(sizeof(table) / sizeof(table[0]));
+  return table;
+}
+
 const GemmTile* gemm_wavek_nn_tiles(int* count) {
   static const GemmTile table[] = {
       {16, 32, 256, 1, 0.8f, 0.39f, 4.8f, launch<1, 2, 8, 5, true>, 32, 512},

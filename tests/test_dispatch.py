@@ -1,6 +1,16 @@
 """Routes of the public calls, without a GPU: which kernels a call launches, and that no size which fits a
 launch is refused."""
-from tests.launch_recorder import routes
+import ctypes
+import math
+import os
+import random
+import subprocess
+
+import pytest
+
+import paper_2605_10905_amd as A
+from tests import kernel_cases as kc
+from tests.launch_recorder import ROOT, routes
 
 
 def test_very_many_rows_are_launched():
@@ -13,3 +23,88 @@ def test_very_many_rows_are_launched():
         assert status == 0 and len(launches) == 1, (c, status, launches)
         name, grid, threads = launches[0]
         assert grid * threads < 2 ** 32 and grid >= max(c["M"], c["N"]) // 256, (c, launches)
+
+
+def test_every_row_of_the_kernel_cases_launches_the_kernel_it_names():
+    rows = kc.ATTENTION + kc.NN + kc.SPLITK
+    got, _ = routes([c for _, c in rows])
+    wrong = [(c, names, launches) for (names, c), (st, launches) in zip(rows, got) if st != 0 or [x[0] for x in launches] != names]
+    assert not wrong, "\n".join(map(str, wrong))
+    for (_, c), (_, launches) in zip(rows, got):
+        if c["op"] == "splitk":  # more slices than one, and a last one that is shorter
+            slices = _slices(c["M"], c["N"], *launches[0][:2])
+            assert 1 < slices <= c["splits"], (c, slices)
+
+
+def _slices(M, N, kernel, workgroups):
+    """Slices of k of a split-K launch, from its number of workgroups."""
+    a = [int(x) for x in kernel[kernel.index("<") + 1:-1].split(",")[:2]]
+    bm, bn = (256, 256) if "m16" in kernel else (16 * a[0], 16 * a[1])
+    tiles = -(-M // bm) * -(-N // bn)
+    assert workgroups % tiles == 0
+    return workgroups // tiles
+
+
+def _variant_calls():
+    return [dict(op="nt_variant", M=300, N=520, K=3 * A.gemm_variant_kmult(v), variant=v) for v in range(A.gemm_num_variants())]
+
+
+def _form_calls():
+    calls = []
+    for v in range(A.attn_num_variants()):
+        name = A.attn_variant_name(v)
+        if name.startswith("bf16"):
+            calls += [dict(op="fwd_variant", variant=v, H=2, N=300, d=int(name.split(" d")[1].split()[0]), causal=c) for c in (False, True)]
+    return calls
+
+
+def test_every_kernel_is_launched_by_a_case_that_a_gpu_test_runs():
+    """The rows of kernel_cases.py, and every variant of gemm_bf16_nt_variant, which the GEMM's tests run one by one."""
+    got, kernels = routes([c for _, c in kc.ATTENTION + kc.NN + kc.SPLITK] + _variant_calls())
+    assert all(st == 0 for st, _ in got)
+    missing = kernels - {x[0] for _, launches in got for x in launches}
+    assert not missing, sorted(missing)
+
+
+def test_what_the_nt_product_chooses_is_among_the_variants():
+    rng = random.Random(20260514)
+
+    def log(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    chosen = [dict(op="nt", M=log(1, 600000), N=log(1, 65536), K=32 * log(1, 512)) for _ in range(4000)]
+    variants = _variant_calls()
+    got, _ = routes(variants + chosen)
+    assert all(st == 0 and len(launches) == 1 for st, launches in got)
+    names = [launches[0][0] for _, launches in got]
+    assert len(set(names[:len(variants)])) >= len(variants) - 1  # (one kernel is listed twice: whole and half last stages)
+    assert set(names[len(variants):]) <= set(names[:len(variants)])
+
+
+def test_the_forms_of_the_forward_are_forced_by_their_variants():
+    """"whole tiles" and "split keys" run that form whatever the size; "pipelined" follows the rule."""
+    calls = _form_calls()
+    got, _ = routes(calls)
+    for c, (st, launches) in zip(calls, got):
+        form = 1 if "whole" in A.attn_variant_name(c["variant"]) else 2  # (2 heads of 300 are few tiles: the rule splits)
+        assert st == 0 and [x[0] for x in launches] == [f"attn_fwd_sp_kernel<{c['d']}, {str(c['causal']).lower()}, 0, false, {form}>"], (c, launches)
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n,splits", [(1, 1, 2), (9, 4, 7), (5, 3, 13), (63, 1, 4), (2, 17, 64), (8, 8, 3)])
+def test_split_tile_map_is_a_bijection_and_keeps_an_xcd_on_few_slices(tmp_path, tiles_m, tiles_n, splits):
+    """gemm_tile_coord_split, compiled from its header: every (slice, tile) once, and an XCD (workgroup ids that
+    agree mod 8) takes a consecutive piece of the list of slices."""
+    src, lib = tmp_path / "map.cpp", tmp_path / "map.so"
+    src.write_text('#define GEMM_HD\n#include "gemm_map.h"\nextern "C" void coord(int wg, int m, int n, int splits, int* out) {\n'
+                   "  const GemmTileCoord c = gemm_tile_coord_split(wg, m, n, splits, out);\n  out[1] = c.tm;\n  out[2] = c.tn;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2605_10905_amd", "csrc"), str(src), "-o", str(lib)], check=True)
+    out, coord = (ctypes.c_int * 3)(), ctypes.CDLL(str(lib)).coord
+    total = tiles_m * tiles_n * splits
+    seen, slices = set(), {}
+    for wg in range(total):
+        coord(wg, tiles_m, tiles_n, splits, out)
+        seen.add(tuple(out))
+        slices.setdefault(wg % 8, set()).add(out[0])
+    assert seen == {(s, i, j) for s in range(splits) for i in range(tiles_m) for j in range(tiles_n)}
+    share = -(-total // 8)  # entries of the list an XCD takes
+    assert all(max(s) - min(s) + 1 == len(s) <= (share - 1 + tiles_m * tiles_n - 1) // (tiles_m * tiles_n) + 1 for s in slices.values())

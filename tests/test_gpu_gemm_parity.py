@@ -76,7 +76,7 @@ def test_gemm_small_shapes_all_variants(M, N, K):
 
 
 # the 16x16x32 kernels at the edges of their pipeline (fewer stages than ring slots, one more, odd and even)
-# and of their tiles
+# and of their tiles.  (So little k is not split: the last line runs gemm_bf16_nt_splitk's unsplit route.)
 @pytest.mark.parametrize("M,N,K", [(256, 256, 64), (257, 255, 128), (300, 270, 192), (1, 513, 256), (511, 40, 320), (130, 258, 704)])
 def test_gemm_m16_stages(M, N, K):
     import paper_2605_10905_amd as A
@@ -157,7 +157,8 @@ def test_gemm_full_size_sampled(name):
 
 
 # outputs of a few tiles: edges of the 16-, 32- and 64-row tiles whose waves split k, k shorter than one
-# chunk per wave, a last half chunk (K = 32 mod 64), many chunks per wave; and one shape per ring tile
+# chunk per wave, a last half chunk (K = 32 mod 64), many chunks per wave; and outputs of some of the larger
+# tiles (test_gpu_kernels.py has one shape and more for every kernel)
 @pytest.mark.parametrize("M,N,K", [(1, 16, 32), (15, 17, 96), (33, 15, 160), (17, 33, 4128), (65, 64, 9952), (63, 300, 2080), (200, 1, 8224),
                                    (300, 328, 2016), (1030, 1000, 1056), (129, 4104, 224), (2050, 1992, 352), (5000, 72, 544)])
 def test_gemm_tile_choice_edges(M, N, K):
@@ -182,14 +183,14 @@ def run_gemm_splitk(a_bits, b_bits, splits, poison=float("nan")):
     return c
 
 
-# one and several tiles, ragged M and N (vector and scalar stores of the partial tiles and of C),
-# slices that divide K evenly, a shorter last slice, more slices asked for than k-steps exist
+# one and several tiles, ragged M and N, more slices asked for than k-steps exist.  The library splits only where
+# it expects to gain: of these it splits 77 x 1031 x 20032 alone; the others run one kernel and leave the
+# workspace alone.  The kernels of split launches are in test_gpu_kernels.py.
 SPLITK = [(256, 256, 512, 2), (300, 520, 4032, 4), (513, 257, 1024, 8), (64, 7, 640, 3), (5, 3, 128, 64), (1000, 72, 2048, 1),
           (512, 384, 8192, 16), (33, 1001, 4096, 5)]
 
 
-# outputs of a few small tiles (waves split a slice's k further), the sum over an element count that is
-# not a multiple of four, more slices than are worth using
+# outputs of a few small tiles, more slices than are worth using
 SPLITK += [(16, 16, 2304, 5), (33, 65, 2112, 7), (100, 300, 8192, 16), (77, 1031, 20032, 15), (700, 900, 4096, 4)]
 
 
@@ -288,7 +289,7 @@ def test_gemm_nn_structured_and_unsupported():
 
 
 def test_gemm_calls_can_be_captured_in_a_graph_and_replayed():
-    """gemm_bf16_nt, gemm_bf16_nn and gemm_bf16_nt_splitk (two kernels) captured into one graph; every
+    """gemm_bf16_nt, gemm_bf16_nn and gemm_bf16_nt_splitk (one kernel at this size) captured into one graph; every
     replay, with eager work in between, must reproduce the eager results bit for bit."""
     import paper_2605_10905_amd as A
 

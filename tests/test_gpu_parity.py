@@ -263,8 +263,8 @@ def test_paper_grid_shapes_sampled(N, causal):
         print(f"paper grid N={N} causal={causal}: whole head {mh}", flush=True)
 
 
-# The cases above are few workgroups, which bf16 launches split over the keys (two waves share 32
-# queries and merge their softmax states).  Here both sides of that rule at the edges of its tiles:
+# The cases above are few workgroups, which attn_fwd splits over the keys (two waves share 32
+# queries and merge their softmax states; the variants run both forms).  Here both sides of that rule at the edges of its tiles:
 # 75 heads x 4 tiles non-causal, 50 x 4 and 60 x 4 causal split, 260 heads of one tile do not; the queue launch
 # follows the same rule and gives the same bytes.
 @pytest.mark.parametrize("d", [64, 128])
@@ -343,7 +343,8 @@ def _run_persistent(inp, dev, queue_fill=0x7F):
 
 
 def _static_twin(d):
-    """Index of the kernel variant whose tile code the persistent launch runs."""
+    """Index of the variant that attn_fwd runs: the persistent launch follows the same rule and computes every tile
+    with the same code."""
     import paper_2605_10905_amd as A
 
     return next(i for i in range(A.attn_num_variants()) if A.attn_variant_name(i) == f"bf16 d{d} pipelined BM256 BN64")
@@ -357,7 +358,8 @@ def test_persistent_reduced_configs(ci, B, Hq, Hkv, N):
     print(f"persistent config{ci + 1} reduced B={B} Hq={Hq} Hkv={Hkv} N={N}", flush=True)
     o, lse = _run_persistent(inp, dev)
     gu.check_full(inp, o, lse, f"persistent cfg{ci + 1} N={N}")
-    # every tile is computed by the same code as in the one-tile-per-workgroup launch of that kernel
+    # the plain launch follows the same rule, so the bytes are the same (most of these sizes are split; launches
+    # that take their tiles from the queue are in test_gpu_kernels.py)
     o2, lse2 = gu.run_gpu(inp, dev, _static_twin(cfg["d"]))
     assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
 
@@ -441,7 +443,7 @@ def test_causal_list_walking_launch(B, Hq, Hkv, N, d, ci):
 
 # ---- stream capture: nothing in the library allocates, synchronises or uses a memset node --------------
 def test_calls_can_be_captured_in_a_graph_and_replayed():
-    """attn_fwd, attn_fwd_persistent (whose queue is cleared by a kernel) and attn_bwd captured into
+    """attn_fwd, attn_fwd_persistent and attn_bwd (all split at this size, no queue) captured into
     one graph; every replay, with eager work in between, must reproduce the eager results."""
     import paper_2605_10905_amd as A
 
