@@ -61,7 +61,14 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr float kTau = 8.0f;
 constexpr float kSumLimit = 65536.0f;  // a lane's 16-term partial sum above this redoes the block with a raised reference
-constexpr float kDeepRef = -134217728.0f;  // -2^27: the unit in the last place is 16 from here down
+// A row sum above this (of N probabilities it stays below 2^36) holds overflow: exponents are taken against the
+// reference mx * c as rounded, and what that rounding leaves reaches 64 at about -2^31 and 128, i.e. infinity, at
+// -2^32 (keys hidden by large negative scores).  Such a state must not outlive the reference that a visible key
+// brings (infinity times alpha = 0): the first block is redone with its exponents bounded, as every redone block
+// of the pipelined steps is, and the other blocks' l and O are dropped where alpha is zero.  Bounding every
+// block behind a flag or by v_minimum3 cost launches of short heads 2 - 4 % (384 heads of 133: 19.5 -> 19.9 us and
+// more); as it is they take 19.6, and 2 heads of 256, the smallest launch, 6.3 -> 6.5.
+constexpr float kSumDrop = 1.8446744073709552e19f;  // 2^64
 // Reference of a row that has seen no key: finite, so that a block whose scores are all -inf gives
 // probabilities of zero (-inf + FLT_MAX) and not NaN, and far enough down that the first real score replaces it.
 constexpr float kNoRef = -3.4028234663852886e38f;
@@ -363,7 +370,6 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   // ---- streaming-softmax state ----------------------------------------------------------------
   f32x16 oacc[NCB];
   float m_ref;            // reference maximum, scaled log2 units
-  bool deep = false;      // some row of the wave has a reference below kDeepRef (bf16 inputs)
   float l_run;            // this lane's share of the row sum (halves are added at the end)
   const float c = p.scale_log2;
   f32x16 s_a, s_b;        // S^T of two consecutive blocks (one consumed, one produced)
@@ -376,24 +382,45 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     for (int r = 2; r < 16; ++r) mx = fmaxf(mx, s[r]);
     return attn_max_halves(mx) * c;
   };
-  // raise the reference maximum to cover mx and rescale what is relative to it: l and O
-  auto raise_reference = [&](float mx) __attribute__((always_inline)) {
+  // raise the reference maximum to cover mx and rescale what is relative to it: l, O and, if there is one, the
+  // packed P^T that has not been multiplied into O yet; `heal`: l and O may hold overflow (kSumDrop)
+  auto raise_reference = [&](float mx, u32x4* pend, auto heal) __attribute__((always_inline)) {
     const float m_new = fmaxf(m_ref, mx);
     const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);  // 0 on the first block
     m_ref = m_new;
-    if constexpr (!FP8) deep = __builtin_amdgcn_ballot_w64(m_ref < kDeepRef) != 0;
+    if constexpr (decltype(heal)::value) {
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(l_run > kSumDrop) != 0, 0)) {
+        const float l_row = attn_sum_halves(l_run);  // (O holds the products of both halves' probabilities; a NaN stays one)
+        if (alpha == 0.f && l_row > kSumDrop) {
+          l_run = 0.f;
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
+          pend[0] = pend[1] = u32x4{0, 0, 0, 0};
+        }
+      }
+    }
     l_run *= alpha;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) oacc[cb] *= alpha;
-    return alpha;
+    if (pend) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const uint32_t u = pend[i][r];
+          pend[i][r] = attn_pack_bf16(__uint_as_float(u << 16) * alpha, __uint_as_float(u & 0xffff0000u) * alpha);
+        }
+    }
   };
   // exponentials of a whole block against the current reference, packed; returns the lane's sum
-  auto exp_pack = [&](const f32x16& s_in, u32x4 (&p_out)[2], auto bounded) __attribute__((always_inline)) {
+  auto exp_block = [&](const f32x16& s_in, u32x4 (&p_out)[2], auto bounded) __attribute__((always_inline)) {
     f32x16 e;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       float x = __builtin_fmaf(s_in[r], c, -m_ref);
-      if constexpr (decltype(bounded)::value) x = x > 16.0f ? 16.0f : x;  // (a NaN stays one)
+      if constexpr (decltype(bounded)::value) x = __builtin_elementwise_minimum(x, 16.0f);  // (a NaN stays one)
       e[r] = __builtin_amdgcn_exp2f(x);
     }
 #pragma unroll
@@ -405,15 +432,6 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       ls1 += e[2 * u + 1];
     }
     return ls0 + ls1;
-  };
-  // The reference covers the block here, so an exponent exceeds kTau only by what rounding left between
-  // mx * c and the reference: half a unit in the last place, at most 8 down to kDeepRef, more than 128 below
-  // -2^32 (keys hidden by large negative scores).  Bounding it keeps l and O finite until a visible key raises the
-  // reference and drops them; among themselves such scores are a unit apart, so the weights stay what they were.
-  // (2 heads of 256, the smallest launch, pay 0.1 us for it; long ones stay within 0.4 %.)
-  auto exp_block = [&](const f32x16& s_in, u32x4 (&p_out)[2]) __attribute__((always_inline)) {
-    if (!FP8 && __builtin_expect(deep, 0)) return exp_pack(s_in, p_out, std::true_type{});
-    return exp_pack(s_in, p_out, std::false_type{});
   };
 
   // ---- boundary-case building blocks (compiler-scheduled, not overlapped) ----------------------
@@ -442,16 +460,15 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     }
     const float mx = block_max(s);
     if (__builtin_amdgcn_ballot_w64(mx > m_ref + kTau) != 0) {
-      const float alpha = raise_reference(mx);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const uint32_t u = pend[i][r];
-          pend[i][r] = attn_pack_bf16(__uint_as_float(u << 16) * alpha, __uint_as_float(u & 0xffff0000u) * alpha);
-        }
+      raise_reference(mx, pend, std::integral_constant<bool, !FP8>{});
     }
-    l_run += exp_block(s, pk);
+    l_run += exp_block(s, pk, std::false_type{});
+  };
+  // the first block's exponentials once more, bounded, if they overflowed (kSumDrop); behind the score products
+  // of the second block, which hide the look at the sum
+  auto bound_first = [&]() __attribute__((always_inline)) {
+    if constexpr (!FP8)
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(l_run > kSumDrop) != 0, 0)) l_run = exp_block(s_b, p_b, std::true_type{});
   };
   auto is_active = [&](int key0) __attribute__((always_inline)) {
     return wave_valid && key0 < kv_end && (!CAUSAL || key0 <= wlast);
@@ -533,9 +550,8 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       // the redo path "reads" the optimistic packs, so that they are computed inside the
       // pipelined region above and not sunk below this branch into the common path's tail
       asm volatile("" ::"v"(p_out[0]), "v"(p_out[1]));
-      raise_reference(block_max(s_in));
-      // (bounded without a look at `deep`: a second copy of the block here cost long launches up to 1.2 %)
-      ls = exp_pack(s_in, p_out, std::integral_constant<bool, !FP8>{});
+      raise_reference(block_max(s_in), nullptr, std::false_type{});
+      ls = exp_block(s_in, p_out, std::integral_constant<bool, !FP8>{});
     }
     l_run += ls;
   };
@@ -674,7 +690,6 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
     m_ref = kNoRef;
-    deep = false;
     l_run = 0.f;
 #pragma unroll
     for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};
@@ -695,11 +710,12 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       // (Measured, without -> with: 2 heads of 256 6.23 -> 6.31 us, 32 of 1000 causal 18.2 -> 18.4.)
       if (kg) {
         qk_block(s_b, 3 * KTILEB - KSUBB);
-        raise_reference(block_max(s_b));
+        m_ref = fmaxf(m_ref, block_max(s_b));
       }
       qk_block(s_b, 3 * KTILEB);
       softmax_block(s_b, p_b, p_a, kg * 32, needs_mask(kg * 32));
       qk_block(s_a, 2 * KTILEB);
+      bound_first();
     }
 #pragma unroll
     for (int kk = 0; kk < NKQ; ++kk) asm volatile("" ::"v"(qf[kk]));  // (read by every wave before the barrier, too)
@@ -726,14 +742,14 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     for (; b < nt; ++b) split_any(b);
 
     // ---- merge: each of the two waves gives away the columns the other one finishes ------------------
-    const float l = attn_sum_halves(l_run);
+    float l = attn_sum_halves(l_run);
     ATTN_WAIT_VMCNT(0);
     attn_wg_barrier();  // no load is in flight and no wave reads the ring any more
     constexpr int NH = NCB / 2, MLBASE = NWAVES * NH * 4096;
     static_assert(MLBASE + NWAVES * 512 <= STGBASE, "the exchanged halves fit the ring");
     const int wq = w % NQW;
     LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((kg ^ 1) * NQW + wq) * NH * 256 + lane;
-    LDS_AS const f32x4* const take = (LDS_AS const f32x4*)smem + w * NH * 256 + lane;
+    LDS_AS f32x4* const take = (LDS_AS f32x4*)smem + w * NH * 256 + lane;
     f32x16 mine[NH];
 #pragma unroll
     for (int cb = 0; cb < NH; ++cb) {
@@ -744,9 +760,24 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     }
     ((LDS_AS f32x2*)(smem + MLBASE))[((kg ^ 1) * NQW + wq) * 64 + lane] = f32x2{m_ref, l};
     __syncthreads();
-    const f32x2 ml = ((LDS_AS const f32x2*)(smem + MLBASE))[w * 64 + lane];
+    f32x2 ml = ((LDS_AS const f32x2*)(smem + MLBASE))[w * 64 + lane];
     const float m = fmaxf(m_ref, ml[0]);
     const float a_mine = __builtin_amdgcn_exp2f(m_ref - m), a_other = __builtin_amdgcn_exp2f(ml[0] - m);
+    const bool drop_mine = a_mine == 0.f && l > kSumDrop, drop_other = a_other == 0.f && ml[1] > kSumDrop;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(drop_mine || drop_other) != 0, 0)) {
+      // (as in raise_reference)
+      if (drop_mine) l = 0.f;
+      if (drop_other) ml[1] = 0.f;
+#pragma unroll
+      for (int cb = 0; cb < NH; ++cb)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          if (drop_other) take[(cb * 4 + a) * 64] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (drop_mine) mine[cb][4 * a + r] = 0.f;
+        }
+    }
     const float l_all = l * a_mine + ml[1] * a_other;
 #pragma unroll
     for (int cb = 0; cb < NH; ++cb)
@@ -787,7 +818,6 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
     m_ref = kNoRef;
-    deep = false;
     l_run = 0.f;
 #pragma unroll
     for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};
@@ -827,6 +857,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
       qk_block(s_b, (NSLOT - 1) * KTILEB);             // S(0)
       softmax_block(s_b, p_b, p_a, 0, needs_mask(0));  // P(0) -> p_b (nothing pending yet)
       qk_block(s_a, (NSLOT - 1) * KTILEB + KSUBB);     // S(1); ignored if block 1 is not visible
+      bound_first();
     }
     if constexpr (FP8) {
       // bundle 1 has arrived once only value tile 2's load is outstanding: convert its value tile into slot 1
