@@ -712,23 +712,26 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
 }  // namespace
 
 // Both kernels split where the launch has few tiles.  Whole backward passes in which only that
-// kernel changes, us, unsplit -> split, d = 128 (d = 64 behaves alike):
-//   dQ     non-causal 128 tiles, N = 4096 264 -> 227; 320, 2048 358 -> 344; 192, 2048 204 -> 224; 384, 512 126 -> 131
-//          causal     128 tiles, N = 8192 491 -> 384; 192, 4096 264 -> 217; 320, 4000 394 -> 428
-//   dK/dV  non-causal 64 tiles, 4 heads of N = 1000 155 -> 110; 384, 4096 386 -> 368; 256, 2048 142 -> 153; 640, 2048 358 -> 361
-//          causal     256 tiles, N = 8192 491 -> 417; 256, 1000 81 -> 75; 384, 4096 264 -> 291
+// kernel changes, us, unsplit -> split, d = 128 (d = 64 behaves alike), heads x N:
+//   dQ     non-causal 16 x 2048 140 -> 119; 41 x 2048 356 -> 339; 22 x 4096 663 -> 627; 24 x 2048 200 -> 218; 64 x 1000 125 -> 136; 80 x 2048 584 -> 586
+//          causal     32 x 2048 155 -> 139; 48 x 1000 84 -> 78; 64 x 300 36 -> 33; 64 x 513 52 -> 53; 85 x 513 65 -> 68
+//   dK/dV  non-causal 12 x 1000 75 -> 67; 38 x 1000 113 -> 110; 16 x 2048 140 -> 151; 64 x 1000 125 -> 141
+//          causal     24 x 1000 76 -> 70; 16 x 2048 135 -> 123; 43 x 513 51 -> 52; 38 x 1000 80 -> 96
 int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
   auto launch = [&](auto dtag, auto causal_tag) {
     constexpr int D = decltype(dtag)::value;
     constexpr bool CAUSAL = decltype(causal_tag)::value;
     const double blocks = (p.N + 31) / 32;  // 32-row blocks of a head
     AttnBwdParams q = p;
-    const bool split_q = attn_split_pays(CAUSAL, (long long)p.B * p.Hq * ((p.N + 255) / 256), (p.N + 127) / 128, blocks, 12.0, 1.0);
+    auto tiles = [&](int heads, int rows) { return (long long)p.B * heads * ((p.N + rows - 1) / rows); };
+    const AttnSplitCost cost_q = CAUSAL ? AttnSplitCost{6.2, 8.4, 1.02, 0.6, 6.0} : AttnSplitCost{14.8, 16.0, 0.89, 0.68, 6.0};
+    const bool split_q = attn_split_pays(CAUSAL, tiles(p.Hq, 256), tiles(p.Hq, 128), (p.N + 127) / 128, blocks, cost_q);
     q.T = split_q ? (p.N + 127) / 128 : (p.N + 255) / 256;
     const dim3 grid_q(p.B * p.Hq * q.T);
     if (split_q) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 2>), grid_q, dim3(512), 0, stream, q);
     else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 1>), grid_q, dim3(512), 0, stream, q);
-    const bool split_k = attn_split_pays(CAUSAL, (long long)p.B * p.Hkv * ((p.N + 127) / 128), (p.N + 63) / 64, blocks * (p.Hq / p.Hkv), 11.0, 1.1);
+    const AttnSplitCost cost_k = CAUSAL ? AttnSplitCost{6.5, 7.5, 0.88, 0.51, 4.0} : AttnSplitCost{10.3, 8.7, 1.09, 0.82, 4.0};
+    const bool split_k = attn_split_pays(CAUSAL, tiles(p.Hkv, 128), tiles(p.Hkv, 64), (p.N + 63) / 64, blocks * (p.Hq / p.Hkv), cost_k);
     const dim3 grid_k(p.B * p.Hkv * (split_k ? (p.N + 63) / 64 : (p.N + 127) / 128));
     if (split_k) hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 2>), grid_k, dim3(256), 0, stream, q);
     else hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 1>), grid_k, dim3(256), 0, stream, q);

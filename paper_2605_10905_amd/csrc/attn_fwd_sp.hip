@@ -949,14 +949,16 @@ int resident_workgroups() {
 // launches run one tile per workgroup: in the list-walking instantiation the compiler's greedy
 // scheduling-group solver interleaves the pipelined step less well (5 % more cycles).
 // bf16 launches of few tiles (`tiles` of 256 queries) split the keys (KS = 2); the plain and the queue
-// launch follow the same rule, so that both give the same bytes.  us, unsplit -> split, d = 128:
-//   non-causal  64 tiles, N = 1000 26.6 -> 18.3; 128, 2048 45.0 -> 35.9; 320, 2048 101.6 -> 94.3; 320, 8192 366 -> 328;
-//               192, 2048 52.0 -> 59.4; 256, 4096 118 -> 129; 320, 512 38.8 -> 39.9; 384, 2048 102.9 -> 103.5
-//   causal      128 tiles, N = 1000 26.6 -> 19.2; 192, 1024 27.1 -> 25.5; 256, 2048 48.4 -> 42.1; 256, 8192 163 -> 133;
-//               256, 256 17.2 -> 24.2; 256, 1024 30.4 -> 30.1; 320, 2048 52.6 -> 65.9; 320, 8192 183 -> 210
-// and d = 64: non-causal 128, 2048 32.9 -> 23.0; 384, 4096 128 -> 120; causal 256, 4096 60.4 -> 45.6; 320, 8192 123 -> 144.
+// launch follow the same rule, so that both give the same bytes.  us, whole tiles -> split keys, d = 128, heads x N:
+//   non-causal  32 x 1000 25.8 -> 20.3; 16 x 2048 42.0 -> 34.2; 34 x 2048 100.4 -> 92.0; 22 x 4096 186.1 -> 172.7;
+//               100 x 64 5.9 -> 7.0; 150 x 150 10.5 -> 17.7; 38 x 1000 26.7 -> 40.5; 90 x 1000 60.6 -> 69.8; 40 x 4096 291.9 -> 301.0
+//   causal      32 x 1000 25.8 -> 18.0; 48 x 1000 26.3 -> 24.3; 32 x 2048 47.3 -> 40.5; 16 x 4096 84.9 -> 69.4;
+//               150 x 150 10.5 -> 16.1; 58 x 1000 28.7 -> 31.2; 85 x 513 20.0 -> 25.4
+// and d = 64: non-causal 34 x 2048 67.8 -> 60.2, 90 x 1000 39.2 -> 40.7; causal 48 x 1000 19.4 -> 16.8, 64 x 513 12.7 -> 12.9.
 bool split_pays(const AttnParams& p, long long tiles) {
-  return attn_split_pays(p.causal != 0, tiles, (p.N + 127) / 128, (p.N + 31) / 32, 11.0, p.causal ? 1.3 : 1.07);
+  const int per_head = (p.N + 127) / 128;
+  const AttnSplitCost cost = p.causal ? AttnSplitCost{7.6, 10.0, 0.82, 0.75, 5.0} : AttnSplitCost{14.7, 12.9, 1.07, 0.66, 5.0};
+  return attn_split_pays(p.causal != 0, tiles, (long long)p.B * p.Hq * per_head, per_head, (p.N + 31) / 32, cost);
 }
 
 template <int D>

@@ -20,22 +20,44 @@ struct AttnParams {
   AttnTileMap map;       // attn_tile_map_make(B, Hq, Hkv, T, causal): workgroup id -> (batch, head, tile)
 };
 
-// Whether a launch of `tiles` workgroups, the longest `steps` serial 32-row block steps each, is better
-// run as twice as many that take half as many steps each, on 256 CUs with one workgroup each.
-// A workgroup costs `fixed` steps beside its chain (first loads, merge, stores), a step of the split form
-// `slower` times one of the whole; `per_head` is the number of split tiles per head.
-//   equal tiles: whole rounds over the CUs;
-//   causal: more tiles than CUs fill each other's gaps, so only up to 256 tiles, where the longest one
-//     sets the time, against the mean length of the split tiles over the CUs.
-// The kernels' callers quote what was measured on both sides.
-inline bool attn_split_pays(bool causal, long long tiles, int per_head, double steps, double fixed, double slower) {
+// Whether a launch of `whole` workgroups, the longest `steps` serial 32-row block steps each, is better run
+// as `split` workgroups of about half the chain each, on 256 CUs with one workgroup each.  In units of a
+// step of the whole form: a workgroup costs `fixed` (`fixed_split`) beside its chain (first loads, merge,
+// stores), a step of the split form `slower`.
+//   equal tiles: whole rounds over the CUs, the last one at `last` of its chain's cost if it is nearly empty
+//     (fewer workgroups share the memory) and all of it if it is full.  Beyond one round only from 24 steps on: a
+//     third round then has to pay for its fixed cost.
+//   causal: only up to 256 whole tiles, where the longest of them sets the time.  The split tiles, longest
+//     first, take their mean over the CUs, and `last` of a mean tile longer where they do not all start at once.
+// The callers' numbers are fits to 908 launches of the forward and 840 of the
+// backward (d = 64 and 128, N = 20 .. 6000, 2 .. 768 whole tiles, grouped heads among them, all forms of each timed
+// in turn).  Of these, one is more than 2 % slower than the whole form (47 causal heads of 983, d = 128: 27.3 -> 28.2 us,
+// where 48 heads of 1000 gain 8 %), and the choice stays within 0.7 % of the better form on average.  (A kernel that needs few enough registers for two workgroups
+// per CU, the dQ kernels at d = 64, blurs its rounds; the same fit holds there.)
+struct AttnSplitCost {
+  double fixed, fixed_split, slower, last;
+  double least;  // steps below which the split form saves nothing: its tiles are then as many, each with a merge
+};
+inline bool attn_split_pays(bool causal, long long whole, long long split, int split_per_head, double steps, const AttnSplitCost& c) {
+  if (steps < c.least) return false;
+  double t_whole = c.fixed + steps, t_split = c.fixed_split + 0.5 * steps * c.slower;
   if (causal) {
-    const double mean = 0.5 * (1.0 + 1.0 / per_head) * 0.5 * steps * slower + fixed;
-    const double rounds = 2.0 * (double)tiles / 256.0;
-    return tiles <= 256 && rounds * mean < steps + fixed;
+    if (whole > 256) return false;
+    if (split > 256) {
+      const double mean = c.fixed_split + 0.5 * (1.0 + 1.0 / split_per_head) * 0.5 * steps * c.slower;
+      const double all = ((double)split / 256.0 + c.last) * mean;
+      if (all > t_split) t_split = all;
+    }
+  } else {
+    if (whole > 65536 || (whole > 256 && steps < 24.0)) return false;  // (65536: the split grid stays in range)
+    auto time = [&](long long n, double fixed, double chain) {
+      const long long before = (n - 1) / 256;  // full rounds in front of the last one
+      return (double)before * (fixed + chain) + fixed + chain * (c.last + (1.0 - c.last) * (double)(n - before * 256) / 256.0);
+    };
+    t_whole = time(whole, c.fixed, t_whole - c.fixed);
+    t_split = time(split, c.fixed_split, t_split - c.fixed_split);
   }
-  if (tiles > 65536) return false;  // (nothing to gain after hundreds of rounds, and the doubled grid stays in range)
-  return (double)((2 * tiles + 255) / 256) * (0.5 * steps * slower + fixed) < (double)((tiles + 255) / 256) * (steps + fixed);
+  return t_split < t_whole;
 }
 
 // persistent bf16 forward (d = 64 or 128): `workgroups` resident workgroups drain the tile queue

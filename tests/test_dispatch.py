@@ -108,3 +108,34 @@ def test_split_tile_map_is_a_bijection_and_keeps_an_xcd_on_few_slices(tmp_path, 
     assert seen == {(s, i, j) for s in range(splits) for i in range(tiles_m) for j in range(tiles_n)}
     share = -(-total // 8)  # entries of the list an XCD takes
     assert all(max(s) - min(s) + 1 == len(s) <= (share - 1 + tiles_m * tiles_n - 1) // (tiles_m * tiles_n) + 1 for s in slices.values())
+
+
+# Sizes at which one form of the bf16 forward was measured at least 4 % faster than the other, us whole -> split
+# (heads, N, causal, d, split is faster)
+_FORMS = [(32, 1000, False, 128, True),    # 25.8 -> 20.3
+          (34, 2048, False, 128, True),    # 100.4 -> 92.0: three rounds of half tiles against two
+          (22, 4096, False, 128, True),    # 186.1 -> 172.7
+          (90, 1000, False, 128, False),   # 60.6 -> 69.8: the third round costs more than the shorter chain gives
+          (68, 1000, False, 128, False),   # 58.2 -> 63.5
+          (38, 1000, False, 128, False),   # 26.7 -> 40.5
+          (150, 150, False, 128, False),   # 10.5 -> 17.7
+          (150, 150, True, 128, False),    # 10.5 -> 16.1: 300 half tiles do not start at once
+          (150, 150, True, 64, False),     # 7.5 -> 11.4
+          (58, 1000, True, 128, False),    # 28.7 -> 31.2
+          (85, 513, True, 64, False),      # 13.2 -> 16.7
+          (32, 1000, True, 128, True),     # 25.8 -> 18.0
+          (48, 1000, True, 128, True),     # 26.3 -> 24.3
+          (16, 4096, True, 128, True),     # 84.9 -> 69.4
+          (75, 300, True, 128, True),      # 13.3 -> 11.2: 225 half tiles, fewer than the 300 that twice the tiles would be
+          (34, 4096, True, 64, False),     # 91.9 -> 110.1 at d = 128
+          (100, 64, False, 128, False),    # 5.9 -> 7.0: as many tiles either way, and a merge
+          (2, 40, False, 128, False),      # 5.3 -> 6.4
+          (100, 90, True, 64, False),      # 6.0 -> 6.4
+          (34, 2048, False, 64, True), (24, 2048, False, 64, False), (128, 2048, False, 64, False)]
+
+
+@pytest.mark.parametrize("op", ["fwd", "persistent"])
+def test_the_forward_takes_the_faster_form(op):
+    got, _ = routes([dict(op=op, H=h, N=n, causal=c, d=d) for h, n, c, d, _ in _FORMS])
+    wrong = [(f, launches) for f, (st, launches) in zip(_FORMS, got) if st != 0 or launches[-1][0].endswith(", 2>") != f[4]]
+    assert not wrong, wrong

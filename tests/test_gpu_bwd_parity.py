@@ -75,9 +75,9 @@ def test_bwd_d64_reduced_configs(ci, B, Hq, Hkv, N):
 
 
 # The cases above are few workgroups, which the launch splits: two waves share 32 rows and add their
-# partial gradients.  Here both sides of that rule: more tiles than CUs (260 heads: one tile a head, neither
-# kernel splits, or dK/dV alone does), and long enough that non-causal dQ alone (75 heads x 4 tiles, three half
-# rounds against two) or non-causal dK/dV alone (48 heads x 8 tiles) splits.
+# partial gradients.  Here sizes around that rule's lines: more tiles than CUs (260 heads: one tile a head), and
+# middle numbers of tiles, where the two kernels may take different forms (test_dispatch.py holds the rule,
+# test_gpu_kernels.py has every pair of forms).
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H,Hkv,N,causal", [(260, 260, 33, False), (260, 260, 97, True), (260, 130, 65, True), (75, 75, 799, False), (48, 48, 1000, False)])
 def test_bwd_split_rule(H, Hkv, N, causal, d):

@@ -264,9 +264,9 @@ def test_paper_grid_shapes_sampled(N, causal):
 
 
 # The cases above are few workgroups, which attn_fwd splits over the keys (two waves share 32
-# queries and merge their softmax states; the variants run both forms).  Here both sides of that rule at the edges of its tiles:
-# 75 heads x 4 tiles non-causal, 50 x 4 and 60 x 4 causal split, 260 heads of one tile do not; the queue launch
-# follows the same rule and gives the same bytes.
+# queries and merge their softmax states; the variants run both forms).  Here sizes near that rule's lines, at the
+# edges of its tiles (test_dispatch.py says which form a size takes); the queue launch follows the same rule and
+# gives the same bytes.
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H,Hkv,N,causal", [(75, 25, 897, False), (50, 50, 897, True), (60, 30, 1024, True), (260, 130, 33, False), (260, 260, 97, True), (260, 260, 256, True)])
 def test_split_rule(H, Hkv, N, causal, d):
