@@ -63,7 +63,8 @@ int gemm_bf16_nt_splitk(const void* a, const void* b, void* c, int M, int N, int
 /* bytes of fp32 workspace for that call: splits * M * N * 4 (0 for non-positive arguments) */
 long long gemm_splitk_workspace_bytes(int M, int N, int splits);
 /* The number of slices the library recommends for a shape: 1 means gemm_bf16_nt is the better
- * call (enough tiles, or too little k per slice), more means gemm_bf16_nt_splitk with that many. */
+ * call (enough tiles, or too little k per slice), more means gemm_bf16_nt_splitk with a workspace for
+ * that many, of which the call may use fewer. */
 int gemm_splitk_plan(int M, int N, int K);
 
 /* Tuning hook: the same with kernel variant `variant` (0 .. gemm_num_variants()-1), among them every

@@ -15,9 +15,9 @@ bool misaligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) !=
 // matrix work and the tile's start and end); with one workgroup per CU the launch takes whole
 // rounds over the 256 CUs, with several the rounds blur (half a round is lost at the end).
 // Operands and result at tb_s are the other bound, and 0.3 of the smaller of the two is not
-// hidden behind the larger.  Against the best tile of an exhaustive run over those shapes the choice
-// loses 2.6 % on average; against the rule it replaces (256 / 128 / 64 squares by number of
-// tiles) it is 1.8 x faster on the nt shapes (half of it from the staged stores) and 1.5 x on nn.
+// hidden behind the larger.  Over 72 nt shapes drawn apart from those of the fit (M 1 .. 321228, N 36 .. 63114, K 64 ..
+// 15040) the choice takes 3.4 % longer on average than the fastest tile, at worst 29 % (994 x 32024 x 96: 22.3 against
+// 17.3 us).  Against 256 / 128 / 64 squares by number of tiles, over 251 nt and 125 nn shapes: 1.8 x and 1.5 x faster.
 double tile_cost(const GemmTile& t, int M, int N, long long K, long long splits, double bytes) {
   if (K % t.kmult != 0) return -1.0;
   const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
@@ -67,10 +67,11 @@ const GemmTile* choose_nn(int M, int N, int K, double* cost) {
 }
 
 // Non-temporal stores of C from 96 MB on: C then does not stay in the caches and should not displace
-// the operands in them.  Measured plain -> non-temporal with the tile chosen here: 442368 x 448 x 192
-// 161.6 -> 128.0 us, 2048 x 64512 x 256 113.2 -> 89.8, 46207 x 1250 x 384 (116 MB) 73.3 -> 60.4, 8192 x 8192 x
-// 1024 140 -> 133, nn 200336 x 1432 x 256 242 -> 198; below the line 5329 x 3495 x 160 (37 MB) 16.9 -> 18.7,
-// 300000 x 100 x 512 (60 MB) 83.5 -> 85.8, nn 2763 x 9272 x 128 (51 MB) 17.3 -> 19.2.
+// the operands in them.  Measured plain -> non-temporal with the tile chosen here, buffers changing from call to
+// call: 442368 x 448 x 192 161.3 -> 159.9 us, 2048 x 64512 x 256 117.9 -> 102.0, 46207 x 1250 x 384 (116 MB) 77.6 -> 71.6,
+// 8192 x 8192 x 1024 131.0 -> 122.7, nn 200336 x 1432 x 256 243.0 -> 220.9, 589824 x 256 x 128 97.7 -> 98.4; below the line
+// 5329 x 3495 x 160 (37 MB) 18.9 -> 20.8, 300000 x 100 x 512 (60 MB) 91.1 -> 91.1, nn 2763 x 9272 x 128 (51 MB) 17.7 -> 21.1.
+// (Over the same buffers again and again it gains more, 442368 x 448 x 192 to 124: half of A stays cached.)
 int stream_c_pays(int M, int N) { return 2.0 * M * N >= 96e6 ? 1 : 0; }
 
 int launch_tile(const GemmTile* t, GemmParams& p, void* stream) {
@@ -132,8 +133,8 @@ int run_splitk(const void* a, const void* b, void* c, int M, int N, int K, int s
   // memory.  The same estimate as above, plus the partial tiles (written and read at 4 TB/s) and the
   // second launch (3 us), over 1, 2, 3, 4, 6, 9, ... slices and `splits` itself.  Measured, always 256 x 256
   // tiles and `splits` slices -> this: 234 x 74 x 21504 67 -> 8.1 us, 896 x 761 x 12288 72 -> 35, 84 x 3775 x 40000
-  // 110 -> 79, 64 x 64 x 65536 57 -> 10; where the large tile stays, its XCD map (gemm_map.h): 2304 x 1024 x 65536
-  // 357 -> 335 us with the sum kernel.
+  // 110 -> 79, 64 x 64 x 65536 57 -> 10; where the large tile stays, its XCD map (gemm_map.h) and the 16x16x32 kernel:
+  // 2304 x 1024 x 65536 357 -> 335 -> 287 us with the sum kernel (12 us of it).
   const int steps = K / 64;
   auto slice = [&](int s) { return ((steps + s - 1) / s) * 64; };  // whole 64-column steps, none empty
   const GemmTile large = {256, 256, 64, 1, 5.9f, 0.985f, 5.5f, gemm_bf16_nt_splitk_launch, 64};

@@ -13,8 +13,8 @@
 //     wave issues its share of the loads itself: on CDNA a wave that only loads would idle a
 //     SIMD, and the loads cost one issue slot each;
 //   * the product is taken transposed (MFMA A operand = rows of B, B operand = rows of A), so a
-//     lane owns one row m of C and, after one exchange between the lane halves, writes 8
-//     consecutive n with one 16-byte store;
+//     lane owns one row m of C and, after one exchange between the lane halves, 8 consecutive n;
+//     the finished tile is staged in LDS and stored along C's rows (gemm_store_staged);
 //   * 16-byte chunks of a tile row are XOR-swizzled so that the 16 lanes the LDS serves together
 //     hit 16 different bank groups;
 //   * tiles are ordered for L2 reuse inside an XCD (gemm_map.h).
@@ -29,7 +29,8 @@
 
 // One 16-byte piece of C: plain, or non-temporal when the launch streams C (GemmParams::stream_c).
 // (Written as an assembly statement: the compiler merges a plain and a non-temporal store behind a
-// run-time condition into one plain store.  It is the kernel's last memory operation.)
+// run-time condition into one plain store.  What it stores has been read from LDS before, and nothing reads C
+// afterwards; only the elements at the row ends are stored behind it.)
 #define GEMM_STORE_C(val, ptr)                                                                          \
   do {                                                                                                  \
     if (p.stream_c) asm volatile("global_store_dwordx4 %0, %1, off nt" ::"v"(ptr), "v"(val) : "memory"); \
@@ -332,7 +333,8 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
     slot = slot == NSTAGE - 1 ? 0 : slot + 1;
   }
 
-  // ---- epilogue: lane (li, h) holds, for row m, the columns n = 32 nb + 8 a + 4 h + (0..3) ---------
+  // ---- epilogue: lane (li, h) holds, for row m, the columns n = 32 nb + 8 a + 4 h + (0..3); the tile goes
+  // to LDS first and from there to C
   __syncthreads();  // no wave reads the ring any more
 #pragma unroll
   for (int mb = 0; mb < WM; ++mb) {
@@ -362,8 +364,9 @@ __global__ void __launch_bounds__(256, MINW) gemm_bf16_kernel(const GemmParams p
 // lane, lane (j, g) = row j, k 8g .. 8g+7) feeds eight MFMAs.  It is what large outputs run on where K is
 // a multiple of 64: stages of 64 k, so that a load covers whole 128-byte lines (half the L2 requests
 // of 32-wide stages), in two slots.  Bound by the board's power limit, then by the matrix pipe; the
-// 32x32x16 kernel with four 32-wide stages -> this one, us: 8192 x 8192 x 1024 134 -> 119, x 4096 427 -> 370,
-// x 8192 822 -> 702, x 16384 1866 -> 1530 (1437 TFLOP/s), 4096^3 108.6 -> 94, 16384 x 4096 x 2048 229 -> 200.
+// 32x32x16 kernel with four 32-wide stages -> this one, us, one run of the same buffers: 8192 x 8192 x 1024 134 -> 119,
+// x 4096 427 -> 370, x 8192 822 -> 702, x 16384 1866 -> 1530, 4096^3 108.6 -> 94, 16384 x 4096 x 2048 229 -> 200; with changing
+// buffers, on other boxes: x 4096 400 - 409 (1345 - 1374 TFLOP/s), x 8192 764, x 16384 1627, 4096^3 99, 16384 x 4096 x 2048 210.
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // SPLITK: the grid holds p.splits workgroups per tile; workgroup (split, tile) contracts its slice
