@@ -328,6 +328,32 @@ def test_hidden_keys_in_front(d, N, score):
             gu.check_full(inp, o, lse, f"hidden keys in front {name} N={N} score={score} d={d} variant {var}")
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_nan_inputs_stay_visible(d, causal):
+    """A NaN in a query row, a key or a value reaches every output that depends on it, and no other.  (Causal rows
+    192 .. 199 multiply the value of key 200 by a probability of zero, which is NaN, too: not looked at.)"""
+    rng = np.random.default_rng(47 + d)
+    N, H = 300, 3
+    q, k, v = (rng.standard_normal((1, H, N, d)).astype(np.float32) for _ in range(3))
+    q[0, 0, 133, 7] = k[0, 1, 70, 2] = v[0, 2, 200, 5] = np.nan
+    inp = _custom(q, k, v, causal, 1.0 / d ** 0.5)
+    dev = gu.to_device(inp)
+    want_o, want_l = np.zeros((H, N, d), bool), np.zeros((H, N), bool)
+    rows = np.arange(N)
+    want_o[0, 133], want_l[0, 133] = True, True
+    sees = (lambda key: rows >= key) if causal else (lambda key: rows >= 0)
+    want_o[1, sees(70)], want_l[1, sees(70)] = True, True
+    want_o[2, sees(200), 5] = True
+    for var in [None] + _variants(d):
+        print(f"NaN inputs causal={causal} d={d} variant {var}", flush=True)
+        o, lse = gu.run_gpu(inp, dev, var)
+        wrong = np.isnan(gu.o_to_f64(o)[0]) != want_o
+        wrong[2, 192:200] = False
+        assert not wrong.any(), f"variant {var}: {np.argwhere(wrong)[:4]}"
+        assert np.array_equal(np.isnan(lse.cpu().numpy()[0]), want_l), f"variant {var}"
+
+
 # ---- persistent launch with the dynamic tile queue ------------------------------------------------
 def _run_persistent(inp, dev, queue_fill=0x7F):
     import paper_2605_10905_amd as A
