@@ -14,7 +14,7 @@
 //   * attn_bwd_dq_kernel: a workgroup owns 256 query rows (128 when the launch is small; Q and dO rows stationary in registers
 //     as MFMA B operands, one query per lane, exactly the forward layout) and streams K/V tiles:
 //     S^T = K Q^T, dP^T = V dO^T, dS^T in registers, dQ^T += K^T dS^T.  It also writes the two
-//     per-row vectors the other kernel needs, delta and lse * log2(e), into the workspace.
+//     per-row vectors the other kernel needs, -delta and lse * log2(e), into the workspace.
 //   * attn_bwd_dkv_pipe_kernel: a workgroup owns 128 keys (64 when the launch is small; K and V rows stationary, one key per
 //     lane) and streams Q/dO tiles of every query head of its group: S = Q K^T, dP = dO V^T, P,
 //     dS = P * (dP - delta), dV^T += dO^T P, dK^T += Q^T dS.
@@ -31,6 +31,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "attn_device.h"
 #include "attn_kernels.h"
@@ -76,6 +77,11 @@ struct BwdCommon {
   static constexpr int NLD = BN * NCH / NT;
   static constexpr int LDS_BYTES = AUXBASE + NSLOT * 512;
 };
+
+template <class F, int... M>
+__device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M...>) {
+  (f(ic<M>{}), ...);
+}
 
 // store a transposed accumulator (lane (ci,h) holds rows 32cb + 8a + 4h + r of column ci) as
 // row `row` of a [.., D] bf16 matrix, scaled; the two lane halves exchange so that every lane
@@ -183,11 +189,11 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
   }
   const float lse2 = p.lse[(size_t)(tc.b * p.Hq + tc.hq) * N + min(qrow, N - 1)] * kLog2e;
   // workspace for the key-side kernels, padded to whole 64-row tiles: rows past N get a
-  // statistic of +inf (their probabilities come out as zero) and delta = 0
+  // statistic of +inf (their probabilities come out as zero) and delta = 0; delta is kept negated
   if (kg == 0 && h == 0 && qrow < p.Npad) {
     float* const wsrow = p.ws + (size_t)(tc.b * p.Hq + tc.hq) * 2 * p.Npad;
     wsrow[qrow] = qrow < N ? lse2 : INFINITY;
-    wsrow[p.Npad + qrow] = qrow < N ? delta : 0.f;
+    wsrow[p.Npad + qrow] = qrow < N ? -delta : 0.f;
   }
   if (nt > 1) issue_tile(1, 1);
 
@@ -323,9 +329,16 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
 // wave is software-pipelined: a step works on three 32-query blocks at once, the score products of
 // block i+1, the exponentials and dS of block i, and the gradient products of block i-1.  The 32
 // MFMAs of a step depend on none of its vector work.  Instruction order inside a step is fixed by
-// hand (one MFMA per slot, operands requested two groups of four slots ahead, the vector work of
-// one row per slot) and fenced slot by slot.  The ring has four slots because a step touches three
+// hand (one MFMA per slot, operands requested two groups of four slots ahead, a row's vector work spread over
+// three slots so that no instruction waits for the one before it, one load of the tile three ahead every few slots)
+// and fenced slot by slot.  The ring has four slots because a step touches three
 // tiles, and the loop is unrolled over them so that every LDS offset is an immediate.
+// One wave per SIMD hides nothing it does not hide itself, so every instruction counts: the gradients and the
+// stationary rows are pinned to accumulation registers, which leaves the scores in ordinary ones (the vector work had
+// fetched them with 64 register moves a step), dP starts from -delta, and the loads are handed out singly (nine in a row behind the barrier stopped
+// all products until the address unit had taken them).  Cycles of this kernel, 4 x 64/8 heads x 4096 causal: 4.13 M -> 3.60 M
+// (matrix pipe 52 -> 60 % of them), time 2.11 -> 1.95 ms at a clock that the power limit lowers; the whole backward of
+// 2 x 16 heads x 1000, d = 64 44.9 -> 43.1 us, of 3 x 48/12 x 835 232 -> 221.
 // Every block of every tile is computed by every wave: a block that is invisible to the wave's keys
 // (causal) or past the end (ragged) contributes exact zeros through the -inf scores and the +inf
 // statistic of the padded workspace rows, and the slowest wave of the workgroup computes it anyway.
@@ -367,6 +380,7 @@ struct BwdPipe {
   static constexpr int read_target(int m) { return (m / 4 + RA / 4) * 4 + 3 - m % 4; }
   static constexpr int VP0 = 6;                                                       // first slot with vector work
   static constexpr int vslot(int r) { return VP0 + (r * (NM - VP0)) / 16; }            // slot of row r's vector work
+  static constexpr int dslot(int a) { return a; }  // slots that read -delta of the next block's rows 4a..4a+3 (its first dP product: slot RA + 2)
   static constexpr int aslot(int a) { return vslot(4 * a) - 6 > 0 ? vslot(4 * a) - 6 : 0; }  // slot that reads the statistics of rows 4a..4a+3
 };
 
@@ -378,7 +392,7 @@ struct BwdPipe {
 template <int D, bool CAUSAL, int QS>
 __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwdParams p) {
   using C = BwdPipe<D>;
-  constexpr int NKK = C::NKK, NCB = C::NCB, ROWB = C::ROWB, NCH = C::NCH, TILEB = C::TILEB, SUBB = C::SUBB, NSLOT = C::NSLOT;
+  constexpr int NKK = C::NKK, NCB = C::NCB, ROWB = C::ROWB, NCH = C::NCH, TILEB = C::TILEB, SUBB = C::SUBB;
   constexpr int NLD = C::NLD, NT = C::NT, BN = C::BN, NKW = C::NWAVES / QS, BM = NKW * 32, NM = C::NM, RA = C::RA;
   static_assert(QS == 1 || QS == 2, "a tile has two query blocks");
 
@@ -405,14 +419,13 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   const int qt0 = CAUSAL ? k0 / BN : 0;
   const int nt = G * (nqt_all - qt0);
 
-  int ld_row[NLD];
-  uint32_t ld_off[NLD];
+  uint32_t ld_off[NLD], ld_off_r[NLD];  // ("_r": inside the ragged last tile, whose rows past N-1 re-read row N-1)
 #pragma unroll
   for (int it = 0; it < NLD; ++it) {
     const int s = it * NT + tid;
     const int r = s / NCH, c = s % NCH;
-    ld_row[it] = r;
     ld_off[it] = r * ROWB + ((c ^ swz_rt<ROWB>(r)) << 4);
+    ld_off_r[it] = ld_off[it] - (uint32_t)max(0, (N - 1) / BN * BN + r - (N - 1)) * ROWB;
   }
   const uint32_t lds_base = (uint32_t)(uintptr_t)smem;
   const uint32_t lds_wave = lds_base + w * 1024;
@@ -429,23 +442,19 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   const char* iss_do = (const char*)p.dout + (size_t)(tc.b * p.Hq + g * G) * head_bytes + (size_t)iss_qt * TILEB;
   const float* iss_ws = p.ws + (size_t)(tc.b * p.Hq + g * G) * 2 * p.Npad + (size_t)iss_qt * BN;
   const uint32_t aoff = (uint32_t)(((lane & 15) * 4 + ((lane >> 4) & 1) * p.Npad) * 4);
-  const bool ragged = (N % BN) != 0;
-  auto issue_next = [&](int slot) __attribute__((always_inline)) {
-    if (ragged && iss_qt == nqt_all - 1) {
-#pragma unroll
-      for (int it = 0; it < NLD; ++it) {
-        const uint32_t over = (uint32_t)max(0, iss_qt * BN + ld_row[it] - (N - 1)) * ROWB;  // rows past N-1 re-read row N-1
-        attn_lds_dma16(iss_q, ld_off[it] - over, lds_wave + slot * TILEB + it * NT * 16);
-        attn_lds_dma16(iss_do, ld_off[it] - over, lds_wave + C::T2BASE + slot * TILEB + it * NT * 16);
-      }
-    } else {
-#pragma unroll
-      for (int it = 0; it < NLD; ++it) {
-        attn_lds_dma16(iss_q, ld_off[it], lds_wave + slot * TILEB + it * NT * 16);
-        attn_lds_dma16(iss_do, ld_off[it], lds_wave + C::T2BASE + slot * TILEB + it * NT * 16);
-      }
+  // load i of that tile into ring slot `slot`: Q and dO pieces, last the workspace rows; issue_advance() goes on to
+  // the tile after it
+  constexpr int LPT = 2 * NLD + 1;  // loads per thread and tile
+  auto issue_load = [&](int slot, int i) __attribute__((always_inline)) {
+    if (i == 2 * NLD) {
+      if (lane < 32) attn_lds_dma16(iss_ws, aoff, lds_base + C::AUXBASE + slot * 512);
+      return;
     }
-    if (lane < 32) attn_lds_dma16(iss_ws, aoff, lds_base + C::AUXBASE + slot * 512);
+    const int it = i >> 1;
+    const uint32_t off = iss_qt == nqt_all - 1 ? ld_off_r[it] : ld_off[it];
+    attn_lds_dma16((i & 1) ? iss_do : iss_q, off, lds_wave + ((i & 1) ? C::T2BASE : 0) + slot * TILEB + it * NT * 16);
+  };
+  auto issue_advance = [&]() __attribute__((always_inline)) {
     const bool wrap = ++iss_h == G;  // back to the group's first query head, one tile down
     iss_q += wrap ? wrap_bytes : head_bytes;
     iss_do += wrap ? wrap_bytes : head_bytes;
@@ -453,7 +462,11 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
     iss_h = wrap ? 0 : iss_h;
     iss_qt -= wrap ? 1 : 0;
   };
-  constexpr int LPT = 2 * NLD + 1;  // loads per thread and tile
+  auto issue_next = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) issue_load(slot, i);
+    issue_advance();
+  };
   issue_next(0);
 
   bf16x8 kf[NKK], vf[NKK];
@@ -475,6 +488,11 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_dv[cb][r] = acc_dk[cb][r] = 0.f;
+  auto grads_settled = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) asm volatile("s_nop 15" : "+a"(acc_dv[cb]), "+a"(acc_dk[cb]));
+  };
+  grads_settled();
 
   // LDS read addresses.  Inside the ring every offset (slot, 32-row half, 16-row group) is a
   // compile-time immediate of the read instruction; the second tensor's slots lie beyond the
@@ -484,6 +502,7 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   for (int kk = 0; kk < NKK; ++kk) {
     raddr[0][kk] = qg * SUBB + ki * ROWB + (((2 * kk + h) ^ swz_rt<ROWB>(ki)) << 4);
     raddr[1][kk] = raddr[0][kk] + C::T2BASE;
+    asm volatile("" : "+v"(raddr[1][kk]));
   }
   uint32_t taddr[2][NCB][2];
   {
@@ -496,6 +515,7 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
         const int chunk = cb * 4 + chalf * 2 + ((s & 3) >> 1);
         taddr[0][cb][e] = qg * SUBB + row * ROWB + ((chunk ^ swz_rt<ROWB>(row)) << 4) + ((s & 1) << 3);
         taddr[1][cb][e] = taddr[0][cb][e] + C::T2BASE;
+        asm volatile("" : "+v"(taddr[1][cb][e]));
       }
   }
   const uint32_t auxaddr = C::AUXBASE + qg * 128 + 16 * h;
@@ -513,54 +533,80 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   auto grad_operand = [&](int off, int i) __attribute__((always_inline)) { return tr_operand((i & 1) ? 0 : 1, off, (i >> 1) % NCB, (i >> 1) / NCB); };
   // operand of score product i of the block at `off`: S += Q K^T (even i), dP += dO V^T (odd i)
   auto score_operand = [&](int off, int i) __attribute__((always_inline)) { return row_operand(i & 1, off, i >> 1); };
-  auto grad_mfma = [&](int i, u32x4 o, const u32x4 (&pp)[2], const u32x4 (&pd)[2]) __attribute__((always_inline)) {
+  // The gradients are accumulated by assembly statements that pin them to accumulation registers , which
+  // the compiler's wait-state insertion does not look into.  In a step the packed P and dS are written a whole step before
+  // they are read here and nothing but these products touches the accumulators; behind the loop, `copied`
+  // covers operands that were just moved (2 wait states) and grads_settled() the readers of the result (8 passes: 12).
+  auto grad_mfma = [&](int i, u32x4 o, const u32x4 (&pp)[2], const u32x4 (&pd)[2], auto copied) __attribute__((always_inline)) {
     const int cb = (i >> 1) % NCB, kc = (i >> 1) / NCB;
-    if (i & 1) acc_dk[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, o), __builtin_bit_cast(bf16x8, pd[kc]), acc_dk[cb], 0, 0, 0);
-    else acc_dv[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, o), __builtin_bit_cast(bf16x8, pp[kc]), acc_dv[cb], 0, 0, 0);
+    if constexpr (decltype(copied)::value) {
+      if (i & 1) asm volatile("s_nop 3\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc_dk[cb]) : "v"(o), "v"(pd[kc]));
+      else asm volatile("s_nop 3\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc_dv[cb]) : "v"(o), "v"(pp[kc]));
+      return;
+    }
+    if (i & 1) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc_dk[cb]) : "v"(o), "v"(pd[kc]));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc_dv[cb]) : "v"(o), "v"(pp[kc]));
   };
 
   const float c = p.scale_log2;
 
   u32x4 pre[RA];  // operands of the next step's first RA MFMAs
+  // slots between the loads of a tile, slot of the first one (QS = 2 waits for them one step later: as early as they go)
+  constexpr int LGAP = QS == 1 ? NM / LPT : 1, LFIRST = QS == 1 ? NM - LPT * LGAP : 0;
   // One step.  (s_in, dp_in): finished scores of the block at CUR whose first query row is q0b;
   // (s_out, dp_out) <- scores of the block at NEXT; (pp_out, pd_out) <- P and dS of the block at
   // CUR; (pp_acc, pd_acc): P and dS of the block at PREV, multiplied into dV and dK.  PREV, CUR,
   // NEXT are compile-time offsets inside the ring, AUX the offset of CUR's statistics.
   auto step = [&](f32x16& s_in, f32x16& dp_in, f32x16& s_out, f32x16& dp_out, u32x4 (&pp_out)[2], u32x4 (&pd_out)[2],
-                  const u32x4 (&pp_acc)[2], const u32x4 (&pd_acc)[2], auto PREV, auto CUR, auto NEXT, auto AUX,
-                  int q0b) __attribute__((always_inline)) {
-    constexpr int prev = decltype(PREV)::value, cur = decltype(CUR)::value, next = decltype(NEXT)::value, auxo = decltype(AUX)::value;
+                  const u32x4 (&pp_acc)[2], const u32x4 (&pd_acc)[2], auto PREV, auto CUR, auto NEXT, auto AUX, auto AUXN,
+                  int q0b, bool load, auto LSLOT) __attribute__((always_inline)) {
+    constexpr int prev = decltype(PREV)::value, cur = decltype(CUR)::value, next = decltype(NEXT)::value;
+    constexpr int auxo = decltype(AUX)::value, auxn = decltype(AUXN)::value;
     u32x4 op[NM];
+    f32x16 dn;  // -delta of the rows of the block at NEXT: dP starts from it
 #pragma unroll
     for (int m = 0; m < RA; ++m) op[m] = pre[m];
-    f32x4 l4[4], d4[4];
-    float e_even = 0.f, f_even = 0.f;
+    f32x4 l4[4];
+    float x[16], e[16], f[16];
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int m = 0; m < NM; ++m) {
+    auto one_slot = [&](auto slot_tag) __attribute__((always_inline)) {
+      constexpr int m = decltype(slot_tag)::value;
       // LDS reads: the operand of slot m + RA, and the statistics of the rows handled six slots on
       {
-        const int t = C::read_target(m);
-        if (t < NM) op[t] = C::is_score(t) ? score_operand(next, C::index(t)) : grad_operand(prev, C::index(t));
+        constexpr int t = C::read_target(m);
+        if constexpr (t < NM) op[t] = C::is_score(t) ? score_operand(next, C::index(t)) : grad_operand(prev, C::index(t));
         else pre[t - NM] = grad_operand(cur, t - NM);
       }
 #pragma unroll
       for (int a = 0; a < 4; ++a)
+        if (C::dslot(a) == m) {
+          const f32x4 t = *(const LDS_AS f32x4*)(smem + auxaddr + auxn + 256 + 32 * a);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dn[4 * a + r] = t[r];
+        }
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
         if (C::aslot(a) == m) {
           l4[a] = *(const LDS_AS f32x4*)(smem + auxaddr + auxo + 32 * a);
-          d4[a] = *(const LDS_AS f32x4*)(smem + auxaddr + auxo + 256 + 32 * a);
         }
       // the matrix product of this slot
       const int i = C::index(m);
       if (C::is_score(m)) {
         if (i == 0 || i == 1) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) (i ? dp_out : s_out)[r] = 0.f;
+          for (int r = 0; r < 16; ++r) (i ? dp_out : s_out)[r] = i ? dn[r] : 0.f;
         }
         if (i & 1) dp_out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op[m]), vf[i >> 1], dp_out, 0, 0, 0);
         else s_out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op[m]), kf[i >> 1], s_out, 0, 0, 0);
       } else {
-        grad_mfma(i, op[m], pp_acc, pd_acc);
+        grad_mfma(i, op[m], pp_acc, pd_acc, std::false_type{});
+      }
+      // the next tile's loads, one at a time: all of them behind the barrier keep the wave from issuing products until
+      // the address unit has taken them
+      if constexpr (decltype(LSLOT)::value >= 0) {
+        if constexpr (m >= LFIRST && (m - LFIRST) % LGAP == 0 && (m - LFIRST) / LGAP < LPT) {
+          if (load) issue_load(decltype(LSLOT)::value, (m - LFIRST) / LGAP);
+        }
       }
       // causal diagonal: -inf scores for the queries before this lane's key (wave-uniform branch)
       if (CAUSAL && m == C::VP0 - 1 && q0b < wk0 + 31) {
@@ -568,22 +614,23 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
         for (int r = 0; r < 16; ++r)
           if (q0b + 8 * (r >> 2) + 4 * h + (r & 3) < krow) s_in[r] = -INFINITY;
       }
-      // vector work: P = exp2(s c - lse2), dS = P (dP - delta) for the rows of this slot
+      // vector work of row r, one link of its chain per slot: P = exp2(s c - lse2), dS = P (dP - delta), packs
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (C::vslot(r) == m) {
-          const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s_in[r], c, -l4[r >> 2][r & 3]));
-          const float f = e * (dp_in[r] - d4[r >> 2][r & 3]);
+      for (int r = 0; r < 16; ++r) {
+        if (C::vslot(r) - 1 == m) x[r] = __builtin_fmaf(s_in[r], c, -l4[r >> 2][r & 3]);
+        if (C::vslot(r) == m) e[r] = __builtin_amdgcn_exp2f(x[r]);
+        if (C::vslot(r) + 1 == m || (m == NM - 1 && C::vslot(r) + 1 > m)) {
+          f[r] = e[r] * dp_in[r];
           if (r & 1) {
-            pp_out[r >> 3][(r >> 1) & 3] = pack_bf16(e_even, e);
-            pd_out[r >> 3][(r >> 1) & 3] = pack_bf16(f_even, f);
-          } else {
-            e_even = e;
-            f_even = f;
+            pp_out[r >> 3][(r >> 1) & 3] = pack_bf16(e[r - 1], e[r]);
+            pd_out[r >> 3][(r >> 1) & 3] = pack_bf16(f[r - 1], f[r]);
           }
         }
+      }
       __builtin_amdgcn_sched_barrier(0);
-    }
+    };
+    for_each_slot(one_slot, std::make_integer_sequence<int, NM>{});
+    asm volatile("" : "+v"(pp_out[0]), "+v"(pp_out[1]), "+v"(pd_out[0]), "+v"(pd_out[1]));  // (made here, not put off to where they are read)
   };
 
   // the block "before the first" lives in the last half of slot 3 (QS = 2: a wave's half of it):
@@ -601,7 +648,7 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   else if (nt > 1) ATTN_WAIT_VMCNT(LPT);
   else ATTN_WAIT_VMCNT(0);
 #pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) asm volatile("" ::"v"(kf[kk]), "v"(vf[kk]));
+  for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+a"(kf[kk]), "+a"(vf[kk]));
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the zero fill is written
   attn_wg_barrier();
 
@@ -609,14 +656,20 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   f32x16 sa, dpa, sb, dpb;
   u32x4 ppa[2], pda[2], ppb[2], pdb[2];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) sa[r] = dpa[r] = 0.f;
+  for (int r = 0; r < 16; ++r) {
+    sa[r] = 0.f;
+    dpa[r] = *(const LDS_AS float*)(smem + auxaddr + 256 + 32 * (r >> 2) + 4 * (r & 3));
+  }
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) {
     sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, row_operand(0, 0, kk)), kf[kk], sa, 0, 0, 0);
     dpa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, row_operand(1, 0, kk)), vf[kk], dpa, 0, 0, 0);
   }
 #pragma unroll
-  for (int t = 0; t < 2; ++t) ppb[t] = pdb[t] = u32x4{0u, 0u, 0u, 0u};
+  for (int t = 0; t < 2; ++t) {
+    ppb[t] = pdb[t] = u32x4{0u, 0u, 0u, 0u};
+    asm volatile("s_nop 1" : "+v"(ppb[t]), "+v"(pdb[t]));  // (not to be made again in front of the first product)
+  }
 #pragma unroll
   for (int m = 0; m < RA; ++m) pre[m] = grad_operand(BEFORE, m);
 
@@ -627,6 +680,10 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
       --qt;
     }
   };
+  // QS = 2: tiles 0, 1 and 2 are requested up front.  (Behind a statement, so that no step is split off the loop: the
+  // copies that takes would move the accumulators.)
+  int first_load = 1;
+  asm volatile("" : "+s"(first_load));
   // tile j lives in slot j % 4 = S
   auto tile = [&](auto S, int j) __attribute__((always_inline)) {
     constexpr int s = decltype(S)::value;
@@ -635,23 +692,25 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
       // (tiles 0, 1 and 2 are requested by the prologue, later ones one step ahead)
       ATTN_WAIT_VMCNT(0);
       attn_wg_barrier();
-      if (j >= 1 && j + 2 < nt) issue_next((s + 2) & 3);
+      const bool load = j >= first_load && j + 2 < nt;
       constexpr int o = s * TILEB, op = ((s + 3) & 3) * TILEB, on = ((s + 1) & 3) * TILEB;
       const int q0b = qt * BN + qg * 32;
-      if constexpr (s & 1) step(sb, dpb, sa, dpa, ppb, pdb, ppa, pda, ic<op>{}, ic<o>{}, ic<on>{}, ic<s * 512>{}, q0b);
-      else step(sa, dpa, sb, dpb, ppa, pda, ppb, pdb, ic<op>{}, ic<o>{}, ic<on>{}, ic<s * 512>{}, q0b);
+      if constexpr (s & 1) step(sb, dpb, sa, dpa, ppb, pdb, ppa, pda, ic<op>{}, ic<o>{}, ic<on>{}, ic<s * 512>{}, ic<((s + 1) & 3) * 512>{}, q0b, load, ic<(s + 2) & 3>{});
+      else step(sa, dpa, sb, dpb, ppa, pda, ppb, pdb, ic<op>{}, ic<o>{}, ic<on>{}, ic<s * 512>{}, ic<((s + 1) & 3) * 512>{}, q0b, load, ic<(s + 2) & 3>{});
+      if (load) issue_advance();
       next_qt();
       return;
     }
     constexpr int b0 = s * TILEB, b1 = b0 + SUBB, bp = ((s + 3) & 3) * TILEB + SUBB, bn = ((s + 1) & 3) * TILEB;
     const int q0b = qt * BN;
-    step(sa, dpa, sb, dpb, ppa, pda, ppb, pdb, ic<bp>{}, ic<b0>{}, ic<b1>{}, ic<s * 512>{}, q0b);
+    step(sa, dpa, sb, dpb, ppa, pda, ppb, pdb, ic<bp>{}, ic<b0>{}, ic<b1>{}, ic<s * 512>{}, ic<s * 512 + 128>{}, q0b, false, ic<-1>{});
     // tile j+1 has landed (the loads of tile j+2 stay in flight); every wave is done with tile j-1
     if (j + 2 < nt) ATTN_WAIT_VMCNT(LPT);
     else ATTN_WAIT_VMCNT(0);
     attn_wg_barrier();
-    if (j + 3 < nt) issue_next((s + 3) & 3);
-    step(sb, dpb, sa, dpa, ppb, pdb, ppa, pda, ic<b0>{}, ic<b1>{}, ic<bn>{}, ic<s * 512 + 128>{}, q0b + 32);
+    const bool load = j + 3 < nt;
+    step(sb, dpb, sa, dpa, ppb, pdb, ppa, pda, ic<b0>{}, ic<b1>{}, ic<bn>{}, ic<s * 512 + 128>{}, ic<((s + 1) & 3) * 512>{}, q0b + 32, load, ic<(s + 3) & 3>{});
+    if (load) issue_advance();
     next_qt();
   };
   int j = 0;
@@ -672,9 +731,10 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   if constexpr (QS == 1) {
     const int last = ((nt - 1) & 3) * TILEB + SUBB;
 #pragma unroll
-    for (int i = RA; i < C::NG; ++i) grad_mfma(i, grad_operand(last, i), ppb, pdb);
+    for (int i = RA; i < C::NG; ++i) grad_mfma(i, grad_operand(last, i), ppb, pdb, std::true_type{});
 #pragma unroll
-    for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], ppb, pdb);
+    for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], ppb, pdb, std::true_type{});
+    grads_settled();
     const size_t roff = koff + (size_t)min(krow, N - 1) * ROWB;
     store_transposed<NCB>(acc_dv, 1.0f, (char*)p.dv + roff, h, krow < N);
     store_transposed<NCB>(acc_dk, p.scale, (char*)p.dk + roff, h, krow < N);
@@ -689,9 +749,10 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
       }
     }
 #pragma unroll
-    for (int i = RA; i < C::NG; ++i) grad_mfma(i, grad_operand(last, i), ppb, pdb);
+    for (int i = RA; i < C::NG; ++i) grad_mfma(i, grad_operand(last, i), ppb, pdb, std::true_type{});
 #pragma unroll
-    for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], ppb, pdb);
+    for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], ppb, pdb, std::true_type{});
+    grads_settled();
     const size_t roff = koff + (size_t)min(krow, N - 1) * ROWB;
     __syncthreads();  // no wave reads the ring any more
     LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((qg ^ 1) * NKW + w % NKW) * (NCB * 4) * 64 + lane;
