@@ -11,8 +11,8 @@
 // Two kernels, neither of which uses atomics or a reduction across workgroups, so the result is
 // deterministic and no gradient needs an fp32 accumulation buffer in memory:
 //
-//   * attn_bwd_dq_kernel: a workgroup owns 256 query rows (128 when the launch is small; Q and dO rows stationary in registers
-//     as MFMA B operands, one query per lane, exactly the forward layout) and streams K/V tiles:
+//   * attn_bwd_dq_kernel: a workgroup owns 128 query rows (64 when the launch is small; Q and dO rows stationary in
+//     registers as MFMA B operands, one query per lane, exactly the forward layout) and streams K/V tiles:
 //     S^T = K Q^T, dP^T = V dO^T, dS^T in registers, dQ^T += K^T dS^T.  It also writes the two
 //     per-row vectors the other kernel needs, -delta and lse * log2(e), into the workspace.
 //   * attn_bwd_dkv_pipe_kernel: a workgroup owns 128 keys (64 when the launch is small; K and V rows stationary, one key per
@@ -67,17 +67,6 @@ __device__ __forceinline__ constexpr int swz_rt(int row) {
   return ROWB == 256 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
 }
 
-template <int D_>
-struct BwdCommon {
-  static constexpr int D = D_, BN = 64, NWAVES = 8, BM = NWAVES * 32, NT = NWAVES * 64;
-  static constexpr int NKK = D / 16, NCB = D / 32, ROWB = D * 2, NCH = ROWB / 16;
-  static constexpr int TILEB = BN * ROWB, SUBB = 32 * ROWB, NSLOT = 3;
-  static constexpr int T2BASE = NSLOT * TILEB;       // second streamed tensor's slots
-  static constexpr int AUXBASE = 2 * NSLOT * TILEB;  // per-slot 512 bytes: lse*log2e and delta of the tile's 64 rows
-  static constexpr int NLD = BN * NCH / NT;
-  static constexpr int LDS_BYTES = AUXBASE + NSLOT * 512;
-};
-
 template <class F, int... M>
 __device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M...>) {
   (f(ic<M>{}), ...);
@@ -110,19 +99,46 @@ __device__ __forceinline__ void store_transposed(const f32x16 (&acc)[NCB], float
 
 // =====================================================================================================
 // dQ (and the workspace vectors)
+// Four waves, one per SIMD, each with 32 queries (Q and dO rows stationary) and up to the whole register file.  K and V
+// tiles are streamed, and a step works on three 32-key blocks at once: the score products of block i+1, the
+// exponentials and dS of block i, the gradient products of block i-1; none of a step's MFMAs depends on its vector
+// work.  A slot is one MFMA with a share of the vector work, the LDS reads of the operand RA slots ahead and, in one step
+// per tile, a load of the tile three ahead.  The gradient products come first, and all their operands were requested by
+// the step before: the ring's slot of tile j-1 is free when tile j begins.
+// Eight waves of 32 queries, two per SIMD, block by block without the pipeline -> this, whole backward: 2 x 1 heads x 656
+// causal 49.4 -> 41.3 us (KS = 2: 37.7), 2 x 16 x 1000, d = 64 42.3 -> 40.1, 3 x 48/12 x 835 220 -> 211, 5 x 4/2 x 3220 438 -> 405 (381),
+// 2 x 32 x 8192 6610 -> 6490; 4 x 16 x 2048 causal 262 -> 267 (the 256-row workgroup read K and V half as often).  Two query
+// blocks per wave (half the LDS reads; a 256-row workgroup again): 4 x 64/8 x 4096 causal 3524 -> 3476, 2 x 32 x 8192 6490 -> 6540,
+// and 5 - 45 % slower wherever the launch is small.
+// KS = 2, for launches that leave CUs idle: the workgroup owns 64 queries, waves w and w + 2 share 32
+// of them, one takes the first key block of every tile, the other the second, and the two partial dQ are added through
+// LDS at the end.
 // =====================================================================================================
-// KS = 1: the 8 waves own 32 queries each and compute both 32-key blocks of every tile.
-// KS = 2, for launches that leave CUs idle: a workgroup owns 128 queries; waves w and w + 4 share 32
-// of them, one takes the first key block of every tile, the other the second, and the two partial
-// dQ are added through LDS at the end: twice the workgroups, half the serial chain.
-template <int D, bool CAUSAL, int KS>
-__global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams p) {
-  using C = BwdCommon<D>;
-  constexpr int NKK = C::NKK, NCB = C::NCB, ROWB = C::ROWB, NCH = C::NCH, TILEB = C::TILEB, SUBB = C::SUBB, NSLOT = C::NSLOT;
-  constexpr int NLD = C::NLD, NT = C::NT, BN = C::BN, NQW = C::NWAVES / KS, BM = NQW * 32;
-  static_assert(KS == 1 || (KS == 2 && NQW * NCB * 2048 <= 2 * NSLOT * TILEB), "the exchanged halves of dQ fit the ring");
+template <int D_>
+struct DqPipe {
+  static constexpr int D = D_, BN = 64, NWAVES = 4, NT = NWAVES * 64;
+  static constexpr int NKK = D / 16, NCB = D / 32, ROWB = D * 2, NCH = ROWB / 16;
+  static constexpr int TILEB = BN * ROWB, SUBB = 32 * ROWB, NSLOT = 4;
+  static constexpr int T2BASE = NSLOT * TILEB;
+  static constexpr int NLD = BN * NCH / NT, LPT = 2 * NLD;  // loads per thread: of one tensor's tile, of both
+  static constexpr int NS = 2 * NKK, NG = 2 * NCB;  // fragments of the score (K, V by turns) and of the gradient products of a block
+  static constexpr int NM = NS + NG;                // 24 (d = 128) or 12 (d = 64)
+  static constexpr int RA = NG;                     // slots 0 .. RA-1: gradient products
+  static_assert(RA % 4 == 0 && NM % 4 == 0 && NM >= 2 * RA && NM / LPT >= 1, "schedule shape");
+  // as in BwdPipe: groups of four slots, inside a group in the reverse of the order of use
+  static constexpr int read_target(int m) { return (m / 4 + RA / 4) * 4 + 3 - m % 4; }
+  static constexpr int VP0 = 3;
+  static constexpr int vslot(int r) { return VP0 + (r * (NM - VP0)) / 16; }  // slot of row r's exponential
+};
 
-  __shared__ __attribute__((aligned(1024))) char smem_raw[2 * NSLOT * TILEB];
+template <int D, bool CAUSAL, int KS>
+__global__ void __launch_bounds__(256, 1) attn_bwd_dq_kernel(const AttnBwdParams p) {
+  using C = DqPipe<D>;
+  constexpr int NKK = C::NKK, NCB = C::NCB, ROWB = C::ROWB, NCH = C::NCH, TILEB = C::TILEB, SUBB = C::SUBB;
+  constexpr int NLD = C::NLD, LPT = C::LPT, NT = C::NT, BN = C::BN, NQW = C::NWAVES / KS, BM = NQW * 32, NM = C::NM, RA = C::RA;
+  static_assert(KS == 1 || KS == 2, "a tile has two key blocks");
+
+  __shared__ __attribute__((aligned(1024))) char smem_raw[2 * C::NSLOT * TILEB];
   LDS_AS char* const smem = (LDS_AS char*)smem_raw;
 
   const int tid = threadIdx.x;
@@ -135,40 +151,43 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
   const int q0 = tc.t * BM;
   const int kg = KS == 1 ? 0 : w / NQW;  // which key block of a tile this wave computes (KS = 2)
   const int wq0 = q0 + (KS == 1 ? w : w % NQW) * 32;
-  const bool wave_valid = wq0 < N;
+
   const int qrow = wq0 + qi;
 
   const size_t qoff = ((size_t)(tc.b * p.Hq + tc.hq) * N) * ROWB;
-  const char* const khead = (const char*)p.k + ((size_t)(tc.b * p.Hkv + hk) * N) * ROWB;
-  const char* const vhead = (const char*)p.v + ((size_t)(tc.b * p.Hkv + hk) * N) * ROWB;
-
   const int kv_end = CAUSAL ? min(N, q0 + BM) : N;
-  const int nt = (kv_end + BN - 1) / BN;
+  const int nt = (kv_end + BN - 1) / BN, nt_all = (N + BN - 1) / BN;
 
-  // ---- producer role ------------------------------------------------------------------------------
-  int ld_row[NLD];
-  uint32_t ld_off[NLD];
+  uint32_t ld_off[NLD], ld_off_r[NLD];  // ("_r": inside the ragged last tile, whose rows past N-1 re-read row N-1)
 #pragma unroll
   for (int it = 0; it < NLD; ++it) {
     const int s = it * NT + tid;
     const int r = s / NCH, c = s % NCH;
-    ld_row[it] = r;
     ld_off[it] = r * ROWB + ((c ^ swz_rt<ROWB>(r)) << 4);
+    ld_off_r[it] = ld_off[it] - (uint32_t)max(0, (N - 1) / BN * BN + r - (N - 1)) * ROWB;
   }
   const uint32_t lds_wave = (uint32_t)(uintptr_t)smem + w * 1024;
-  auto issue_tile = [&](int j, int slot) __attribute__((always_inline)) {
-    const char* const kb = khead + (size_t)j * TILEB;
-    const char* const vb = vhead + (size_t)j * TILEB;
-#pragma unroll
-    for (int it = 0; it < NLD; ++it) {
-      const uint32_t over = (uint32_t)max(0, j * BN + ld_row[it] - (N - 1)) * ROWB;  // rows past N-1 re-read row N-1
-      attn_lds_dma16(kb, ld_off[it] - over, lds_wave + slot * TILEB + it * NT * 16);
-      attn_lds_dma16(vb, ld_off[it] - over, lds_wave + C::T2BASE + slot * TILEB + it * NT * 16);
-    }
+  // load i of the next tile, iss_j, into ring slot `slot`: K and V pieces by turns
+  int iss_j = 0;
+  const char* iss_k = (const char*)p.k + ((size_t)(tc.b * p.Hkv + hk) * N) * ROWB;
+  const char* iss_v = (const char*)p.v + ((size_t)(tc.b * p.Hkv + hk) * N) * ROWB;
+  auto issue_load = [&](int slot, int i) __attribute__((always_inline)) {
+    const uint32_t off = iss_j == nt_all - 1 ? ld_off_r[i >> 1] : ld_off[i >> 1];
+    attn_lds_dma16((i & 1) ? iss_v : iss_k, off, lds_wave + ((i & 1) ? C::T2BASE : 0) + slot * TILEB + (i >> 1) * NT * 16);
   };
-  issue_tile(0, 0);
+  auto issue_advance = [&]() __attribute__((always_inline)) {
+    ++iss_j;
+    iss_k += TILEB;
+    iss_v += TILEB;
+  };
+  auto issue_next = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) issue_load(slot, i);
+    issue_advance();
+  };
+  issue_next(0);
 
-  // ---- stationary operands: Q and dO rows of this lane's query; delta from dO and O ---------------
+  // ---- stationary operands: Q and dO rows of this lane's queries; delta from dO and O ---------------
   bf16x8 qf[NKK], dof[NKK];
   float delta;
   {
@@ -188,20 +207,25 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
     delta = attn_sum_halves(acc);
   }
   const float lse2 = p.lse[(size_t)(tc.b * p.Hq + tc.hq) * N + min(qrow, N - 1)] * kLog2e;
-  // workspace for the key-side kernels, padded to whole 64-row tiles: rows past N get a
+  // workspace for the key-side kernel, padded to whole 64-row tiles: rows past N get a
   // statistic of +inf (their probabilities come out as zero) and delta = 0; delta is kept negated
   if (kg == 0 && h == 0 && qrow < p.Npad) {
     float* const wsrow = p.ws + (size_t)(tc.b * p.Hq + tc.hq) * 2 * p.Npad;
     wsrow[qrow] = qrow < N ? lse2 : INFINITY;
     wsrow[p.Npad + qrow] = qrow < N ? -delta : 0.f;
   }
-  if (nt > 1) issue_tile(1, 1);
+  if (nt > 1) issue_next(1);
+  if (nt > 2) issue_next(2);
 
-  // ---- LDS read addresses (slot 0, first 32-row block) --------------------------------------------
-  uint32_t raddr[NKK];  // row-wise operand: row qi, chunk 2kk + h
+  // ---- LDS read addresses; inside the ring every offset is a compile-time immediate, V's slots lie beyond its range ----
+  uint32_t raddr[2][NKK];
 #pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) raddr[kk] = qi * ROWB + (((2 * kk + h) ^ swz_rt<ROWB>(qi)) << 4);
-  uint32_t taddr[NCB][2];  // transposed operand through the transposing load
+  for (int kk = 0; kk < NKK; ++kk) {
+    raddr[0][kk] = kg * SUBB + qi * ROWB + (((2 * kk + h) ^ swz_rt<ROWB>(qi)) << 4);
+    raddr[1][kk] = raddr[0][kk] + C::T2BASE;
+    asm volatile("" : "+v"(raddr[1][kk]));
+  }
+  uint32_t taddr[NCB][2];
   {
     const int s = lane & 15, chalf = (lane >> 4) & 1;
 #pragma unroll
@@ -210,17 +234,20 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
       for (int e = 0; e < 2; ++e) {
         const int key = 8 * e + 4 * h + (s >> 2);
         const int chunk = cb * 4 + chalf * 2 + ((s & 3) >> 1);
-        taddr[cb][e] = key * ROWB + ((chunk ^ swz_rt<ROWB>(key)) << 4) + ((s & 1) << 3);
+        taddr[cb][e] = kg * SUBB + key * ROWB + ((chunk ^ swz_rt<ROWB>(key)) << 4) + ((s & 1) << 3);
       }
   }
-  auto row_operand = [&](int base, int kk) __attribute__((always_inline)) { return *(LDS_AS bf16x8*)(smem + raddr[kk] + base); };
-  auto tr_operand = [&](int base, int cb, int kc) __attribute__((always_inline)) {
-    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(smem + taddr[cb][0] + base + kc * 16 * ROWB));
-    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(smem + taddr[cb][1] + base + kc * 16 * ROWB));
+  // operand of score fragment i of the block at `off`: S^T = K Q^T (even i), dP^T = V dO^T (odd i)
+  auto score_operand = [&](int off, int i) __attribute__((always_inline)) { return *(LDS_AS u32x4*)(smem + raddr[i & 1][i >> 1] + off); };
+  // operand of gradient fragment i of the block at `off`: dQ^T += K^T dS^T
+  auto grad_operand = [&](int off, int i) __attribute__((always_inline)) {
+    const int cb = i % NCB, kc = i / NCB;
+    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(smem + taddr[cb][0] + off + kc * 16 * ROWB));
+    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(smem + taddr[cb][1] + off + kc * 16 * ROWB));
     s16x8 av;
     av[0] = v0[0]; av[1] = v0[1]; av[2] = v0[2]; av[3] = v0[3];
     av[4] = v1[0]; av[5] = v1[1]; av[6] = v1[2]; av[7] = v1[3];
-    return __builtin_bit_cast(bf16x8, av);
+    return __builtin_bit_cast(u32x4, av);
   };
 
   f32x16 acc[NCB];  // dQ^T
@@ -228,75 +255,166 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
   for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
-  const float c = p.scale_log2;
-  const int limit = CAUSAL ? min(qrow, N - 1) : (N - 1);
-  const int wlast = wq0 + 31;
-
-  // one 32-key block: `base` = byte offset of the block inside the K slots (V: + T2BASE)
-  auto block = [&](int key0, int base) __attribute__((always_inline)) {
-    f32x16 s, dp;
+  auto grads_settled = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(base, kk), qf[kk], s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(base + C::T2BASE, kk), dof[kk], dp, 0, 0, 0);
-    }
-    // invisible keys (causal diagonal, ragged tail): a score of -inf gives P = 0 and dS = 0.  The
-    // compare / select work sits behind a wave-uniform branch, the common case carries none of it.
-    if ((CAUSAL && key0 + 31 > wq0) || key0 + 31 >= N) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (key0 + 4 * h + 8 * (r >> 2) + (r & 3) > limit) s[r] = -INFINITY;
-    }
-    u32x4 dsk[2];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      float e[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int r = 2 * u + t;
-        const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -lse2));
-        e[t] = pr * (dp[r] - delta);
-      }
-      dsk[u >> 2][u & 3] = pack_bf16(e[0], e[1]);
-    }
-#pragma unroll
-    for (int i = 0; i < 2 * NCB; ++i) {
-      const int cb = i % NCB, kc = i / NCB;
-      acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_operand(base, cb, kc), __builtin_bit_cast(bf16x8, dsk[kc]), acc[cb], 0, 0, 0);
-    }
+    for (int cb = 0; cb < NCB; ++cb) asm volatile("s_nop 15" : "+a"(acc[cb]));
+  };
+  grads_settled();
+  // (an assembly statement for the reason, and under the conditions, given at the dK/dV kernel's)
+  auto grad_mfma = [&](int i, u32x4 o, const u32x4 (&pd)[2], auto copied) __attribute__((always_inline)) {
+    f32x16& sum = acc[i % NCB];
+    const u32x4 ds = pd[i / NCB];
+    if constexpr (decltype(copied)::value) asm volatile("s_nop 3\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(sum) : "v"(o), "v"(ds));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(sum) : "v"(o), "v"(ds));
   };
 
-  if (nt > 1) ATTN_WAIT_VMCNT(2 * NLD);
+  const float c = p.scale_log2;
+  f32x16 from;  // what dP starts from (instead of a subtraction per element)
+#pragma unroll
+  for (int r = 0; r < 16; ++r) from[r] = -delta;
+  asm volatile("" : "+v"(from));
+
+  struct Scores {
+    f32x16 s, dp;
+  };
+  struct Packed {
+    u32x4 d[2];
+  };
+  u32x4 pre[RA];  // operands of the next step's gradient products
+  constexpr int LGAP = NM / LPT;
+  // One step: scores of the block at NEXT -> out; dS of the block at CUR (scores `in`, first key key0) -> pd_out; pd_acc, the
+  // block before, multiplied into dQ.  `load`: the tile iss_j is requested into slot LSLOT (-1: none)
+  auto step = [&](Scores& in, Scores& out, Packed& pd_out, const Packed& pd_acc, auto CUR, auto NEXT, auto LSLOT, int key0, bool load) __attribute__((always_inline)) {
+    constexpr int cur = decltype(CUR)::value, next = decltype(NEXT)::value;
+    u32x4 op[NM];
+#pragma unroll
+    for (int m = 0; m < RA; ++m) op[m] = pre[m];
+    float x[16], e[16], f[16];
+    __builtin_amdgcn_sched_barrier(0);
+    auto one_slot = [&](auto slot_tag) __attribute__((always_inline)) {
+      constexpr int m = decltype(slot_tag)::value;
+      constexpr int tgt = C::read_target(m);
+      if constexpr (tgt < NM) op[tgt] = score_operand(next, tgt - RA);
+      else pre[tgt - NM] = grad_operand(cur, tgt - NM);
+      if constexpr (m < RA) {
+        grad_mfma(m, op[m], pd_acc.d, std::false_type{});
+      } else {
+        constexpr int i = m - RA;
+        f32x16& dst = (i & 1) ? out.dp : out.s;
+        if constexpr (i < 2) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dst[r] = i ? from[r] : 0.f;
+        }
+        dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op[m]), (i & 1) ? dof[i >> 1] : qf[i >> 1], dst, 0, 0, 0);
+      }
+      if constexpr (decltype(LSLOT)::value >= 0 && m % LGAP == 0 && m / LGAP < LPT) {
+        if (load) issue_load(decltype(LSLOT)::value, m / LGAP);
+      }
+      // invisible keys (causal diagonal, ragged end): a score of -inf gives P = 0 and dS = 0 (wave-uniform branch)
+      if constexpr (m == C::VP0 - 2) {
+        if ((CAUSAL && key0 + 31 > wq0) || key0 + 31 >= N) {
+          const int limit = CAUSAL ? min(qrow, N - 1) : N - 1;
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (key0 + 4 * h + 8 * (r >> 2) + (r & 3) > limit) in.s[r] = -INFINITY;
+        }
+      }
+      // vector work of row r, one link of its chain per slot: P = exp2(s c - lse2), dS = P (dP - delta), packs
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (C::vslot(r) - 1 == m) x[r] = __builtin_fmaf(in.s[r], c, -lse2);
+        if (C::vslot(r) == m) e[r] = __builtin_amdgcn_exp2f(x[r]);
+        if (C::vslot(r) + 1 == m || (m == NM - 1 && C::vslot(r) + 1 > m)) {
+          f[r] = e[r] * in.dp[r];
+          if (r & 1) pd_out.d[r >> 3][(r >> 1) & 3] = pack_bf16(f[r - 1], f[r]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for_each_slot(one_slot, std::make_integer_sequence<int, NM>{});
+    // (the packs are made here, not put off to where they are read)
+    asm volatile("" : "+v"(pd_out.d[0]), "+v"(pd_out.d[1]), "+v"(out.s), "+v"(out.dp));
+  };
+
+  if (nt > 2) ATTN_WAIT_VMCNT(2 * LPT);
+  else if (nt > 1) ATTN_WAIT_VMCNT(LPT);
   else ATTN_WAIT_VMCNT(0);
 #pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) asm volatile("" ::"v"(qf[kk]), "v"(dof[kk]));  // stationary operands are in registers
+  for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+a"(qf[kk]), "+a"(dof[kk]));  // in registers from here on
   attn_wg_barrier();
 
-  int slot = 0;
-  for (int j = 0; j < nt; ++j) {
-    const int pslot = slot == 0 ? NSLOT - 1 : slot - 1;  // slot of tile j+2 = slot of tile j-1
-    if (j + 2 < nt) issue_tile(j + 2, pslot);
+  // prologue: scores of block 0
+  Scores sa, sb;
+  Packed pa, pb;
 #pragma unroll
-    for (int i = 0; i < 2 / KS; ++i) {
-      const int kb = KS == 1 ? i : kg;
-      const int key0 = j * BN + kb * 32;
-      if (wave_valid && key0 < kv_end && (!CAUSAL || key0 <= wlast)) block(key0, slot * TILEB + kb * SUBB);
-    }
-    if (j + 2 < nt) ATTN_WAIT_VMCNT(2 * NLD);  // tile j+1 has landed; the loads of tile j+2 stay in flight
-    else ATTN_WAIT_VMCNT(0);
-    attn_wg_barrier();
-    slot = slot == NSLOT - 1 ? 0 : slot + 1;
+  for (int r = 0; r < 16; ++r) sa.s[r] = 0.f;
+  sa.dp = from;
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) {
+    sa.s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, score_operand(0, 2 * kk)), qf[kk], sa.s, 0, 0, 0);
+    sa.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, score_operand(0, 2 * kk + 1)), dof[kk], sa.dp, 0, 0, 0);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    pb.d[t] = u32x4{0u, 0u, 0u, 0u};
+    asm volatile("s_nop 1" : "+v"(pb.d[t]));  // (not to be made again in front of the first product)
+  }
+#pragma unroll
+  for (int m = 0; m < RA; ++m) {
+    pre[m] = u32x4{0u, 0u, 0u, 0u};
+    asm volatile("s_nop 1" : "+v"(pre[m]));
   }
 
-  char* const dq_row = (char*)p.dq + qoff + (size_t)min(qrow, N - 1) * ROWB;
+  // tile j lives in slot j % 4 = S
+  auto tile = [&](auto S, int j) __attribute__((always_inline)) {
+    constexpr int s = decltype(S)::value;
+    constexpr int b0 = s * TILEB, b1 = b0 + SUBB, bn = ((s + 1) & 3) * TILEB;
+    const bool load = j + 3 < nt;
+    // tile j+1 has landed (the loads of tile j+2 stay in flight); every wave is done with tile j-1
+    auto between = [&]() __attribute__((always_inline)) {
+      if (KS == 2) __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's reads of tile j-1, whose slot is refilled, are done
+      if (j + 2 < nt) ATTN_WAIT_VMCNT(LPT);
+      else ATTN_WAIT_VMCNT(0);
+      attn_wg_barrier();
+    };
+    if constexpr (KS == 2) {
+      between();
+      if constexpr (s & 1) step(sb, sa, pb, pa, ic<b0>{}, ic<bn>{}, ic<(s + 3) & 3>{}, j * BN + kg * 32, load);
+      else step(sa, sb, pa, pb, ic<b0>{}, ic<bn>{}, ic<(s + 3) & 3>{}, j * BN + kg * 32, load);
+    } else {
+      step(sa, sb, pa, pb, ic<b0>{}, ic<b1>{}, ic<-1>{}, j * BN, false);
+      between();
+      step(sb, sa, pb, pa, ic<b1>{}, ic<bn>{}, ic<(s + 3) & 3>{}, j * BN + 32, load);
+    }
+    if (load) issue_advance();
+  };
+  int j = 0;
+  for (; j + 4 <= nt; j += 4) {
+    tile(ic<0>{}, j);
+    tile(ic<1>{}, j + 1);
+    tile(ic<2>{}, j + 2);
+    tile(ic<3>{}, j + 3);
+  }
+  if (j < nt) {
+    tile(ic<0>{}, j);
+    if (j + 1 < nt) {
+      tile(ic<1>{}, j + 1);
+      if (j + 2 < nt) tile(ic<2>{}, j + 2);
+    }
+  }
+  // the gradient products of the last block (its operands are already here)
+  if (KS == 2 && ((nt - 1) & 1) == 0) pb = pa;  // (the parity of the last step says which registers hold dS)
+#pragma unroll
+  for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], pb.d, std::true_type{});
+  grads_settled();
+
   if constexpr (KS == 1) {
-    store_transposed<NCB>(acc, p.scale, dq_row, h, qrow < N);
+    store_transposed<NCB>(acc, p.scale, (char*)p.dq + qoff + (size_t)min(qrow, N - 1) * ROWB, h, qrow < N);
   } else {
-    // every wave is past the loop's last barrier, so the ring is free: the two waves of a query block
-    // exchange halves of their partial dQ (each gives away the columns the other one finishes)
+    // the two waves of a query block exchange halves of their partial dQ (each gives away the columns the other one
+    // finishes)
     constexpr int NH = NCB / 2;
+    __syncthreads();  // no wave reads the ring any more
     LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((kg ^ 1) * NQW + w % NQW) * (NH * 4) * 64 + lane;
     LDS_AS const f32x4* const take = (LDS_AS const f32x4*)smem + (kg * NQW + w % NQW) * (NH * 4) * 64 + lane;
     f32x16 mine[NH];
@@ -316,7 +434,7 @@ __global__ void __launch_bounds__(512, 2) attn_bwd_dq_kernel(const AttnBwdParams
 #pragma unroll
         for (int r = 0; r < 4; ++r) mine[cb][4 * a + r] += o[r];
       }
-    store_transposed<NH>(mine, p.scale, dq_row + kg * NH * 64, h, qrow < N);
+    store_transposed<NH>(mine, p.scale, (char*)p.dq + qoff + (size_t)min(qrow, N - 1) * ROWB + kg * NH * 64, h, qrow < N);
   }
 }
 
@@ -779,12 +897,14 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
 
 }  // namespace
 
-// Both kernels split where the launch has few tiles.  Whole backward passes in which only that
-// kernel changes, us, unsplit -> split, d = 128 (d = 64 behaves alike), heads x N:
-//   dQ     non-causal 16 x 2048 140 -> 119; 41 x 2048 356 -> 339; 22 x 4096 663 -> 627; 24 x 2048 200 -> 218; 64 x 1000 125 -> 136; 80 x 2048 584 -> 586
-//          causal     32 x 2048 155 -> 139; 48 x 1000 84 -> 78; 64 x 300 36 -> 33; 64 x 513 52 -> 53; 85 x 513 65 -> 68
-//   dK/dV  non-causal 12 x 1000 75 -> 67; 38 x 1000 113 -> 110; 16 x 2048 140 -> 151; 64 x 1000 125 -> 141
-//          causal     24 x 1000 76 -> 70; 16 x 2048 135 -> 123; 43 x 513 51 -> 52; 38 x 1000 80 -> 96
+// Both kernels split where the launch has few tiles; d = 64 dK/dV nearly always.  Whole backward passes in which only that
+// kernel changes, us, unsplit -> split, heads x N (both forms of 1380 random shapes were timed, N 60 .. 6000, up to 1600 tiles; the
+// choice is 0.1 % (d = 128) to 0.6 % (d = 64) slower than the faster form on average, and at worst 3 % and 8 %):
+//   dQ     d = 128  2 x 656 causal 41 -> 38; 20 x 3220 405 -> 381; 128 x 369 causal 52 -> 57; 64 x 2048 causal 260 -> 297
+//          d = 64   8 x 2919 causal 68 -> 59; 32 x 1000 40 -> 43; 64 x 8192 3532 -> 3669
+//   dK/dV  d = 128  12 x 1000 75 -> 67; 16 x 2048 140 -> 151; 64 x 2048 causal 260 -> 292; 256/32 x 4096 causal 3491 -> 3687
+//          d = 64   64 x 8192 3532 -> 3446, causal 1911 -> 1833; 256/32 x 4096 causal 1924 -> 1852; 96/12 x 413 causal 93 -> 76;
+//                   64 x 597 causal 31 -> 35
 int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
   auto launch = [&](auto dtag, auto causal_tag) {
     constexpr int D = decltype(dtag)::value;
@@ -792,14 +912,23 @@ int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
     const double blocks = (p.N + 31) / 32;  // 32-row blocks of a head
     AttnBwdParams q = p;
     auto tiles = [&](int heads, int rows) { return (long long)p.B * heads * ((p.N + rows - 1) / rows); };
-    const AttnSplitCost cost_q = CAUSAL ? AttnSplitCost{6.2, 8.4, 1.02, 0.6, 6.0} : AttnSplitCost{14.8, 16.0, 0.89, 0.68, 6.0};
-    const bool split_q = attn_split_pays(CAUSAL, tiles(p.Hq, 256), tiles(p.Hq, 128), (p.N + 127) / 128, blocks, cost_q);
-    q.T = split_q ? (p.N + 127) / 128 : (p.N + 255) / 256;
+    const AttnSplitCost cost_q = D == 128 ? (CAUSAL ? AttnSplitCost{13.2, 14.5, 1.14, 0.46, 2.8} : AttnSplitCost{20.3, 18.6, 1.12, 0.63, 4.4})
+                                          : (CAUSAL ? AttnSplitCost{6.5, 6.1, 0.3, 0.74, 2.7} : AttnSplitCost{6.9, 7.7, 1.03, 0.45, 4.5});
+    const bool split_q = attn_split_pays(CAUSAL, tiles(p.Hq, 128), tiles(p.Hq, 64), (p.N + 63) / 64, blocks, cost_q);
+    q.T = split_q ? (p.N + 63) / 64 : (p.N + 127) / 128;
     const dim3 grid_q(p.B * p.Hq * q.T);
-    if (split_q) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 2>), grid_q, dim3(512), 0, stream, q);
-    else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 1>), grid_q, dim3(512), 0, stream, q);
-    const AttnSplitCost cost_k = CAUSAL ? AttnSplitCost{6.5, 7.5, 0.88, 0.51, 4.0} : AttnSplitCost{10.3, 8.7, 1.09, 0.82, 4.0};
-    const bool split_k = attn_split_pays(CAUSAL, tiles(p.Hkv, 128), tiles(p.Hkv, 64), (p.N + 63) / 64, blocks * (p.Hq / p.Hkv), cost_k);
+    if (split_q) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 2>), grid_q, dim3(256), 0, stream, q);
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 1>), grid_q, dim3(256), 0, stream, q);
+    const double steps_k = blocks * (p.Hq / p.Hkv);
+    const long long whole_k = tiles(p.Hkv, 128);
+    bool split_k;
+    if constexpr (D == 128) {
+      const AttnSplitCost cost_k = CAUSAL ? AttnSplitCost{6.5, 7.5, 0.88, 0.51, 4.0} : AttnSplitCost{10.3, 8.7, 1.09, 0.82, 4.0};
+      split_k = attn_split_pays(CAUSAL, whole_k, tiles(p.Hkv, 64), (p.N + 63) / 64, steps_k, cost_k);
+    } else {
+      // (two of the split form's workgroups fit a CU, one of the whole form's: only where those fill the CUs once is it ahead)
+      split_k = whole_k <= 65536 && steps_k >= (CAUSAL ? 3 : 5) && !(whole_k > 224 && whole_k <= (CAUSAL ? 448 : 288));
+    }
     const dim3 grid_k(p.B * p.Hkv * (split_k ? (p.N + 63) / 64 : (p.N + 127) / 128));
     if (split_k) hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 2>), grid_k, dim3(256), 0, stream, q);
     else hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 1>), grid_k, dim3(256), 0, stream, q);

@@ -76,7 +76,7 @@ struct AttnBwdParams {
   void* dv;
   float* ws;         // [B, Hq, 2, Npad] floats: lse * log2(e) and -delta, rows padded to whole 64-row tiles
   int B, Hq, Hkv, N;
-  int T = 0;         // query tiles per head of the dQ kernel, set by the launch (256 rows each, 128 when it splits the keys)
+  int T = 0;         // query tiles per head of the dQ kernel, set by the launch (128 rows each, 64 when it splits the keys)
   int Npad;          // ceil(N / 64) * 64
   int causal;
   float scale_log2;  // scale * log2(e)

@@ -30,9 +30,14 @@ for _d in (64, 128):
         _fwd(_d, False, 1, 1, op="persistent", H=520, Hkv=260, N=300), _fwd(_d, True, 1, 1, op="persistent", H=520, Hkv=260, N=300),
         _fwd(_d, False, 0, 2, op="persistent", H=5, N=300), _fwd(_d, True, 0, 2, op="persistent", H=5, N=300),
         _bwd(_d, False, 2, 2, H=6, Hkv=3, N=517), _bwd(_d, True, 2, 2, H=6, Hkv=2, N=517),
-        _bwd(_d, False, 1, 1, H=70, N=513), _bwd(_d, False, 1, 1, H=70, Hkv=35, N=513), _bwd(_d, False, 1, 2, H=140, Hkv=20, N=513), _bwd(_d, True, 1, 1, H=90, N=513),
-        _bwd(_d, True, 1, 1, H=180, Hkv=90, N=300), _bwd(_d, True, 1, 2, H=90, Hkv=45, N=513),
+        _bwd(_d, False, 1, 2, H=140, Hkv=20, N=513), _bwd(_d, True, 1, 1, H=180, Hkv=90, N=300),
     ]
+# backward, the dK/dV launches whose form depends on the head dimension
+ATTENTION += [
+    _bwd(128, False, 1, 1, H=70, N=513), _bwd(128, False, 1, 1, H=70, Hkv=35, N=513), _bwd(128, True, 1, 1, H=90, N=513), _bwd(128, True, 1, 2, H=90, Hkv=45, N=513),
+    _bwd(64, False, 1, 2, H=70, N=513), _bwd(64, False, 1, 2, H=70, Hkv=35, N=513), _bwd(64, True, 1, 2, H=90, N=513), _bwd(64, True, 1, 1, H=90, Hkv=45, N=513),
+    _bwd(64, False, 1, 1, H=46, N=513),
+]
 ATTENTION += [
     _fwd(128, False, 0, 1, op="fp8", H=4, Hkv=2, N=517), _fwd(128, True, 0, 1, op="fp8", H=4, Hkv=2, N=517),
     _fwd(128, True, 2, 1, op="fp8", H=800, Hkv=400, N=201),
