@@ -42,10 +42,14 @@ const GemmTile* cheapest(const GemmTile* best, double* cost, const GemmTile* tab
 
 // the variant tables, concatenated
 const GemmVariant* variant_at(int i) {
-  int n1 = 0, n2 = 0;
-  const GemmVariant* const t1 = gemm_bf16_nt_variants(&n1);
-  const GemmVariant* const t2 = gemm_wavek_nt_variants(&n2);
-  return i < 0 ? nullptr : i < n1 ? &t1[i] : i < n1 + n2 ? &t2[i - n1] : nullptr;
+  if (i < 0) return nullptr;
+  for (auto list : {gemm_bf16_nt_variants, gemm_wavek_nt_variants, gemm_bf16_nt_ahead_variants}) {
+    int n = 0;
+    const GemmVariant* const t = list(&n);
+    if (i < n) return &t[i];
+    i -= n;
+  }
+  return nullptr;
 }
 
 double gemm_bytes(int M, int N, int K) { return 2.0 * ((double)M * K + (double)N * K + (double)M * N); }
@@ -134,7 +138,7 @@ int run_splitk(const void* a, const void* b, void* c, int M, int N, int K, int s
   // second launch (3 us), over 1, 2, 3, 4, 6, 9, ... slices and `splits` itself.  Measured, always 256 x 256
   // tiles and `splits` slices -> this: 234 x 74 x 21504 67 -> 8.1 us, 896 x 761 x 12288 72 -> 35, 84 x 3775 x 40000
   // 110 -> 79, 64 x 64 x 65536 57 -> 10; where the large tile stays, its XCD map (gemm_map.h) and the 16x16x32 kernel:
-  // 2304 x 1024 x 65536 357 -> 335 -> 287 us with the sum kernel (12 us of it).
+  // 2304 x 1024 x 65536 357 -> 335 -> 287 us with the sum kernel (12 us of it), 258 with operands fetched ahead.
   const int steps = K / 64;
   auto slice = [&](int s) { return ((steps + s - 1) / s) * 64; };  // whole 64-column steps, none empty
   const GemmTile large = {256, 256, 64, 1, 5.9f, 0.985f, 5.5f, gemm_bf16_nt_splitk_launch, 64};
@@ -207,10 +211,9 @@ int gemm_bf16_nt_variant(const void* a, const void* b, void* c, int M, int N, in
 }
 
 int gemm_num_variants(void) {
-  int n1 = 0, n2 = 0;
-  gemm_bf16_nt_variants(&n1);
-  gemm_wavek_nt_variants(&n2);
-  return n1 + n2;
+  int n = 0;
+  while (variant_at(n)) ++n;
+  return n;
 }
 
 const char* gemm_variant_name(int variant) {

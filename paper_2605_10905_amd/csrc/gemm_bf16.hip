@@ -371,7 +371,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // SPLITK: the grid holds p.splits workgroups per tile; workgroup (split, tile) contracts its slice
 // of k and stores the fp32 accumulators to p.partial instead of rounding them into c.
-template <int BK, int NSTAGE, bool SPLITK>
+// AHEAD: operands are fetched into the L2 a few stages before they are requested.
+template <int BK, int NSTAGE, bool SPLITK, bool AHEAD>
 __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmParams p) {
   using C = GemmCfg<4, 4, BK, NSTAGE>;
   constexpr int ROWB = C::ROWB, NCH = C::NCH, TILEA = C::TILEA, STAGEB = C::STAGEB;
@@ -420,6 +421,23 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
 #pragma unroll
       for (int it = 0; it < LPS; ++it) issue_load(s, s, it);
     }
+
+  // Two slots request an operand one stage, about 1 us, before it is used: enough for what another workgroup has brought
+  // into the XCD's L2, not for what comes from memory.  So the workgroups that share a panel fetch it into the L2 four stages
+  // ahead between them: per stage one load of one line per lane and wave (waves 0, 1 half of the A panel's rows, waves 2, 3 of
+  // B's, which half by the tile's place; written into LDS that the ring leaves over and never read).  It goes out
+  // behind the stage's own loads, so that a wait for those leaves it in flight.  Split-K always; otherwise by
+  // launch_m16_by_size.  Measured, without -> with, buffers changing from call to call: split-K 2304 x 1024 x 65536
+  // 298 -> 258 us, x 65600 262 -> 244, 3000 x 1000 x 20480 122 -> 116.
+  constexpr int DIST = 4;
+  static_assert(!AHEAD || (NSTAGE == 2 && C::LDS_BYTES >= NSTAGE * STAGEB + 4096), "room for what is fetched ahead");
+  const char* const pf_tile = w < 2 ? a_tile : b_tile;
+  const int pf_row = (((w < 2 ? tc.tn : tc.tm) * 2 + w) & 3) * 64, pf_last = w < 2 ? M - 1 - m0 : N - 1 - n0;
+  auto fetch_ahead = [&](int ks) __attribute__((always_inline)) {
+    int r = lane;
+    asm volatile("" : "+v"(r));  // (the offset is made here each time: no register is left to keep it in)
+    attn_lds_dma16(pf_tile + (size_t)min(ks + DIST, nk - 1) * ROWB, (uint32_t)min(pf_row + r, pf_last) * (uint32_t)rowbytes, lds_wave + NSTAGE * STAGEB);
+  };
 
   // fragment addresses: row block 0 of this wave's quarter, k-step ph
   uint32_t ra[NPH], rb[NPH];
@@ -476,7 +494,8 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
       for (int row = 0; row < 8; ++row) {
         if (last && row == 1 && more) {
           __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of the slot about to be refilled are done
-          if (STEADY || ks + NSTAGE - 1 < nk) ATTN_WAIT_VMCNT((NSTAGE - 2) * LPS);
+          if (AHEAD) ATTN_WAIT_VMCNT(1);
+          else if (STEADY || ks + NSTAGE - 1 < nk) ATTN_WAIT_VMCNT((NSTAGE - 2) * LPS);
           else ATTN_WAIT_VMCNT(0);
           attn_wg_barrier();
         }
@@ -499,6 +518,7 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
             const int it = q * DPR + (mb == 7 ? 1 : 0);
             if (it < LPS) issue_load(dks, behind ? slot : pslot, it);
           }
+          if (AHEAD && ph == 0 && row == 2 && mb == 5) fetch_ahead(ks);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -524,6 +544,7 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
   if (nk > 0) step(std::false_type{});
   while (ks + PER_STEP - 1 + NSTAGE < nk) step(std::true_type{});
   while (ks < nk) step(std::false_type{});
+  if (AHEAD) ATTN_WAIT_VMCNT(0);
 
   // ---- epilogue: lane (lj, g) holds, for row m, the columns n = 16 nb + 4 g + (0..3); a pair of
   // neighbouring n blocks is exchanged between odd and even lane groups so that every lane owns 8
@@ -575,10 +596,18 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
   gemm_store_staged<C::BM, C::BN>(smem, p, m0, n0, tid);
 }
 
-template <int BK, int NSTAGE>
+template <int BK, int NSTAGE, bool AHEAD = false>
 int launch_m16(const GemmParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<BK, NSTAGE, false>), dim3(p.tiles_m * p.tiles_n), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<BK, NSTAGE, false, AHEAD>), dim3(p.tiles_m * p.tiles_n), dim3(256), 0, stream, p);
   return (int)hipGetLastError();
+}
+
+// Fetching ahead (see the kernel) pays where K is long and every panel has several tiles to share it; us, without -> with:
+// 4000 x 4000 x 9984 237 -> 231, 4096 x 4096 x 16384 413 -> 399, 8192 x 8192 x 16384 1634 -> 1610, 4096 x 4096 x 65536 1882 -> 1582,
+// 1000 x 15000 x 16384 405 -> 392; 512 x 30000 x 16384 (two tile rows) 403 -> 421, 8192 x 8192 x 4096 370 -> 385,
+// 3000 x 30000 x 2752 393 -> 400.  (One kernel with a branch instead: 0.5 % slower on the launches that do not fetch ahead.)
+int launch_m16_by_size(const GemmParams& p, hipStream_t stream) {
+  return p.K >= 8192 && p.tiles_m >= 4 && p.tiles_n >= 4 ? launch_m16<64, 2, true>(p, stream) : launch_m16<64, 2>(p, stream);
 }
 
 // c[i] = bf16(sum over splits of partial[s][i]), splits added in index order.  VEC: four consecutive
@@ -625,7 +654,7 @@ int launch(const GemmParams& p, hipStream_t stream) {
 }  // namespace
 
 int gemm_bf16_nt_splitk_launch(const GemmParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true>), dim3(p.tiles_m * p.tiles_n * p.splits), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true, true>), dim3(p.tiles_m * p.tiles_n * p.splits), dim3(256), 0, stream, p);
   return (int)hipGetLastError();
 }
 
@@ -660,10 +689,16 @@ const GemmVariant* gemm_bf16_nt_variants(int* count) {
   return table;
 }
 
+const GemmVariant* gemm_bf16_nt_ahead_variants(int* count) {
+  static const GemmVariant table[] = {{"bf16 nt 256x256x64 ring2 mfma16x16x32 fetched ahead", 256, 256, 64, 64, launch_m16<64, 2, true>}};
+  *count = 1;
+  return table;
+}
+
 // The rates (GemmTile) are a fit to about 70 shapes per layout, M 1 .. 590000, N 32 .. 65536, K 64 .. 16384.
 const GemmTile* gemm_bf16_nt_tiles(int* count) {
   static const GemmTile table[] = {
-      {256, 256, 64, 1, 5.9f, 0.985f, 5.5f, launch_m16<64, 2>, 64},
+      {256, 256, 64, 1, 5.9f, 0.985f, 5.5f, launch_m16_by_size, 64},
       {256, 256, 32, 1, 6.1f, 0.58f, 5.5f, launch<4, 4, 32, 4, 1>},
       {256, 128, 64, 1, 4.4f, 0.62f, 5.5f, launch<4, 2, 64, 3, 1>},
       {128, 256, 64, 1, 4.1f, 0.65f, 5.5f, launch<2, 4, 64, 3, 1>},

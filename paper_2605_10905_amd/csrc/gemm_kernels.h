@@ -26,6 +26,7 @@ struct GemmVariant {
 // what gemm_bf16_nt_variant offers: every kernel that gemm_bf16_nt chooses from, and a few that it does not
 const GemmVariant* gemm_bf16_nt_variants(int* count);
 const GemmVariant* gemm_wavek_nt_variants(int* count);
+const GemmVariant* gemm_bf16_nt_ahead_variants(int* count);  // (last, so that the others keep their numbers)
 // A tile of the library's own choice (gemm_api.hip): one workgroup of it takes about
 // fixed_us + ceil(K / step) * step_us, `per_cu` of them share a CU.
 struct GemmTile {
