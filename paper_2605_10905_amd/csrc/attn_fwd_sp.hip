@@ -17,10 +17,8 @@
 //     * exponentiates block u            (VALU:  P(u)   = exp2(c S(u) - m))
 //     * computes the scores of block u+1 (MFMA:  S(u+1) = K(u+1) Q^T)
 //     * accumulates block u-1            (MFMA:  O^T   += V(u-1)^T P(u-1)^T)
-// The three streams are independent inside a step; a scheduling-group pipeline at the end of
-// each scheduling region tells the compiler's scheduler the interleave: per MFMA its share of the
-// exponentials and of the plain vector instructions, and the LDS reads of the operand a few
-// MFMAs ahead.
+// The three streams are independent inside a step, which is laid out by hand in fenced slots of one MFMA each, with its
+// share of the vector work and the LDS reads of the operand a few MFMAs ahead.
 //
 // K/V streaming (the producer role).  Block u+1 of K and block u-1 of V travel together:
 // "bundle" b holds key tile b+1 and value tile b (64 keys each) and is consumed by exactly one
@@ -48,6 +46,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "attn_device.h"
 #include "attn_kernels.h"
@@ -76,21 +75,9 @@ constexpr float kNoRef = -3.4028234663852886e38f;
 template <int V>
 using ic = std::integral_constant<int, V>;
 
-// Scheduling-group pipeline of the MFMAs [M, M1) of a step (the builtin wants literal constants,
-// hence the recursion).  The region [M0, M1) holds NVALU plain vector instructions and NEXP
-// exponentials, spread evenly over its MFMAs; behind each MFMA come the LDS reads of the operand
-// RA MFMAs ahead: QKR reads for a K fragment, two transposing reads for a V fragment.  MFMA m of a
-// step is a score product iff m % STRIDE == 0.
-template <int M, int M1, int NM, int RA, int NVALU, int NEXP, int STRIDE, int QKR, int M0 = M>
-__device__ __forceinline__ void step_pipeline() {
-  if constexpr (M < M1) {
-    constexpr int NS = M1 - M0, J = M - M0;
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                        // MFMA
-    __builtin_amdgcn_sched_group_barrier(0x002, (NVALU * (J + 1)) / NS - (NVALU * J) / NS, 0);  // VALU
-    __builtin_amdgcn_sched_group_barrier(0x400, (NEXP * (J + 1)) / NS - (NEXP * J) / NS, 0);    // transcendental
-    __builtin_amdgcn_sched_group_barrier(0x100, ((M + RA) % NM) % STRIDE == 0 ? QKR : 2, 0);    // LDS read
-    step_pipeline<M + 1, M1, NM, RA, NVALU, NEXP, STRIDE, QKR, M0>();
-  }
+template <class F, int... M>
+__device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M...>) {
+  (f(ic<M>{}), ...);
 }
 
 // MODE says where a workgroup's query tiles come from.
@@ -487,11 +474,10 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   // next step reads).  The vector work needs no block maximum: exponentials are taken against
   // the current reference and the block is redone, after raising the reference and rescaling,
   // only if a lane's partial sum comes out large or not a number (always on the very first
-  // block).  Source order inside a scheduling region does not matter: the scheduling-group
-  // pipeline at its end tells the scheduler how to interleave the four instruction classes.
-  // NSEG > 1 cuts the step into NSEG regions of NM / NSEG MFMAs (each with its share of the
-  // exponentials, sums and packs); between(i) runs in front of region i, which is where the
-  // producer role's work goes.
+  // block).  A row's multiply-add, exponential, and sum and pack lie in three consecutive slots, so that none waits for the
+  // one before it.  (A scheduling-group pipeline that left the order to the compiler had all three in one slot: 2 x 32 x 8192 1753 -> 1750 us,
+  // causal 910 -> 905, d = 64 1095 -> 1079, 4 x 16/8 x 2693, d = 64 135.0 -> 133.1, 4 x 16 x 2048 causal 71.2 -> 70.8.)
+  // NSEG: between(i) runs in front of slot i * NM / NSEG, which is where the producer role's work goes.
   Operand pre[RA];
   auto koff_of = [](auto bid) __attribute__((always_inline)) { return ic<(decltype(bid)::value >> 1) * KTILEB + (decltype(bid)::value & 1) * KSUBB>{}; };
   auto voff_of = [](auto bid) __attribute__((always_inline)) { return ic<(decltype(bid)::value >> 1) * TILEB + (decltype(bid)::value & 1) * SUBB>{}; };
@@ -501,50 +487,50 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   };
   auto step_hot = [&](f32x16& s_in, f32x16& s_out, u32x4 (&p_out)[2], u32x4 (&p_pv)[2], auto bid, auto bidnext, auto nseg_tag, auto between) __attribute__((always_inline)) {
     constexpr int NSEG = decltype(nseg_tag)::value, SEG = NM / NSEG;
-    static_assert(NSEG <= 4 && NM % NSEG == 0 && (16 / NSEG) % 2 == 0 && 16 % NSEG == 0, "regions hold whole MFMAs and whole pairs of scores");
+    static_assert(NSEG <= 4 && NM % NSEG == 0, "whole regions");
     Operand op[NM];
 #pragma unroll
     for (int m = 0; m < RA; ++m) op[m] = pre[m];
 #pragma unroll
     for (int r = 0; r < 16; ++r) s_out[r] = 0.f;
     float ls0 = 0.f, ls1 = 0.f;
-    float e[16];
-    auto segment = [&](auto seg_tag) __attribute__((always_inline)) {
-      constexpr int SG = decltype(seg_tag)::value, M0 = SG * SEG, M1 = M0 + SEG;
-      constexpr int R0 = 16 * SG / NSEG, R1 = 16 * (SG + 1) / NSEG;  // scores exponentiated in this region
-      between(SG);
-      if constexpr (SG > 0) __builtin_amdgcn_sched_barrier(0);
+    float x[16], e[16];
+    // the slot of row r's exponential; its multiply-add comes a slot earlier, its sum and pack a slot later
+    auto eslot = [](int r) constexpr { return 1 + r * (NM - 1) / 16; };
+    auto one_slot = [&](auto slot_tag) __attribute__((always_inline)) {
+      constexpr int m = decltype(slot_tag)::value;
+      if constexpr (m % SEG == 0) {
+        between(m / SEG);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (m % STRIDE == 0) {
+        s_out = qk_mfma(op[m], m / STRIDE, s_out);
+      } else {
+        constexpr int i = m - m / STRIDE - 1;
+        oacc[i % NCB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op[m].x), __builtin_bit_cast(bf16x8, p_pv[i / NCB]),
+                                                                oacc[i % NCB], 0, 0, 0);
+      }
 #pragma unroll
-      for (int m = M0; m < M1; ++m) {
-        if (m % STRIDE == 0) {
-          s_out = qk_mfma(op[m], m / STRIDE, s_out);
-        } else {
-          const int i = m - m / STRIDE - 1;
-          oacc[i % NCB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, op[m].x), __builtin_bit_cast(bf16x8, p_pv[i / NCB]),
-                                                                  oacc[i % NCB], 0, 0, 0);
+      for (int r = 0; r < 16; ++r) {
+        if (eslot(r) - 1 == m) x[r] = __builtin_fmaf(s_in[r], c, -m_ref);
+        if (eslot(r) == m) e[r] = __builtin_amdgcn_exp2f(x[r]);
+        if (eslot(r) + 1 == m || (m == NM - 1 && eslot(r) == m)) {
+          if (r & 1) {
+            p_out[r >> 3][(r >> 1) & 3] = attn_pack_bf16(e[r - 1], e[r]);
+            ls1 = r == 1 ? e[r] : ls1 + e[r];
+          } else {
+            ls0 = r == 0 ? e[r] : ls0 + e[r];
+          }
         }
-        if (m + RA < NM) op[m + RA] = step_operand(bid, m + RA);
-        else pre[m + RA - NM] = step_operand(bidnext, m + RA - NM);
       }
-#pragma unroll
-      for (int r = R0; r < R1; ++r) e[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s_in[r], c, -m_ref));
-#pragma unroll
-      for (int u = R0 / 2; u < R1 / 2; ++u) {
-        p_out[u >> 2][u & 3] = attn_pack_bf16(e[2 * u], e[2 * u + 1]);
-        ls0 = u == 0 ? e[0] : ls0 + e[2 * u];
-        ls1 = u == 0 ? e[1] : ls1 + e[2 * u + 1];
-      }
-      if constexpr (SG == NSEG - 1) ls0 += ls1;
-      // multiply-adds, packs and adds of this region (the first pair starts the two sums, the
-      // last region adds them and compares)
-      constexpr int NVALU = (R1 - R0) + 3 * ((R1 - R0) / 2) - (SG == 0 ? 2 : 0) + (SG == NSEG - 1 ? 2 : 0);
-      step_pipeline<M0, M1, NM, RA, NVALU, R1 - R0, STRIDE, QKR>();
-      if constexpr (SG + 1 < NSEG) __builtin_amdgcn_sched_barrier(0);
+      if constexpr (m + RA < NM) op[m + RA] = step_operand(bid, m + RA);
+      else pre[m + RA - NM] = step_operand(bidnext, m + RA - NM);
+      __builtin_amdgcn_sched_barrier(0);
     };
-    segment(ic<0>{});
-    if constexpr (NSEG > 1) segment(ic<1>{});
-    if constexpr (NSEG > 2) segment(ic<2>{});
-    if constexpr (NSEG > 3) segment(ic<3>{});
+    __builtin_amdgcn_sched_barrier(0);
+    for_each_slot(one_slot, std::make_integer_sequence<int, NM>{});
+    ls0 += ls1;
+    asm volatile("" ::"v"(p_out[0]), "v"(p_out[1]));
     float ls = ls0;
     if (__builtin_amdgcn_ballot_w64(!(ls <= kSumLimit)) != 0) {
       // the redo path "reads" the optimistic packs, so that they are computed inside the
