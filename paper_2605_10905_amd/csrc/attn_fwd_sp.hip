@@ -929,11 +929,10 @@ int resident_workgroups() {
   return cus - cus % 8;
 }
 
-// Causal launches with at least three tiles per CU walk static tile lists (mode 2): the seams
+// Launches with at least three tiles per CU walk static tile lists (mode 2): the seams
 // between a workgroup's tiles hide part of what a workgroup pays per tile outside its main loop
-// (measured: +0.5 .. +4.5 %; with two tiles per CU the plain launch is 1 % faster).  Non-causal
-// launches run one tile per workgroup: in the list-walking instantiation the compiler's greedy
-// scheduling-group solver interleaves the pipelined step less well (5 % more cycles).
+// (measured: causal +0.5 .. +4.5 %; with two tiles per CU the plain launch is 1 % faster; non-causal, 81 launches of three tiles per CU
+// and more, d = 64 and 128: 0.92 - 0.95 of the plain launch's time on average, at worst 1.04).
 // bf16 launches of few tiles (`tiles` of 256 queries) split the keys (KS = 2); the plain and the queue
 // launch follow the same rule, so that both give the same bytes.  us, whole tiles -> split keys, d = 128, heads x N:
 //   non-causal  32 x 1000 25.8 -> 20.3; 16 x 2048 42.0 -> 34.2; 34 x 2048 100.4 -> 92.0; 22 x 4096 186.1 -> 172.7;
@@ -960,11 +959,12 @@ int launch_split(const AttnParams& p, int, hipStream_t stream) {
 
 template <int D, bool FP8>
 int launch_whole(const AttnParams& p, int grid, hipStream_t stream) {
-  const int resident = p.causal ? resident_workgroups() : 0;
-  if (p.causal && resident >= 8 && grid >= 3 * resident) {
+  const int resident = resident_workgroups();
+  if (resident >= 8 && grid >= 3 * resident) {
     AttnParams q = p;
     q.total = grid;
-    hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 2, FP8>), dim3(resident), dim3(512), 0, stream, q);
+    if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 2, FP8>), dim3(resident), dim3(512), 0, stream, q);
+    else hipLaunchKernelGGL((attn_fwd_sp_kernel<D, false, 2, FP8>), dim3(resident), dim3(512), 0, stream, q);
   } else if (p.causal) {
     hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 0, FP8>), dim3(grid), dim3(512), 0, stream, p);
   } else {

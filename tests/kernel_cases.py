@@ -21,11 +21,11 @@ def _bwd(d, causal, q, k, **size):
 ATTENTION = []
 for _d in (64, 128):
     ATTENTION += [
-        # few tiles: two waves share 32 queries; many: one tile a workgroup; causal and three or more tiles per
+        # few tiles: two waves share 32 queries; many: one tile a workgroup; three or more tiles per
         # CU: one workgroup per CU walks a list of them
         _fwd(_d, False, 0, 2, H=6, Hkv=3, N=517), _fwd(_d, True, 0, 2, H=6, Hkv=2, N=517),
         _fwd(_d, False, 0, 1, H=70, Hkv=35, N=513), _fwd(_d, True, 0, 1, H=90, Hkv=45, N=513),
-        _fwd(_d, True, 2, 1, H=800, Hkv=400, N=201), _fwd(_d, True, 2, 1, B=3, H=130, Hkv=65, N=430),
+        _fwd(_d, False, 2, 1, H=800, Hkv=400, N=201), _fwd(_d, True, 2, 1, H=800, Hkv=400, N=201), _fwd(_d, True, 2, 1, B=3, H=130, Hkv=65, N=430),
         # the queue: four tiles and more for each resident workgroup
         _fwd(_d, False, 1, 1, op="persistent", H=520, Hkv=260, N=300), _fwd(_d, True, 1, 1, op="persistent", H=520, Hkv=260, N=300),
         _fwd(_d, False, 0, 2, op="persistent", H=5, N=300), _fwd(_d, True, 0, 2, op="persistent", H=5, N=300),
@@ -40,7 +40,7 @@ ATTENTION += [
 ]
 ATTENTION += [
     _fwd(128, False, 0, 1, op="fp8", H=4, Hkv=2, N=517), _fwd(128, True, 0, 1, op="fp8", H=4, Hkv=2, N=517),
-    _fwd(128, True, 2, 1, op="fp8", H=800, Hkv=400, N=201),
+    _fwd(128, True, 2, 1, op="fp8", H=800, Hkv=400, N=201), _fwd(128, False, 2, 1, op="fp8", H=800, Hkv=400, N=201),
     (["attn_fwd_fp8_kernel<128, false>"], dict(op="fp8_variant", variant=3, H=4, Hkv=2, N=517, d=128, causal=False)),
     (["attn_fwd_fp8_kernel<128, true>"], dict(op="fp8_variant", variant=3, H=4, Hkv=2, N=517, d=128, causal=True)),
 ]
