@@ -75,6 +75,8 @@ constexpr float kNoRef = -3.4028234663852886e38f;
 template <int V>
 using ic = std::integral_constant<int, V>;
 
+enum { kWhole = 1, kSplit = 2, kPair = 3 };  // FORM of attn_fwd_sp_kernel
+
 template <class F, int... M>
 __device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M...>) {
   (f(ic<M>{}), ...);
@@ -107,11 +109,16 @@ __device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M.
 // the step, and the ring has four slots so that a bundle is requested three steps ahead.  Q travels
 // through LDS as well: with no load the compiler knows of, the waits are exact, and the first scores
 // need only Q and key tiles 0 and 1 to have arrived, not bundles 0 and 1 requested behind them.
-template <int D, bool CAUSAL, int MODE, bool FP8, int KS = 1>
-__global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p) {
+// FORM = kPair (bf16, MODE 0): four waves own 128 queries, key tiles of 32 and otherwise the one-step iterations of the split
+// form.  The ring is 64 KB (d = 64: 32), so two (three) such workgroups share a CU, and one's first loads, first
+// block, diagonal and stores run beside the other's steps; its bytes are those of the whole form.  By itself a step
+// takes it 0.56 us (d = 128), beside another one 0.78.
+template <int D, bool CAUSAL, int MODE, bool FP8, int FORM = kWhole>
+__global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kernel(const AttnParams p) {
   static_assert(!FP8 || (D == 128 && MODE != 1), "fp8 inputs: head dimension 128, no queue launch");
-  static_assert(KS == 1 || (KS == 2 && MODE == 0 && !FP8), "split keys: bf16, one tile per workgroup");
-  constexpr int BN = 64, NWAVES = 8, NQW = NWAVES / KS, BM = NQW * 32, NT = NWAVES * 64;
+  static_assert(FORM == kWhole || (MODE == 0 && !FP8), "split keys and paired workgroups: bf16, one tile per workgroup");
+  constexpr int KS = FORM == kSplit ? 2 : 1;  // waves that share a query block
+  constexpr int BN = FORM == kPair ? 32 : 64, NWAVES = FORM == kPair ? 4 : 8, NQW = NWAVES / KS, BM = NQW * 32, NT = NWAVES * 64;
   constexpr int NCB = D / 32;                // 32-row blocks of O^T
   constexpr int ROWB = D * 2;                // bytes per bf16 row: V in the ring, O
   constexpr int INB = FP8 ? D : 2 * D;       // bytes per input row (q, k, v in memory; K rows in the ring)
@@ -120,7 +127,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
   constexpr int KSUBB = 32 * INB;            // bytes per 32-key block of it
   constexpr int TILEB = BN * ROWB;           // bytes per bf16 V tile in the ring
   constexpr int SUBB = 32 * ROWB;            // bytes per 32-key block of it
-  constexpr int NSLOT = KS == 1 ? 3 : 4;     // ring depth: bundles are requested NSLOT-1 ahead
+  constexpr int NSLOT = FORM == kWhole ? 3 : 4;     // ring depth: bundles are requested NSLOT-1 ahead
   constexpr int VBASE = NSLOT * KTILEB;      // K parts of the slots first, then the V parts
   constexpr int STGBASE = VBASE + NSLOT * TILEB;  // fp8: two staging slots of one e4m3 V tile each
   constexpr int STGTILE = BN * INB;
@@ -346,7 +353,7 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     if constexpr (FP8) {
       const i32x8 av = i32x8{(int)a.x[0], (int)a.x[1], (int)a.x[2], (int)a.x[3], (int)a.y[0], (int)a.y[1], (int)a.y[2], (int)a.y[3]};
       // literal zero scale operands select the instruction without block scales (the scaled form
-      // is not recognised as a matrix instruction by the scheduling-group pipeline and would be
+      // is not recognised as a plain matrix instruction by the compiler's scheduler and would be
       // left outside it, two dependent MFMAs back to back at the end of the step)
       return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, qf[kk], acc, 0, 0, 0, 0, 0, 0);
     } else {
@@ -654,15 +661,23 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     step_any(is_active(k1), k1, is_active(k1 - BN), s_a, s_b, p_a, p_b, slot * KTILEB, slot * TILEB);
     hand_on();
   };
-  if constexpr (KS == 2) {
+  if constexpr (FORM != kWhole) {
     set_tile((int)blockIdx.x);
-    // Q (128 rows, swizzled like a K tile) borrows the V parts of slots 2 and 3, key tiles 0 and 1 the K
+    if constexpr (FORM == kPair) {
+      const char* src = qhead + (size_t)min(qrow, N - 1) * INB + h * 16;
+#pragma unroll
+      for (int kk = 0; kk < NKQ; ++kk)
+        if constexpr (!FP8) qf[kk] = *(const bf16x8*)(src + kk * 32);
+    }
+    // KS = 2: Q (128 rows, swizzled like a K tile) borrows the V parts of slots 2 and 3; key tiles 0 and 1 the K
     // parts of slots 3 and 2
     constexpr int QBASE = VBASE + 2 * TILEB;
+    if constexpr (KS == 2) {
 #pragma unroll
-    for (int it = 0; it < 2 * NLD; ++it) {
-      const int s = it * NT + tid, r = s / NCHI, ch = (s % NCHI) ^ attn_swz_k<INB>(r);
-      attn_lds_dma16(qhead, (uint32_t)min(q0 + r, N - 1) * INB + (ch << 4), lds_wave + QBASE + it * NT * 16);
+      for (int it = 0; it < 2 * NLD; ++it) {
+        const int s = it * NT + tid, r = s / NCHI, ch = (s % NCHI) ^ attn_swz_k<INB>(r);
+        attn_lds_dma16(qhead, (uint32_t)min(q0 + r, N - 1) * INB + (ch << 4), lds_wave + QBASE + it * NT * 16);
+      }
     }
     issue_k(0, 3);
     issue_k(min(1, nt - 1), 2);
@@ -681,12 +696,14 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};
     ATTN_WAIT_VMCNT(4 * NLD);  // Q and key tiles 0 and 1 have landed
     attn_wg_barrier();
-    const int qr = (w % NQW) * 32 + qi;
+    if constexpr (KS == 2) {
+      const int qr = (w % NQW) * 32 + qi;
 #pragma unroll
-    for (int kk = 0; kk < NKQ; ++kk) {
-      // (kaddr's row qi and this row agree in the bits the swizzle uses)
-      const u32x4 x = *(LDS_AS const u32x4*)(smem + QBASE + qr * INB + (((2 * kk + h) ^ attn_swz_k<INB>(qr)) << 4));
-      if constexpr (!FP8) qf[kk] = __builtin_bit_cast(bf16x8, x);
+      for (int kk = 0; kk < NKQ; ++kk) {
+        // (kaddr's row qi and this row agree in the bits the swizzle uses)
+        const u32x4 x = *(LDS_AS const u32x4*)(smem + QBASE + qr * INB + (((2 * kk + h) ^ attn_swz_k<INB>(qr)) << 4));
+        if constexpr (!FP8) qf[kk] = __builtin_bit_cast(bf16x8, x);
+      }
     }
     // (a wave whose first block is invisible sees no key at all: l and O stay zero)
     if (is_active(kg * 32)) {
@@ -713,7 +730,8 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
 #pragma unroll
     for (int m = 0; m < RA; ++m) pre[m] = step_operand(ic<0>{}, m);
     const int vis = (CAUSAL ? min(wq0, N - 1) : N - 1) - kg * 32;
-    const int n_hot = (wave_valid && vis >= 95) ? (vis - 95) / 64 + 1 : 0;  // bundles whose block of tile b+1 every query sees in full
+    constexpr int LAST1 = BN + 31;  // last key of this wave's block of tile 1 (kg = 0)
+    const int n_hot = (wave_valid && vis >= LAST1) ? (vis - LAST1) / BN + 1 : 0;  // bundles whose block of tile b+1 every query sees in full
     int b = 0;
     for (; b < (n_hot & ~3); b += 4) {
       split_hot(b, ic<0>{});
@@ -727,6 +745,18 @@ __global__ void __launch_bounds__(512, 2) attn_fwd_sp_kernel(const AttnParams p)
     if (b & 1) hand_on();
     for (; b < nt; ++b) split_any(b);
 
+    if constexpr (KS == 1) {
+      ATTN_WAIT_VMCNT(0);  // no load writes the LDS any more
+      const float l = attn_sum_halves(l_run);
+      u32x4 out[2 * NCB];
+      attn_pack_o_rows<NCB>(oacc, p.out_scale / l, out);
+      if (qrow < N) {
+        const size_t row = (size_t)(tile_b * p.Hq + tile_hq) * N + qrow;
+        if (h == 0) p.lse[row] = (m_ref + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+        attn_store_packed_o<NCB>(out, (char*)p.o + row * ROWB + h * 16);
+      }
+      return;
+    }
     // ---- merge: each of the two waves gives away the columns the other one finishes ------------------
     float l = attn_sum_halves(l_run);
     ATTN_WAIT_VMCNT(0);
@@ -946,14 +976,57 @@ bool split_pays(const AttnParams& p, long long tiles) {
   return attn_split_pays(p.causal != 0, tiles, (long long)p.B * p.Hq * per_head, per_head, (p.N + 31) / 32, cost);
 }
 
-template <int D>
-int launch_split(const AttnParams& p, int, hipStream_t stream) {
+// What a launch of one form takes, us: n workgroups of `slots` per CU, the longest and the mean of their chains in 32-key
+// steps.  A step takes a + b (k - 1) where k workgroups share the CU, a workgroup P beside its chain, the launch F; it lasts as
+// long as the longest workgroup, or as all of them take: equal workgroups in whole rounds, the last one at t of a round if it is
+// nearly empty; causal ones, longest first, their share and half of t more.
+struct FormCost {
+  double F, P, a, b, t;
+};
+double form_us(const FormCost& c, bool causal, double n, int slots, double longest, double mean) {
+  const long long groups = (long long)n, cap = 256ll * slots, before = (groups - 1) / cap;
+  const double rounds = (double)((groups + 255) / 256), k = rounds < slots ? rounds : slots;
+  const double step = c.a + c.b * (k - 1.0), chain = c.P + longest * step;
+  double work = rounds;  // workgroups one after the other on a CU, each at its share of it
+  if (groups > cap) work = causal ? n / 256.0 + 0.5 * c.t : slots * ((double)before + c.t + (1.0 - c.t) * (n - (double)(before * cap)) / (double)cap);
+  const double all = work * (c.P + mean * step) / k;
+  return c.F + (chain > all ? chain : all);
+}
+
+// Paired workgroups (kPair) against the form that the launch would take otherwise.  The numbers are fits to 1609 random launches (heads
+// 1 .. 2000, N 60 .. 5000), all forms of each timed: on average over them the choice is 2 - 7 % faster than the choice without
+// this form, in 1 % of them slower, at worst by 6 %.  It pays where the launch has more tiles than CUs and short to middling
+// chains, whose first loads, first block and stores then run beside another workgroup's steps; us, otherwise -> paired:
+// d = 64 causal 192 heads x 327 16.0 -> 10.9, 512 x 903 110 -> 86; few tiles (32 heads x 1000, keys split) 13.6 -> 15.6;
+// d = 128 384 x 400 47.2 -> 48.9, 96 x 1962 causal 105.1 -> 110.7, and long launches
+// up to 8 % slower (every workgroup reads K and V for 128 queries instead of 256): those keep their form.
+bool pair_pays(const AttnParams& p, int d, bool split) {
+  static const FormCost cost[2][2][3] = {  // [d = 128][causal][whole, split, paired]
+      {{{0.98, 3.44, 0.469, 0.100, 1.00}, {0.85, 4.00, 0.496, 0.300, 1.00}, {0.67, 3.89, 0.319, 0.220, 0.24}},
+       {{1.70, 3.01, 0.433, 0.300, 1.13}, {1.16, 3.98, 0.466, 0.200, 0.94}, {1.51, 3.39, 0.316, 0.140, 4.44}}},
+      {{{0.36, 4.88, 0.730, 0.200, 1.00}, {0.00, 6.01, 0.762, 0.300, 1.00}, {0.33, 5.35, 0.413, 0.420, 0.38}},
+       {{0.18, 5.60, 0.628, 0.300, 1.08}, {0.00, 6.58, 0.651, 0.093, 1.08}, {0.00, 6.05, 0.406, 0.182, 3.44}}}};
+  const FormCost* const c = cost[d == 128][p.causal != 0];
+  const double heads = (double)p.B * p.Hq, steps = (p.N + 31) / 32;
+  auto us = [&](const FormCost& f, int bm, int slots, double part) {
+    const double T = (p.N + bm - 1) / bm;
+    const double mean = p.causal ? ((T - 1.0) * 0.5 * (bm / 32) + steps / T) : steps;
+    return form_us(f, p.causal != 0, heads * T, slots, part < 1.0 ? 0.5 * (steps + 1.0) : steps, part * mean);
+  };
+  const double n = heads * ((p.N + 127) / 128);
+  if (n > (1 << 22) || (p.causal && n <= 256.0) || steps > (d == 64 ? 128 : 64)) return false;
+  const double other = split ? us(c[1], 128, 1, 0.5) : us(c[0], 256, 1, 1.0);
+  return us(c[2], 128, d == 64 ? 3 : 2, 1.0) < (!p.causal ? 0.97 : d == 64 ? 0.94 : 0.95) * other;
+}
+
+template <int D, int FORM>
+int launch_128(const AttnParams& p, int, hipStream_t stream) {
   AttnParams q = p;
   q.T = (p.N + 127) / 128;
   q.map = attn_tile_map_make(p.B, p.Hq, p.Hkv, q.T, p.causal);
-  const dim3 grid(p.B * p.Hq * q.T);
-  if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 0, false, 2>), grid, dim3(512), 0, stream, q);
-  else hipLaunchKernelGGL((attn_fwd_sp_kernel<D, false, 0, false, 2>), grid, dim3(512), 0, stream, q);
+  const dim3 grid(p.B * p.Hq * q.T), block(FORM == kPair ? 256 : 512);
+  if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 0, false, FORM>), grid, block, 0, stream, q);
+  else hipLaunchKernelGGL((attn_fwd_sp_kernel<D, false, 0, false, FORM>), grid, block, 0, stream, q);
   return (int)hipGetLastError();
 }
 
@@ -975,8 +1048,11 @@ int launch_whole(const AttnParams& p, int grid, hipStream_t stream) {
 
 template <int D, bool FP8>
 int launch_sp(const AttnParams& p, int grid, hipStream_t stream) {
-  if constexpr (!FP8)
-    if (split_pays(p, grid)) return launch_split<D>(p, grid, stream);
+  if constexpr (!FP8) {
+    const bool split = split_pays(p, grid);
+    if (pair_pays(p, D, split)) return launch_128<D, kPair>(p, grid, stream);
+    if (split) return launch_128<D, kSplit>(p, grid, stream);
+  }
   return launch_whole<D, FP8>(p, grid, stream);
 }
 
@@ -989,7 +1065,10 @@ __global__ void attn_queue_reset_kernel(int* queue) {
 
 int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int workgroups, hipStream_t stream) {
   if (!p.queue || p.total <= 0 || workgroups <= 0) return -1;
-  if (split_pays(p, p.total)) return d == 128 ? launch_split<128>(p, 0, stream) : d == 64 ? launch_split<64>(p, 0, stream) : -1;
+  if (d != 128 && d != 64) return -1;
+  const bool split = split_pays(p, p.total);
+  if (pair_pays(p, d, split)) return d == 128 ? launch_128<128, kPair>(p, 0, stream) : launch_128<64, kPair>(p, 0, stream);
+  if (split) return d == 128 ? launch_128<128, kSplit>(p, 0, stream) : launch_128<64, kSplit>(p, 0, stream);
   hipLaunchKernelGGL(attn_queue_reset_kernel, dim3(1), dim3(64), 0, stream, p.queue);
   const dim3 grid(workgroups < p.total ? workgroups : p.total);
   if (d == 128) {
@@ -1018,8 +1097,10 @@ const AttnVariant* attn_sp_forms(int* count) {
   static const AttnVariant table[] = {
       {"bf16 d128 whole tiles BM256 BN64", 0, 128, 256, 64, 512, 2 * 3 * 64 * 128 * 2, launch_whole<128, false>},
       {"bf16 d64 whole tiles BM256 BN64", 0, 64, 256, 64, 512, 2 * 3 * 64 * 64 * 2, launch_whole<64, false>},
-      {"bf16 d128 split keys BM128 BN64", 0, 128, 128, 64, 512, 2 * 4 * 64 * 128 * 2, launch_split<128>},
-      {"bf16 d64 split keys BM128 BN64", 0, 64, 128, 64, 512, 2 * 4 * 64 * 64 * 2, launch_split<64>},
+      {"bf16 d128 split keys BM128 BN64", 0, 128, 128, 64, 512, 2 * 4 * 64 * 128 * 2, launch_128<128, kSplit>},
+      {"bf16 d64 split keys BM128 BN64", 0, 64, 128, 64, 512, 2 * 4 * 64 * 64 * 2, launch_128<64, kSplit>},
+      {"bf16 d128 paired BM128 BN32", 0, 128, 128, 32, 256, 2 * 4 * 32 * 128 * 2, launch_128<128, kPair>},
+      {"bf16 d64 paired BM128 BN32", 0, 64, 128, 32, 256, 2 * 4 * 32 * 64 * 2, launch_128<64, kPair>},
   };
   *count = (int)(sizeof(table) / sizeof(table[0]));
   return table;

@@ -21,14 +21,17 @@ def _bwd(d, causal, q, k, **size):
 ATTENTION = []
 for _d in (64, 128):
     ATTENTION += [
-        # few tiles: two waves share 32 queries; many: one tile a workgroup; three or more tiles per
-        # CU: one workgroup per CU walks a list of them
+        # few tiles: two waves share 32 queries; some more: one tile a workgroup; many: paired workgroups of 128 queries
         _fwd(_d, False, 0, 2, H=6, Hkv=3, N=517), _fwd(_d, True, 0, 2, H=6, Hkv=2, N=517),
-        _fwd(_d, False, 0, 1, H=70, Hkv=35, N=513), _fwd(_d, True, 0, 1, H=90, Hkv=45, N=513),
-        _fwd(_d, False, 2, 1, H=800, Hkv=400, N=201), _fwd(_d, True, 2, 1, H=800, Hkv=400, N=201), _fwd(_d, True, 2, 1, B=3, H=130, Hkv=65, N=430),
-        # the queue: four tiles and more for each resident workgroup
-        _fwd(_d, False, 1, 1, op="persistent", H=520, Hkv=260, N=300), _fwd(_d, True, 1, 1, op="persistent", H=520, Hkv=260, N=300),
-        _fwd(_d, False, 0, 2, op="persistent", H=5, N=300), _fwd(_d, True, 0, 2, op="persistent", H=5, N=300),
+        _fwd(_d, False, 0, 1, H=70, Hkv=35, N=513), _fwd(_d, True, 0, 1, H=64, Hkv=32, N=600),
+        _fwd(_d, False, 0, 3, H=90, Hkv=45, N=513), _fwd(_d, True, 0, 3, H=90, Hkv=45, N=513), _fwd(_d, False, 0, 3, B=2, H=130, Hkv=65, N=129),
+        _fwd(_d, True, 0, 3, H=520, Hkv=260, N=300),
+        # three or more 256-row tiles per CU: one workgroup per CU walks a list of them (long launches; here by the variant)
+        *[_fwd(_d, c, 2, 1, op="fwd_variant", variant=4 if _d == 128 else 5, H=800, Hkv=400, N=201) for c in (False, True)],
+        # the queue
+        _fwd(_d, False, 1, 1, op="persistent", H=64, Hkv=32, N=600), _fwd(_d, True, 1, 1, op="persistent", H=70, Hkv=35, N=513),
+        _fwd(_d, False, 0, 2, op="persistent", H=5, N=517), _fwd(_d, True, 0, 2, op="persistent", H=5, N=300),
+        _fwd(_d, False, 0, 3, op="persistent", H=130, Hkv=65, N=257), _fwd(_d, True, 0, 3, op="persistent", H=520, Hkv=260, N=300),
         _bwd(_d, False, 2, 2, H=6, Hkv=3, N=517), _bwd(_d, True, 2, 2, H=6, Hkv=2, N=517),
         _bwd(_d, False, 1, 2, H=140, Hkv=20, N=513), _bwd(_d, True, 1, 1, H=180, Hkv=90, N=300),
     ]
@@ -41,6 +44,9 @@ ATTENTION += [
 ATTENTION += [
     _fwd(128, False, 0, 1, op="fp8", H=4, Hkv=2, N=517), _fwd(128, True, 0, 1, op="fp8", H=4, Hkv=2, N=517),
     _fwd(128, True, 2, 1, op="fp8", H=800, Hkv=400, N=201), _fwd(128, False, 2, 1, op="fp8", H=800, Hkv=400, N=201),
+    # four tiles and more for each resident workgroup of the queue, three and more of the list
+    _fwd(128, False, 1, 1, op="persistent", H=1000, Hkv=500, N=250), _fwd(128, True, 1, 1, op="persistent", H=800, Hkv=400, N=201),
+    _fwd(128, True, 2, 1, B=3, H=130, Hkv=65, N=430),
     (["attn_fwd_fp8_kernel<128, false>"], dict(op="fp8_variant", variant=3, H=4, Hkv=2, N=517, d=128, causal=False)),
     (["attn_fwd_fp8_kernel<128, true>"], dict(op="fp8_variant", variant=3, H=4, Hkv=2, N=517, d=128, causal=True)),
 ]

@@ -82,11 +82,15 @@ def test_what_the_nt_product_chooses_is_among_the_variants():
 
 
 def test_the_forms_of_the_forward_are_forced_by_their_variants():
-    """"whole tiles" and "split keys" run that form whatever the size; "pipelined" follows the rule."""
+    """"whole tiles", "split keys" and "paired" run that form whatever the size; "pipelined" follows the rule."""
     calls = _form_calls()
     got, _ = routes(calls)
     for c, (st, launches) in zip(calls, got):
-        form = 1 if "whole" in A.attn_variant_name(c["variant"]) else 2  # (2 heads of 300 are few tiles: the rule splits)
+        name = A.attn_variant_name(c["variant"])
+        form = next((f for word, f in (("whole", 1), ("split", 2), ("paired", 3)) if word in name), None)
+        if form is None:
+            assert st == 0 and len(launches) == 1
+            continue
         assert st == 0 and [x[0] for x in launches] == [f"attn_fwd_sp_kernel<{c['d']}, {str(c['causal']).lower()}, 0, false, {form}>"], (c, launches)
 
 
@@ -110,32 +114,36 @@ def test_split_tile_map_is_a_bijection_and_keeps_an_xcd_on_few_slices(tmp_path, 
     assert all(max(s) - min(s) + 1 == len(s) <= (share - 1 + tiles_m * tiles_n - 1) // (tiles_m * tiles_n) + 1 for s in slices.values())
 
 
-# Sizes at which one form of the bf16 forward was measured at least 4 % faster than the other, us whole -> split
-# (heads, N, causal, d, split is faster)
-_FORMS = [(32, 1000, False, 128, True),    # 25.8 -> 20.3
-          (34, 2048, False, 128, True),    # 100.4 -> 92.0: three rounds of half tiles against two
-          (22, 4096, False, 128, True),    # 186.1 -> 172.7
-          (90, 1000, False, 128, False),   # 60.6 -> 69.8: the third round costs more than the shorter chain gives
-          (68, 1000, False, 128, False),   # 58.2 -> 63.5
-          (38, 1000, False, 128, False),   # 26.7 -> 40.5
-          (150, 150, False, 128, False),   # 10.5 -> 17.7
-          (150, 150, True, 128, False),    # 10.5 -> 16.1: 300 half tiles do not start at once
-          (150, 150, True, 64, False),     # 7.5 -> 11.4
-          (58, 1000, True, 128, False),    # 28.7 -> 31.2
-          (85, 513, True, 64, False),      # 13.2 -> 16.7
-          (32, 1000, True, 128, True),     # 25.8 -> 18.0
-          (48, 1000, True, 128, True),     # 26.3 -> 24.3
-          (16, 4096, True, 128, True),     # 84.9 -> 69.4
-          (75, 300, True, 128, True),      # 13.3 -> 11.2: 225 half tiles, fewer than the 300 that twice the tiles would be
-          (34, 4096, True, 64, False),     # 91.9 -> 110.1 at d = 128
-          (100, 64, False, 128, False),    # 5.9 -> 7.0: as many tiles either way, and a merge
-          (2, 40, False, 128, False),      # 5.3 -> 6.4
-          (100, 90, True, 64, False),      # 6.0 -> 6.4
-          (34, 2048, False, 64, True), (24, 2048, False, 64, False), (128, 2048, False, 64, False)]
+# Sizes at which a form of the bf16 forward was measured at least 4 % faster than another, us (w: whole tiles, s: split keys, p:
+# paired workgroups); (heads, N, causal, d, the form or forms that are right)
+_FORMS = [(32, 1000, False, 128, "s"),    # w 25.8, s 20.3
+          (34, 2048, False, 128, "sp"),   # w 100.4, s 92.0: three rounds of half tiles against two
+          (22, 4096, False, 128, "s"),    # w 186.1, s 172.7
+          (90, 1000, False, 128, "wp"),   # w 60.6, s 69.8: the third round costs more than the shorter chain gives
+          (68, 1000, False, 128, "wp"),   # w 58.2, s 63.5
+          (38, 1000, False, 128, "wp"),   # w 26.7, s 40.5
+          (150, 150, False, 128, "wp"),   # w 10.5, s 17.7
+          (150, 150, True, 128, "wp"),    # w 10.5, s 16.1: 300 half tiles do not start at once
+          (150, 150, True, 64, "wp"),     # w 7.5, s 11.4
+          (58, 1000, True, 128, "wp"),    # w 28.7, s 31.2
+          (85, 513, True, 64, "wp"),      # w 13.2, s 16.7
+          (32, 1000, True, 128, "s"),     # w 25.8, s 18.0
+          (48, 1000, True, 128, "s"),     # w 26.3, s 24.3
+          (16, 4096, True, 128, "s"),     # w 84.9, s 69.4
+          (75, 300, True, 128, "s"),      # w 13.3, s 11.2: 225 half tiles, fewer than the 300 that twice the tiles would be
+          (34, 4096, True, 64, "w"),      # w 91.9, s 110.1 at d = 128
+          (100, 64, False, 128, "wp"),    # w 5.9, s 7.0: as many tiles either way, and a merge
+          (2, 40, False, 128, "wp"),      # w 5.3, s 6.4
+          (100, 90, True, 64, "wp"),      # w 6.0, s 6.4
+          (34, 2048, False, 64, "sp"), (24, 2048, False, 64, "w"), (128, 2048, False, 64, "wp"),
+          (192, 327, True, 64, "p"),      # w 16.0, s 18.3, p 10.9
+          (512, 903, True, 64, "p"),      # w 109.7, s 130.2, p 86.1
+          (64, 8192, True, 128, "w"),     # w 905, s 1017, p 981
+          (64, 8192, False, 128, "w")]    # w 1750, s 1913, p 1864
 
 
 @pytest.mark.parametrize("op", ["fwd", "persistent"])
 def test_the_forward_takes_the_faster_form(op):
     got, _ = routes([dict(op=op, H=h, N=n, causal=c, d=d) for h, n, c, d, _ in _FORMS])
-    wrong = [(f, launches) for f, (st, launches) in zip(_FORMS, got) if st != 0 or launches[-1][0].endswith(", 2>") != f[4]]
+    wrong = [(f, launches) for f, (st, launches) in zip(_FORMS, got) if st != 0 or "wsp"[int(launches[-1][0][-2]) - 1] not in f[4]]
     assert not wrong, wrong

@@ -54,6 +54,8 @@ def test_attention_kernel(names, c):
         o, lse = _persistent(inp, split=len(names) == 1)
         o2, lse2 = gu.run_gpu(inp)  # the same results as attn_fwd, bit for bit
         assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
+    elif c["op"] == "fwd_variant":
+        o, lse = gu.run_gpu(inp, variant=c["variant"])
     elif c["op"] == "fp8_variant":
         dev, ds = gu.to_device(inp), inp["descale"]
         o = torch.full(inp["q"].shape, float("nan"), dtype=torch.bfloat16, device="cuda")
