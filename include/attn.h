@@ -161,8 +161,9 @@ long long attn_bwd_noalloc_max_workspace_bytes(void);
  * forced (see attn_variant_name) instead of chosen by the library.  Returns
  * ATTN_ERR_UNSUPPORTED if the variant does not exist for this d / dtype.
  * The bf16 variants named "pipelined" are what attn_fwd runs: they choose between
- * two forms by size, 256-row tiles or, for few tiles, 128-row tiles whose keys are
- * split between two waves; "whole tiles" and "split keys" are these forms by themselves.
+ * three forms by size, 256-row tiles, for few tiles 128-row tiles whose keys are
+ * split between two waves, for many short ones 128-row tiles of which two or three share a
+ * CU; "whole tiles", "split keys" and "paired" are these forms by themselves.
  */
 int attn_fwd_variant(const void* q, const void* k, const void* v, void* o, float* lse,
                      int B, int Hq, int Hkv, int N, int d, int causal, float scale,
@@ -184,7 +185,7 @@ const char* attn_variant_name(int variant);
  * attn_tile_coord -- host-side copy of the work decomposition the kernels use:
  * workgroup `wg` of a launch of attn_num_workgroups(...) workgroups with one tile each
  * processes query tile *t (rows t*BM .. t*BM+BM-1) of head *hq in batch *b (BM = 256,
- * or 128 where bf16 keys are split; resident workgroups take the same tiles in turn).  Host
+ * or 128 where bf16 keys are split or workgroups are paired; resident workgroups take the same tiles in turn).  Host
  * pointers.  Used to check that the map is a bijection and keeps the
  * workgroups that share a K/V head on one XCD.  Returns an attn_status.
  */

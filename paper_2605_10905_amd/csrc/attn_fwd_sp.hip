@@ -26,7 +26,7 @@
 // needs one workgroup barrier per 64 keys: it is both the "full" signal of bundle b+1 and the
 // "empty" signal of bundle b-1 (stage = b mod 3).  The barrier sits between the two 32-key steps
 // of an iteration so that the first K operands of the next iteration can be read one step
-// early; the loads into the slot it frees are issued one at a time at the region cuts of the
+// early; the loads into the slot it frees are issued one at a time between the slots of the
 // iteration's second step, never in a burst that keeps every wave off the matrix pipe at once.
 //
 // No block maximum is taken on the common path: exponentials are computed against the current
@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
   };
   auto step_hot = [&](f32x16& s_in, f32x16& s_out, u32x4 (&p_out)[2], u32x4 (&p_pv)[2], auto bid, auto bidnext, auto nseg_tag, auto between) __attribute__((always_inline)) {
     constexpr int NSEG = decltype(nseg_tag)::value, SEG = NM / NSEG;
-    static_assert(NSEG <= 4 && NM % NSEG == 0, "whole regions");
+    static_assert(NSEG <= 4 && NM % NSEG == 0, "whole slots");
     Operand op[NM];
 #pragma unroll
     for (int m = 0; m < RA; ++m) op[m] = pre[m];
@@ -541,7 +541,7 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
     float ls = ls0;
     if (__builtin_amdgcn_ballot_w64(!(ls <= kSumLimit)) != 0) {
       // the redo path "reads" the optimistic packs, so that they are computed inside the
-      // pipelined region above and not sunk below this branch into the common path's tail
+      // pipelined step above and not sunk below this branch into the common path's tail
       asm volatile("" ::"v"(p_out[0]), "v"(p_out[1]));
       raise_reference(block_max(s_in), nullptr, std::false_type{});
       ls = exp_block(s_in, p_out, std::integral_constant<bool, !FP8>{});
@@ -584,8 +584,8 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
       if (b + 3 < nt) issue_v(b + 3, (b + 1) & 1);
   };
   auto nothing = [](int) __attribute__((always_inline)) {};
-  // Pipelined form: the same work is handed out over the region cuts of the iteration's second
-  // step, one piece in front of each region, between the operand reads.  A bundle index past the
+  // Pipelined form: the same work is handed out over the iteration's second
+  // step, one piece in front of every SEG-th slot, between the operand reads.  A bundle index past the
   // end re-requests the last tiles into the free slot, which is never read again (and converts
   // whatever the staging slot holds): the loads in flight per wave are then the same in every
   // iteration.

@@ -29,11 +29,10 @@ struct AttnParams {
 //     third round then has to pay for its fixed cost.
 //   causal: only up to 256 whole tiles, where the longest of them sets the time.  The split tiles, longest
 //     first, take their mean over the CUs, and `last` of a mean tile longer where they do not all start at once.
-// The callers' numbers are fits to 908 launches of the forward and 840 of the
-// backward (d = 64 and 128, N = 20 .. 6000, 2 .. 768 whole tiles, grouped heads among them, all forms of each timed
-// in turn).  Of these, one is more than 2 % slower than the whole form (47 causal heads of 983, d = 128: 27.3 -> 28.2 us,
-// where 48 heads of 1000 gain 8 %), and the choice stays within 0.7 % of the better form on average.  (A kernel that needs few enough registers for two workgroups
-// per CU, the dQ kernels at d = 64, blurs its rounds; the same fit holds there.)
+// The callers' numbers are fits to 908 launches of the forward and 1380 of the
+// backward (d = 64 and 128, N = 20 .. 6000, grouped heads among them, both forms of each timed
+// in turn); what the choice costs against the better form stands at the callers.  (A kernel that needs few enough
+// registers for two workgroups per CU, dQ at d = 64, blurs its rounds; its fit holds that.)
 struct AttnSplitCost {
   double fixed, fixed_split, slower, last;
   double least;  // steps below which the split form saves nothing: its tiles are then as many, each with a merge
