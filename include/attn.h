@@ -96,9 +96,10 @@ int attn_fwd_fp8(const void* q, const void* k, const void* v, void* o, float* ls
  * attn_fwd_persistent -- attn_fwd for bfloat16 as a persistent launch: one workgroup per compute
  * unit, each taking query tiles from a queue in device memory until it is drained (the software
  * form of the paper's dynamic tile assignment by cluster launch control, section 4.2: a kernel
- * that stays resident and balances irregular tile run times).  Launches of few tiles, which attn_fwd
- * splits over the keys, have nothing to balance and run that same kernel here, one workgroup per
- * 128-row tile; they do not use the queue.  Same results as attn_fwd, bit for bit.
+ * that stays resident and balances irregular tile run times), or several of them where the launch takes the form
+ * whose workgroups share a compute unit.  Launches of few tiles have nothing to balance: those that attn_fwd splits over the
+ * keys, and those of workgroups that share compute units and all start at once, run that same kernel here, one
+ * workgroup per 128-row tile, and do not use the queue.  Same results as attn_fwd, bit for bit.
  *   queue   device, attn_persistent_queue_bytes() bytes, 128-byte aligned, owned by the caller, required
  *           at every size; contents on entry are irrelevant (a launch that uses it enqueues a kernel
  *           that clears it first), it must not be shared by calls that can overlap on the device

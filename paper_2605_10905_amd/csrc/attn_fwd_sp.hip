@@ -76,6 +76,8 @@ template <int V>
 using ic = std::integral_constant<int, V>;
 
 enum { kWhole = 1, kSplit = 2, kPair = 3 };  // FORM of attn_fwd_sp_kernel
+template <int D>
+constexpr int kPairSlots = D == 64 ? 3 : 2;  // paired workgroups that share a CU
 
 template <class F, int... M>
 __device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M...>) {
@@ -109,14 +111,15 @@ __device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M.
 // the step, and the ring has four slots so that a bundle is requested three steps ahead.  Q travels
 // through LDS as well: with no load the compiler knows of, the waits are exact, and the first scores
 // need only Q and key tiles 0 and 1 to have arrived, not bundles 0 and 1 requested behind them.
-// FORM = kPair (bf16, MODE 0): four waves own 128 queries, key tiles of 32 and otherwise the one-step iterations of the split
+// FORM = kPair (bf16, MODE 0 and 1): four waves own 128 queries, key tiles of 32 and otherwise the one-step iterations of the split
 // form.  The ring is 64 KB (d = 64: 32), so two (three) such workgroups share a CU, and one's first loads, first
 // block, diagonal and stores run beside the other's steps; its bytes are those of the whole form.  By itself a step
 // takes it 0.56 us (d = 128), beside another one 0.78.
 template <int D, bool CAUSAL, int MODE, bool FP8, int FORM = kWhole>
 __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kernel(const AttnParams p) {
   static_assert(!FP8 || (D == 128 && MODE != 1), "fp8 inputs: head dimension 128, no queue launch");
-  static_assert(FORM == kWhole || (MODE == 0 && !FP8), "split keys and paired workgroups: bf16, one tile per workgroup");
+  static_assert(FORM == kWhole || !FP8, "split keys and paired workgroups: bf16");
+  static_assert(FORM == kWhole || MODE == 0 || (FORM == kPair && MODE == 1), "split keys: one tile per workgroup; paired workgroups: also from the queue");
   constexpr int KS = FORM == kSplit ? 2 : 1;  // waves that share a query block
   constexpr int BN = FORM == kPair ? 32 : 64, NWAVES = FORM == kPair ? 4 : 8, NQW = NWAVES / KS, BM = NQW * 32, NT = NWAVES * 64;
   constexpr int NCB = D / 32;                // 32-row blocks of O^T
@@ -662,153 +665,157 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
     hand_on();
   };
   if constexpr (FORM != kWhole) {
-    set_tile((int)blockIdx.x);
-    if constexpr (FORM == kPair) {
-      const char* src = qhead + (size_t)min(qrow, N - 1) * INB + h * 16;
+    // (from the queue: next_tile_index() holds the barrier behind which no wave reads the finished tile's ring; nothing of the next tile
+    // is requested before it, the workgroups beside this one fill the seam)
+    for (int wg = MODE == 1 ? next_tile_index() : (int)blockIdx.x; wg >= 0; wg = MODE == 1 ? next_tile_index() : -1) {
+      set_tile(wg);
+      if constexpr (FORM == kPair) {
+        const char* src = qhead + (size_t)min(qrow, N - 1) * INB + h * 16;
 #pragma unroll
-      for (int kk = 0; kk < NKQ; ++kk)
-        if constexpr (!FP8) qf[kk] = *(const bf16x8*)(src + kk * 32);
-    }
-    // KS = 2: Q (128 rows, swizzled like a K tile) borrows the V parts of slots 2 and 3; key tiles 0 and 1 the K
-    // parts of slots 3 and 2
-    constexpr int QBASE = VBASE + 2 * TILEB;
-    if constexpr (KS == 2) {
-#pragma unroll
-      for (int it = 0; it < 2 * NLD; ++it) {
-        const int s = it * NT + tid, r = s / NCHI, ch = (s % NCHI) ^ attn_swz_k<INB>(r);
-        attn_lds_dma16(qhead, (uint32_t)min(q0 + r, N - 1) * INB + (ch << 4), lds_wave + QBASE + it * NT * 16);
+        for (int kk = 0; kk < NKQ; ++kk)
+          if constexpr (!FP8) qf[kk] = *(const bf16x8*)(src + kk * 32);
       }
-    }
-    issue_k(0, 3);
-    issue_k(min(1, nt - 1), 2);
+      // KS = 2: Q (128 rows, swizzled like a K tile) borrows the V parts of slots 2 and 3; key tiles 0 and 1 the K
+      // parts of slots 3 and 2
+      constexpr int QBASE = VBASE + 2 * TILEB;
+      if constexpr (KS == 2) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      issue_k(min(b + 2, nt - 1), b);
-      issue_v(min(b, nt - 1), b);
-    }
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
-    m_ref = kNoRef;
-    l_run = 0.f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};
-    ATTN_WAIT_VMCNT(4 * NLD);  // Q and key tiles 0 and 1 have landed
-    attn_wg_barrier();
-    if constexpr (KS == 2) {
-      const int qr = (w % NQW) * 32 + qi;
-#pragma unroll
-      for (int kk = 0; kk < NKQ; ++kk) {
-        // (kaddr's row qi and this row agree in the bits the swizzle uses)
-        const u32x4 x = *(LDS_AS const u32x4*)(smem + QBASE + qr * INB + (((2 * kk + h) ^ attn_swz_k<INB>(qr)) << 4));
-        if constexpr (!FP8) qf[kk] = __builtin_bit_cast(bf16x8, x);
+        for (int it = 0; it < 2 * NLD; ++it) {
+          const int s = it * NT + tid, r = s / NCHI, ch = (s % NCHI) ^ attn_swz_k<INB>(r);
+          attn_lds_dma16(qhead, (uint32_t)min(q0 + r, N - 1) * INB + (ch << 4), lds_wave + QBASE + it * NT * 16);
+        }
       }
-    }
-    // (a wave whose first block is invisible sees no key at all: l and O stay zero)
-    if (is_active(kg * 32)) {
-      // Both waves start from the reference maximum of keys 0 .. 31, all of which this wave's queries see,
-      // as the unsplit form does: blocks far below it (masked keys, down to -inf) get probabilities of zero
-      // instead of a reference of their own against which they would overflow, and P is rounded as there.
-      // (Measured, without -> with: 2 heads of 256 6.23 -> 6.31 us, 32 of 1000 causal 18.2 -> 18.4.)
-      if (kg) {
-        qk_block(s_b, 3 * KTILEB - KSUBB);
-        m_ref = fmaxf(m_ref, block_max(s_b));
+      issue_k(0, 3);
+      issue_k(min(1, nt - 1), 2);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        issue_k(min(b + 2, nt - 1), b);
+        issue_v(min(b, nt - 1), b);
       }
-      qk_block(s_b, 3 * KTILEB);
-      softmax_block(s_b, p_b, p_a, kg * 32, needs_mask(kg * 32));
-      qk_block(s_a, 2 * KTILEB);
-      bound_first();
-    }
 #pragma unroll
-    for (int kk = 0; kk < NKQ; ++kk) asm volatile("" ::"v"(qf[kk]));  // (read by every wave before the barrier, too)
-    lds_ops_done();
-    ATTN_WAIT_VMCNT(2 * NLD);
-    attn_wg_barrier();  // bundle 0 is full; slots 2 and 3 are free
-    issue_k(min(4, nt - 1), 2);
-    issue_v(min(2, nt - 1), 2);
+      for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-    for (int m = 0; m < RA; ++m) pre[m] = step_operand(ic<0>{}, m);
-    const int vis = (CAUSAL ? min(wq0, N - 1) : N - 1) - kg * 32;
-    constexpr int LAST1 = BN + 31;  // last key of this wave's block of tile 1 (kg = 0)
-    const int n_hot = (wave_valid && vis >= LAST1) ? (vis - LAST1) / BN + 1 : 0;  // bundles whose block of tile b+1 every query sees in full
-    int b = 0;
-    for (; b < (n_hot & ~3); b += 4) {
-      split_hot(b, ic<0>{});
-      split_hot(b + 1, ic<1>{});
-      split_hot(b + 2, ic<2>{});
-      split_hot(b + 3, ic<3>{});
-    }
-    if (b < n_hot) { split_hot(b, ic<0>{}); ++b; }
-    if (b < n_hot) { split_hot(b, ic<1>{}); ++b; }
-    if (b < n_hot) { split_hot(b, ic<2>{}); ++b; }
-    if (b & 1) hand_on();
-    for (; b < nt; ++b) split_any(b);
+        for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
+      m_ref = kNoRef;
+      l_run = 0.f;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) p_a[i] = p_b[i] = u32x4{0, 0, 0, 0};
+      ATTN_WAIT_VMCNT(4 * NLD);  // Q and key tiles 0 and 1 have landed
+      attn_wg_barrier();
+      if constexpr (KS == 2) {
+        const int qr = (w % NQW) * 32 + qi;
+#pragma unroll
+        for (int kk = 0; kk < NKQ; ++kk) {
+          // (kaddr's row qi and this row agree in the bits the swizzle uses)
+          const u32x4 x = *(LDS_AS const u32x4*)(smem + QBASE + qr * INB + (((2 * kk + h) ^ attn_swz_k<INB>(qr)) << 4));
+          if constexpr (!FP8) qf[kk] = __builtin_bit_cast(bf16x8, x);
+        }
+      }
+      // (a wave whose first block is invisible sees no key at all: l and O stay zero)
+      if (is_active(kg * 32)) {
+        // Both waves start from the reference maximum of keys 0 .. 31, all of which this wave's queries see,
+        // as the unsplit form does: blocks far below it (masked keys, down to -inf) get probabilities of zero
+        // instead of a reference of their own against which they would overflow, and P is rounded as there.
+        // (Measured, without -> with: 2 heads of 256 6.23 -> 6.31 us, 32 of 1000 causal 18.2 -> 18.4.)
+        if (kg) {
+          qk_block(s_b, 3 * KTILEB - KSUBB);
+          m_ref = fmaxf(m_ref, block_max(s_b));
+        }
+        qk_block(s_b, 3 * KTILEB);
+        softmax_block(s_b, p_b, p_a, kg * 32, needs_mask(kg * 32));
+        qk_block(s_a, 2 * KTILEB);
+        bound_first();
+      }
+#pragma unroll
+      for (int kk = 0; kk < NKQ; ++kk) asm volatile("" ::"v"(qf[kk]));  // (read by every wave before the barrier, too)
+      lds_ops_done();
+      ATTN_WAIT_VMCNT(2 * NLD);
+      attn_wg_barrier();  // bundle 0 is full; slots 2 and 3 are free
+      issue_k(min(4, nt - 1), 2);
+      issue_v(min(2, nt - 1), 2);
+#pragma unroll
+      for (int m = 0; m < RA; ++m) pre[m] = step_operand(ic<0>{}, m);
+      const int vis = (CAUSAL ? min(wq0, N - 1) : N - 1) - kg * 32;
+      constexpr int LAST1 = BN + 31;  // last key of this wave's block of tile 1 (kg = 0)
+      const int n_hot = (wave_valid && vis >= LAST1) ? (vis - LAST1) / BN + 1 : 0;  // bundles whose block of tile b+1 every query sees in full
+      int b = 0;
+      for (; b < (n_hot & ~3); b += 4) {
+        split_hot(b, ic<0>{});
+        split_hot(b + 1, ic<1>{});
+        split_hot(b + 2, ic<2>{});
+        split_hot(b + 3, ic<3>{});
+      }
+      if (b < n_hot) { split_hot(b, ic<0>{}); ++b; }
+      if (b < n_hot) { split_hot(b, ic<1>{}); ++b; }
+      if (b < n_hot) { split_hot(b, ic<2>{}); ++b; }
+      if (b & 1) hand_on();
+      for (; b < nt; ++b) split_any(b);
 
-    if constexpr (KS == 1) {
-      ATTN_WAIT_VMCNT(0);  // no load writes the LDS any more
-      const float l = attn_sum_halves(l_run);
-      u32x4 out[2 * NCB];
-      attn_pack_o_rows<NCB>(oacc, p.out_scale / l, out);
-      if (qrow < N) {
-        const size_t row = (size_t)(tile_b * p.Hq + tile_hq) * N + qrow;
-        if (h == 0) p.lse[row] = (m_ref + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
-        attn_store_packed_o<NCB>(out, (char*)p.o + row * ROWB + h * 16);
+      if constexpr (KS == 1) {
+        ATTN_WAIT_VMCNT(0);  // no load writes the LDS any more
+        const float l = attn_sum_halves(l_run);
+        u32x4 out[2 * NCB];
+        attn_pack_o_rows<NCB>(oacc, p.out_scale / l, out);
+        if (qrow < N) {
+          const size_t row = (size_t)(tile_b * p.Hq + tile_hq) * N + qrow;
+          if (h == 0) p.lse[row] = (m_ref + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+          attn_store_packed_o<NCB>(out, (char*)p.o + row * ROWB + h * 16);
+        }
+        continue;
       }
-      return;
-    }
-    // ---- merge: each of the two waves gives away the columns the other one finishes ------------------
-    float l = attn_sum_halves(l_run);
-    ATTN_WAIT_VMCNT(0);
-    attn_wg_barrier();  // no load is in flight and no wave reads the ring any more
-    constexpr int NH = NCB / 2, MLBASE = NWAVES * NH * 4096;
-    static_assert(MLBASE + NWAVES * 512 <= STGBASE, "the exchanged halves fit the ring");
-    const int wq = w % NQW;
-    LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((kg ^ 1) * NQW + wq) * NH * 256 + lane;
-    LDS_AS f32x4* const take = (LDS_AS f32x4*)smem + w * NH * 256 + lane;
-    f32x16 mine[NH];
+      // ---- merge: each of the two waves gives away the columns the other one finishes ------------------
+      float l = attn_sum_halves(l_run);
+      ATTN_WAIT_VMCNT(0);
+      attn_wg_barrier();  // no load is in flight and no wave reads the ring any more
+      constexpr int NH = NCB / 2, MLBASE = NWAVES * NH * 4096;
+      static_assert(MLBASE + NWAVES * 512 <= STGBASE, "the exchanged halves fit the ring");
+      const int wq = w % NQW;
+      LDS_AS f32x4* const give = (LDS_AS f32x4*)smem + ((kg ^ 1) * NQW + wq) * NH * 256 + lane;
+      LDS_AS f32x4* const take = (LDS_AS f32x4*)smem + w * NH * 256 + lane;
+      f32x16 mine[NH];
 #pragma unroll
-    for (int cb = 0; cb < NH; ++cb) {
-      const f32x16 other = kg ? oacc[cb] : oacc[NH + cb];
-      mine[cb] = kg ? oacc[NH + cb] : oacc[cb];
+      for (int cb = 0; cb < NH; ++cb) {
+        const f32x16 other = kg ? oacc[cb] : oacc[NH + cb];
+        mine[cb] = kg ? oacc[NH + cb] : oacc[cb];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) give[(cb * 4 + a) * 64] = f32x4{other[4 * a], other[4 * a + 1], other[4 * a + 2], other[4 * a + 3]};
-    }
-    ((LDS_AS f32x2*)(smem + MLBASE))[((kg ^ 1) * NQW + wq) * 64 + lane] = f32x2{m_ref, l};
-    __syncthreads();
-    f32x2 ml = ((LDS_AS const f32x2*)(smem + MLBASE))[w * 64 + lane];
-    const float m = fmaxf(m_ref, ml[0]);
-    const float a_mine = __builtin_amdgcn_exp2f(m_ref - m), a_other = __builtin_amdgcn_exp2f(ml[0] - m);
-    const bool drop_mine = a_mine == 0.f && l > kSumDrop, drop_other = a_other == 0.f && ml[1] > kSumDrop;
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(drop_mine || drop_other) != 0, 0)) {
-      // (as in raise_reference)
-      if (drop_mine) l = 0.f;
-      if (drop_other) ml[1] = 0.f;
+        for (int a = 0; a < 4; ++a) give[(cb * 4 + a) * 64] = f32x4{other[4 * a], other[4 * a + 1], other[4 * a + 2], other[4 * a + 3]};
+      }
+      ((LDS_AS f32x2*)(smem + MLBASE))[((kg ^ 1) * NQW + wq) * 64 + lane] = f32x2{m_ref, l};
+      __syncthreads();
+      f32x2 ml = ((LDS_AS const f32x2*)(smem + MLBASE))[w * 64 + lane];
+      const float m = fmaxf(m_ref, ml[0]);
+      const float a_mine = __builtin_amdgcn_exp2f(m_ref - m), a_other = __builtin_amdgcn_exp2f(ml[0] - m);
+      const bool drop_mine = a_mine == 0.f && l > kSumDrop, drop_other = a_other == 0.f && ml[1] > kSumDrop;
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(drop_mine || drop_other) != 0, 0)) {
+        // (as in raise_reference)
+        if (drop_mine) l = 0.f;
+        if (drop_other) ml[1] = 0.f;
+#pragma unroll
+        for (int cb = 0; cb < NH; ++cb)
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            if (drop_other) take[(cb * 4 + a) * 64] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (drop_mine) mine[cb][4 * a + r] = 0.f;
+          }
+      }
+      const float l_all = l * a_mine + ml[1] * a_other;
 #pragma unroll
       for (int cb = 0; cb < NH; ++cb)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          if (drop_other) take[(cb * 4 + a) * 64] = f32x4{0.f, 0.f, 0.f, 0.f};
+          const f32x4 o = take[(cb * 4 + a) * 64];
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (drop_mine) mine[cb][4 * a + r] = 0.f;
+          for (int r = 0; r < 4; ++r) mine[cb][4 * a + r] = mine[cb][4 * a + r] * a_mine + o[r] * a_other;
         }
-    }
-    const float l_all = l * a_mine + ml[1] * a_other;
-#pragma unroll
-    for (int cb = 0; cb < NH; ++cb)
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const f32x4 o = take[(cb * 4 + a) * 64];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) mine[cb][4 * a + r] = mine[cb][4 * a + r] * a_mine + o[r] * a_other;
+      u32x4 out[2 * NH];
+      attn_pack_o_rows<NH>(mine, p.out_scale / l_all, out);
+      if (qrow < N) {
+        const size_t row = (size_t)(tile_b * p.Hq + tile_hq) * N + qrow;
+        if (kg == 0 && h == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f;
+        attn_store_packed_o<NH>(out, (char*)p.o + row * ROWB + kg * NH * 64 + h * 16);
       }
-    u32x4 out[2 * NH];
-    attn_pack_o_rows<NH>(mine, p.out_scale / l_all, out);
-    if (qrow < N) {
-      const size_t row = (size_t)(tile_b * p.Hq + tile_hq) * N + qrow;
-      if (kg == 0 && h == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f;
-      attn_store_packed_o<NH>(out, (char*)p.o + row * ROWB + kg * NH * 64 + h * 16);
     }
     return;
   }
@@ -1017,15 +1024,22 @@ bool pair_pays(const AttnParams& p, int d, bool split) {
   const double n = heads * ((p.N + 127) / 128);
   if (n > (1 << 22) || (p.causal && n <= 256.0) || steps > (d == 64 ? 128 : 64)) return false;
   const double other = split ? us(c[1], 128, 1, 0.5) : us(c[0], 256, 1, 1.0);
-  return us(c[2], 128, d == 64 ? 3 : 2, 1.0) < (!p.causal ? 0.97 : d == 64 ? 0.94 : 0.95) * other;
+  return us(c[2], 128, d == 64 ? kPairSlots<64> : kPairSlots<128>, 1.0) < (!p.causal ? 0.97 : d == 64 ? 0.94 : 0.95) * other;
+}
+
+// the launch in tiles of 128 queries
+AttnParams in_tiles_of_128(const AttnParams& p) {
+  AttnParams q = p;
+  q.T = (p.N + 127) / 128;
+  q.total = p.B * p.Hq * q.T;
+  q.map = attn_tile_map_make(p.B, p.Hq, p.Hkv, q.T, p.causal);
+  return q;
 }
 
 template <int D, int FORM>
 int launch_128(const AttnParams& p, int, hipStream_t stream) {
-  AttnParams q = p;
-  q.T = (p.N + 127) / 128;
-  q.map = attn_tile_map_make(p.B, p.Hq, p.Hkv, q.T, p.causal);
-  const dim3 grid(p.B * p.Hq * q.T), block(FORM == kPair ? 256 : 512);
+  const AttnParams q = in_tiles_of_128(p);
+  const dim3 grid(q.total), block(FORM == kPair ? 256 : 512);
   if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 0, false, FORM>), grid, block, 0, stream, q);
   else hipLaunchKernelGGL((attn_fwd_sp_kernel<D, false, 0, false, FORM>), grid, block, 0, stream, q);
   return (int)hipGetLastError();
@@ -1062,26 +1076,31 @@ __global__ void attn_queue_reset_kernel(int* queue) {
   if (threadIdx.x < 8) queue[threadIdx.x * 32] = 0;
 }
 
+template <int D, int FORM>
+void launch_resident(const AttnParams& p, int workgroups, hipStream_t stream) {
+  const dim3 grid(workgroups < p.total ? workgroups : p.total), block(FORM == kPair ? 256 : 512);
+  if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 1, false, FORM>), grid, block, 0, stream, p);
+  else hipLaunchKernelGGL((attn_fwd_sp_kernel<D, false, 1, false, FORM>), grid, block, 0, stream, p);
+}
+
+// The form is the one that attn_fwd takes.  Launches that are few enough tiles for split keys (run paired where that is faster
+// still) leave the queue alone, all others drain it: one whole-tile workgroup per CU, or as many paired ones as share a CU.
+template <int D>
+int launch_queue(const AttnParams& p, int cus, hipStream_t stream) {
+  const bool split = split_pays(p, p.total), pair = pair_pays(p, D, split);
+  if (pair && (split || in_tiles_of_128(p).total <= cus * kPairSlots<D>)) return launch_128<D, kPair>(p, 0, stream);
+  if (split) return launch_128<D, kSplit>(p, 0, stream);
+  hipLaunchKernelGGL(attn_queue_reset_kernel, dim3(1), dim3(64), 0, stream, p.queue);
+  if (pair) launch_resident<D, kPair>(in_tiles_of_128(p), cus * kPairSlots<D>, stream);
+  else launch_resident<D, kWhole>(p, cus, stream);
+  return (int)hipGetLastError();
+}
+
 }  // namespace
 
-int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int workgroups, hipStream_t stream) {
-  if (!p.queue || p.total <= 0 || workgroups <= 0) return -1;
-  if (d != 128 && d != 64) return -1;
-  const bool split = split_pays(p, p.total);
-  if (pair_pays(p, d, split)) return d == 128 ? launch_128<128, kPair>(p, 0, stream) : launch_128<64, kPair>(p, 0, stream);
-  if (split) return d == 128 ? launch_128<128, kSplit>(p, 0, stream) : launch_128<64, kSplit>(p, 0, stream);
-  hipLaunchKernelGGL(attn_queue_reset_kernel, dim3(1), dim3(64), 0, stream, p.queue);
-  const dim3 grid(workgroups < p.total ? workgroups : p.total);
-  if (d == 128) {
-    if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<128, true, 1, false>), grid, dim3(512), 0, stream, p);
-    else hipLaunchKernelGGL((attn_fwd_sp_kernel<128, false, 1, false>), grid, dim3(512), 0, stream, p);
-  } else if (d == 64) {
-    if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<64, true, 1, false>), grid, dim3(512), 0, stream, p);
-    else hipLaunchKernelGGL((attn_fwd_sp_kernel<64, false, 1, false>), grid, dim3(512), 0, stream, p);
-  } else {
-    return -1;
-  }
-  return (int)hipGetLastError();
+int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int cus, hipStream_t stream) {
+  if (!p.queue || p.total <= 0 || cus <= 0 || (d != 128 && d != 64)) return -1;
+  return d == 128 ? launch_queue<128>(p, cus, stream) : launch_queue<64>(p, cus, stream);
 }
 
 const AttnVariant* attn_sp_variants(int* count) {

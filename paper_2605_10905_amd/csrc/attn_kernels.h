@@ -59,8 +59,8 @@ inline bool attn_split_pays(bool causal, long long whole, long long split, int s
   return t_split < t_whole;
 }
 
-// persistent bf16 forward (d = 64 or 128): `workgroups` resident workgroups drain the tile queue
-int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int workgroups, hipStream_t stream);
+// persistent bf16 forward (d = 64 or 128): workgroups that stay resident on `cus` CUs drain the tile queue
+int attn_fwd_bf16_persistent_launch(const AttnParams& p, int d, int cus, hipStream_t stream);
 
 // backward pass (bf16, head dimension 128 or 64)
 struct AttnBwdParams {

@@ -23,15 +23,16 @@ for _d in (64, 128):
     ATTENTION += [
         # few tiles: two waves share 32 queries; some more: one tile a workgroup; many: paired workgroups of 128 queries
         _fwd(_d, False, 0, 2, H=6, Hkv=3, N=517), _fwd(_d, True, 0, 2, H=6, Hkv=2, N=517),
-        _fwd(_d, False, 0, 1, H=70, Hkv=35, N=513), _fwd(_d, True, 0, 1, H=64, Hkv=32, N=600),
-        _fwd(_d, False, 0, 3, H=90, Hkv=45, N=513), _fwd(_d, True, 0, 3, H=90, Hkv=45, N=513), _fwd(_d, False, 0, 3, B=2, H=130, Hkv=65, N=129),
-        _fwd(_d, True, 0, 3, H=520, Hkv=260, N=300),
-        # three or more 256-row tiles per CU: one workgroup per CU walks a list of them (long launches; here by the variant)
+        _fwd(_d, False, 0, 1, H=70, Hkv=35, N=513), _fwd(_d, True, 0, 3, H=90, Hkv=45, N=513), _fwd(_d, True, 0, 1, H=64, Hkv=32, N=600),
+        _fwd(_d, False, 0, 3, H=90, Hkv=45, N=513), _fwd(_d, False, 0, 3, B=2, H=130, Hkv=65, N=129), _fwd(_d, True, 0, 3, H=520, Hkv=260, N=300),
+        # three or more 256-row tiles per CU: one workgroup per CU walks a list of them (d = 64: long launches, and here by the variant)
+        _fwd(_d, True, *((2, 1) if _d == 128 else (0, 3)), H=800, Hkv=400, N=201), _fwd(_d, True, *((2, 1) if _d == 128 else (0, 3)), B=3, H=130, Hkv=65, N=430),
         *[_fwd(_d, c, 2, 1, op="fwd_variant", variant=4 if _d == 128 else 5, H=800, Hkv=400, N=201) for c in (False, True)],
-        # the queue
+        # the queue: more tiles than start at once (paired), and whole tiles; few tiles leave it alone
+        _fwd(_d, False, 1, 3, op="persistent", H=520, Hkv=260, N=300), _fwd(_d, True, 1, 3, op="persistent", H=520, Hkv=260, N=300),
         _fwd(_d, False, 1, 1, op="persistent", H=64, Hkv=32, N=600), _fwd(_d, True, 1, 1, op="persistent", H=70, Hkv=35, N=513),
-        _fwd(_d, False, 0, 2, op="persistent", H=5, N=517), _fwd(_d, True, 0, 2, op="persistent", H=5, N=300),
-        _fwd(_d, False, 0, 3, op="persistent", H=130, Hkv=65, N=257), _fwd(_d, True, 0, 3, op="persistent", H=520, Hkv=260, N=300),
+        _fwd(_d, False, 0, 2 if _d == 64 else 3, op="persistent", H=5, N=300), _fwd(_d, True, 0, 2, op="persistent", H=5, N=300),
+        _fwd(_d, False, 0, 2, op="persistent", H=5, N=517), _fwd(_d, False, 0, 3, op="persistent", H=130, Hkv=65, N=257),
         _bwd(_d, False, 2, 2, H=6, Hkv=3, N=517), _bwd(_d, True, 2, 2, H=6, Hkv=2, N=517),
         _bwd(_d, False, 1, 2, H=140, Hkv=20, N=513), _bwd(_d, True, 1, 1, H=180, Hkv=90, N=300),
     ]
@@ -44,12 +45,23 @@ ATTENTION += [
 ATTENTION += [
     _fwd(128, False, 0, 1, op="fp8", H=4, Hkv=2, N=517), _fwd(128, True, 0, 1, op="fp8", H=4, Hkv=2, N=517),
     _fwd(128, True, 2, 1, op="fp8", H=800, Hkv=400, N=201), _fwd(128, False, 2, 1, op="fp8", H=800, Hkv=400, N=201),
-    # four tiles and more for each resident workgroup of the queue, three and more of the list
+    # four tiles and more for each resident workgroup of the queue
     _fwd(128, False, 1, 1, op="persistent", H=1000, Hkv=500, N=250), _fwd(128, True, 1, 1, op="persistent", H=800, Hkv=400, N=201),
-    _fwd(128, True, 2, 1, B=3, H=130, Hkv=65, N=430),
     (["attn_fwd_fp8_kernel<128, false>"], dict(op="fp8_variant", variant=3, H=4, Hkv=2, N=517, d=128, causal=False)),
     (["attn_fwd_fp8_kernel<128, true>"], dict(op="fp8_variant", variant=3, H=4, Hkv=2, N=517, d=128, causal=True)),
 ]
+
+
+# Workgroups that stay resident and take several tiles, by the list (three or more 256-row tiles for every CU; K/V heads a multiple of
+# eight and not) and from the queue (whole tiles and paired).  Lengths: an odd number of key tiles, enough of them for the
+# ring's unrolled loop, last query tiles of few rows.
+RESIDENT = []
+for _c in (False, True):
+    for _B, _H, _Hkv, _N in ((1, 256, 64, 700), (1, 300, 100, 700), (3, 24, 12, 2900)):
+        RESIDENT += [_fwd(128, _c, 2, 1, op="fp8", B=_B, H=_H, Hkv=_Hkv, N=_N)]
+        RESIDENT += [_fwd(_d, _c, 2, 1, op="fwd_variant", variant=4 if _d == 128 else 5, B=_B, H=_H, Hkv=_Hkv, N=_N) for _d in (64, 128)]
+    for _form, _B, _H, _Hkv, _N in ((1, 1, 64, 16, 4200), (1, 1, 40, 10, 4200), (1, 3, 16, 8, 4200), (3, 1, 300, 300, 270), (3, 5, 44, 11, 530)):
+        RESIDENT += [_fwd(_d, _c, 1, _form, op="persistent", B=_B, H=_H, Hkv=_Hkv, N=_N) for _d in (64, 128)]
 
 
 def _nn(kernel, M, N, K):

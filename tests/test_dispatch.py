@@ -26,7 +26,7 @@ def test_very_many_rows_are_launched():
 
 
 def test_every_row_of_the_kernel_cases_launches_the_kernel_it_names():
-    rows = kc.ATTENTION + kc.NN + kc.SPLITK
+    rows = kc.ATTENTION + kc.RESIDENT + kc.NN + kc.SPLITK
     got, _ = routes([c for _, c in rows])
     wrong = [(c, names, launches) for (names, c), (st, launches) in zip(rows, got) if st != 0 or [x[0] for x in launches] != names]
     assert not wrong, "\n".join(map(str, wrong))

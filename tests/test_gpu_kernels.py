@@ -206,3 +206,47 @@ def test_queue_launch_in_a_replayed_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(o.view(torch.int16), want.view(torch.int16)) and torch.equal(lse, want_lse), f"replay {rep}"
+
+
+def _one_tile_each(run, q, k, v, limit):
+    """run(q, k, v) on as many heads at a time as stay below `limit` 256-row tiles: one tile for every workgroup."""
+    B, H, N, _ = q.shape
+    G, T = H // k.shape[1], (N + 255) // 256
+    step = max(1, (limit - 1) // (T * G))
+    parts = [run(*(x[b:b + 1, i * g:(i + step) * g].contiguous() for x, g in ((q, G), (k, 1), (v, 1)))) for b in range(B) for i in range(0, k.shape[1], step)]
+    return [torch.cat([p[i].flatten(0, 1) for p in parts]).view(B, H, *parts[0][i].shape[2:]) for i in range(2)]
+
+
+@pytest.mark.parametrize("names,c", kc.RESIDENT, ids=[kc.case_id(r) for r in kc.RESIDENT])
+def test_resident_workgroups_give_the_bytes_of_single_tiles(names, c):
+    """Workgroups that take several tiles, one after the other: the same bytes as launches of one tile for every workgroup."""
+    import paper_2605_10905_amd as A
+
+    B, H, Hkv, N, d, causal, op = c.get("B", 1), c["H"], c["Hkv"], c["N"], c["d"], c["causal"], c["op"]
+    whole = next(v for v in range(A.attn_num_variants()) if A.attn_variant_name(v).startswith(f"bf16 d{d} whole tiles"))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(71 + N + d)
+    q, k, v = (torch.randn((B, h, N, d), generator=gen, device="cuda") for h in (H, Hkv, Hkv))
+    q, k, v = (x.to(torch.float8_e4m3fn).view(torch.uint8) if op == "fp8" else x.bfloat16() for x in (q, k, v))
+
+    def run(q, k, v, queue=None):
+        o = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+        lse = torch.full(q.shape[:3], float("nan"), device="cuda")
+        sizes = (q.shape[0], q.shape[1], k.shape[1], N, d, causal, d ** -0.5)
+        if op == "fp8":
+            A.attn_fwd_fp8(q, k, v, o, lse, *sizes, 1.0, 1.0, 1.0)
+        elif queue is not None:
+            A.attn_fwd_persistent(q, k, v, o, lse, *sizes, A.ATTN_BF16, queue)
+        else:
+            A.attn_fwd_variant(q, k, v, o, lse, *sizes, A.ATTN_BF16, whole)
+        torch.cuda.synchronize()
+        return o, lse
+
+    print(f"{c} launches {names}", flush=True)
+    queue = torch.full((A.attn_persistent_queue_bytes() // 4,), -77, dtype=torch.int32, device="cuda") if op == "persistent" else None
+    o, lse = run(q, k, v, queue)
+    if op == "persistent":
+        assert int(queue[::32].min()) >= 0 and int(queue[::32].sum()) >= A.attn_num_workgroups(B, H, N, 256)
+    want, want_lse = _one_tile_each(run, q, k, v, 768)
+    assert bool(torch.isfinite(want.float()).all()) and bool(torch.isfinite(want_lse).all())
+    assert torch.equal(o.view(torch.int16), want.view(torch.int16)) and torch.equal(lse, want_lse)
