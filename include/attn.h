@@ -126,6 +126,9 @@ int attn_persistent_queue_bytes(void);
  *                 caller; contents on entry are irrelevant, contents on return unspecified
  *   dtype         ATTN_BF16 only; d must be 128 or 64 (ATTN_ERR_UNSUPPORTED otherwise)
  *
+ * When causal, an infinite or NaN key or value j reaches dq of queries from 32 * (j / 32) on only (queries of its own 32-key
+ * block before j meet it with P = 0).
+ *
  * Deterministic (no atomics).  Two kernels are enqueued on `stream`; the call returns without
  * synchronising.  Returns an attn_status; argument checks run before anything is enqueued.
  */

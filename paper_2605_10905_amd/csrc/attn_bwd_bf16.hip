@@ -365,47 +365,55 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dq_kernel(const AttnBwdParams
     asm volatile("s_nop 1" : "+v"(pre[m]));
   }
 
+  // Tiles that hold a block of this wave's that one of its queries sees.  Behind them (one tile at most: no loads are left) the wave only
+  // keeps the barrier: a block none of its queries sees would add P = 0 times its keys and values, which is not zero where those are
+  // infinite or NaN.
+  const int last_block = (CAUSAL ? min(wq0 + 31, N - 1) : N - 1) >> 5;
+  const int mine = (last_block + 2 - kg) >> 1;
+  // tile j+1 has landed (the loads of tile j+2 stay in flight); every wave is done with tile j-1
+  auto between = [&](int j) __attribute__((always_inline)) {
+    if (KS == 2) __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's reads of tile j-1, whose slot is refilled, are done
+    if (j + 2 < nt) ATTN_WAIT_VMCNT(LPT);
+    else ATTN_WAIT_VMCNT(0);
+    attn_wg_barrier();
+  };
   // tile j lives in slot j % 4 = S
   auto tile = [&](auto S, int j) __attribute__((always_inline)) {
     constexpr int s = decltype(S)::value;
     constexpr int b0 = s * TILEB, b1 = b0 + SUBB, bn = ((s + 1) & 3) * TILEB;
     const bool load = j + 3 < nt;
-    // tile j+1 has landed (the loads of tile j+2 stay in flight); every wave is done with tile j-1
-    auto between = [&]() __attribute__((always_inline)) {
-      if (KS == 2) __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's reads of tile j-1, whose slot is refilled, are done
-      if (j + 2 < nt) ATTN_WAIT_VMCNT(LPT);
-      else ATTN_WAIT_VMCNT(0);
-      attn_wg_barrier();
-    };
     if constexpr (KS == 2) {
-      between();
+      between(j);
       if constexpr (s & 1) step(sb, sa, pb, pa, ic<b0>{}, ic<bn>{}, ic<(s + 3) & 3>{}, j * BN + kg * 32, load);
       else step(sa, sb, pa, pb, ic<b0>{}, ic<bn>{}, ic<(s + 3) & 3>{}, j * BN + kg * 32, load);
     } else {
       step(sa, sb, pa, pb, ic<b0>{}, ic<b1>{}, ic<-1>{}, j * BN, false);
-      between();
+      between(j);
       step(sb, sa, pb, pa, ic<b1>{}, ic<bn>{}, ic<(s + 3) & 3>{}, j * BN + 32, load);
     }
     if (load) issue_advance();
   };
   int j = 0;
-  for (; j + 4 <= nt; j += 4) {
+  for (; j + 4 <= mine; j += 4) {
     tile(ic<0>{}, j);
     tile(ic<1>{}, j + 1);
     tile(ic<2>{}, j + 2);
     tile(ic<3>{}, j + 3);
   }
-  if (j < nt) {
+  if (j < mine) {
     tile(ic<0>{}, j);
-    if (j + 1 < nt) {
+    if (j + 1 < mine) {
       tile(ic<1>{}, j + 1);
-      if (j + 2 < nt) tile(ic<2>{}, j + 2);
+      if (j + 2 < mine) tile(ic<2>{}, j + 2);
     }
   }
-  // the gradient products of the last block (its operands are already here)
-  if (KS == 2 && ((nt - 1) & 1) == 0) pb = pa;  // (the parity of the last step says which registers hold dS)
+  if (mine < nt) between(mine);
+  // the gradient products of the last block (its operands are already here), if that is a block the queries see
+  if (KS == 2 && ((mine - 1) & 1) == 0) pb = pa;  // (the parity of the last step says which registers hold dS)
+  if (KS == 2 || (last_block & 1)) {
 #pragma unroll
-  for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], pb.d, std::true_type{});
+    for (int i = 0; i < RA; ++i) grad_mfma(i, pre[i], pb.d, std::true_type{});
+  }
   grads_settled();
 
   if constexpr (KS == 1) {

@@ -195,3 +195,36 @@ def test_bwd_random_shapes(B, Hq, Hkv, N, causal, seed):
     print(f"bwd random B={B} Hq={Hq} Hkv={Hkv} N={N} causal={causal}", flush=True)
     dq, dk, dv, _, _ = gu.run_gpu_bwd(inp, dob)
     gu.check_bwd_full(inp, dob, dq, dk, dv, f"bwd random B={B} Hq={Hq} Hkv={Hkv} N={N} causal={causal}")
+
+
+# Rows that see no non-finite key: a key or value that is infinite or NaN may reach dQ of its own 32-key block's queries,
+# where P = 0 of hidden keys meets it, and of later ones, but not of earlier ones, in whichever workgroup they are.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,N", [(2, 300), (90, 513), (144, 201), (300, 97)])
+def test_dq_of_queries_before_non_finite_keys(H, N, d):
+    import paper_2605_10905_amd as A
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(61 + N + d)
+    q, k, v, do = (torch.randn((1, H, N, d), generator=gen, device="cuda").bfloat16() for _ in range(4))
+    o, lse = torch.empty_like(q), torch.empty((1, H, N), device="cuda")
+    ws = torch.empty(A.attn_bwd_workspace_bytes(1, H, N) // 4, device="cuda")
+    args = (1, H, H, N, d, True, d ** -0.5, A.ATTN_BF16)
+    A.attn_fwd(q, k, v, o, lse, *args)
+
+    def dq(k, v):
+        out = [torch.full_like(q, float("nan")) for _ in range(3)]
+        A.attn_bwd(q, k, v, o, do, lse, *out, ws, *args)
+        torch.cuda.synchronize()
+        return out[0]
+
+    want = dq(k, v)
+    assert bool(torch.isfinite(want.float()).all())
+    for first in sorted({32, 64, 96, 160, 192, (N - 1) // 32 * 32}):
+        for bad in (float("nan"), float("inf")):
+            for where in ("k", "v"):
+                print(f"dq before non-finite {where}: H={H} N={N} d={d} first={first} {bad}", flush=True)
+                x = (k if where == "k" else v).clone()
+                x[:, :, first:, ::3] = bad
+                got = dq(x if where == "k" else k, x if where == "v" else v)
+                assert torch.equal(got[:, :, :first].view(torch.int16), want[:, :, :first].view(torch.int16)), (first, bad, where)
