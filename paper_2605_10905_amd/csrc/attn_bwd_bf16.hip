@@ -918,15 +918,10 @@ int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
     constexpr int D = decltype(dtag)::value;
     constexpr bool CAUSAL = decltype(causal_tag)::value;
     const double blocks = (p.N + 31) / 32;  // 32-row blocks of a head
-    AttnBwdParams q = p;
     auto tiles = [&](int heads, int rows) { return (long long)p.B * heads * ((p.N + rows - 1) / rows); };
     const AttnSplitCost cost_q = D == 128 ? (CAUSAL ? AttnSplitCost{13.2, 14.5, 1.14, 0.46, 2.8} : AttnSplitCost{20.3, 18.6, 1.12, 0.63, 4.4})
                                           : (CAUSAL ? AttnSplitCost{6.5, 6.1, 0.3, 0.74, 2.7} : AttnSplitCost{6.9, 7.7, 1.03, 0.45, 4.5});
     const bool split_q = attn_split_pays(CAUSAL, tiles(p.Hq, 128), tiles(p.Hq, 64), (p.N + 63) / 64, blocks, cost_q);
-    q.T = split_q ? (p.N + 63) / 64 : (p.N + 127) / 128;
-    const dim3 grid_q(p.B * p.Hq * q.T);
-    if (split_q) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 2>), grid_q, dim3(256), 0, stream, q);
-    else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, CAUSAL, 1>), grid_q, dim3(256), 0, stream, q);
     const double steps_k = blocks * (p.Hq / p.Hkv);
     const long long whole_k = tiles(p.Hkv, 128);
     bool split_k;
@@ -937,16 +932,21 @@ int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
       // (two of the split form's workgroups fit a CU, one of the whole form's: only where those fill the CUs once is it ahead)
       split_k = whole_k <= 65536 && steps_k >= (CAUSAL ? 3 : 5) && !(whole_k > 224 && whole_k <= (CAUSAL ? 448 : 288));
     }
-    const dim3 grid_k(p.B * p.Hkv * (split_k ? (p.N + 63) / 64 : (p.N + 127) / 128));
-    if (split_k) hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 2>), grid_k, dim3(256), 0, stream, q);
-    else hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 1>), grid_k, dim3(256), 0, stream, q);
+    const int rows_q = split_q ? 64 : 128;
+    const long long grid_q = tiles(p.Hq, rows_q), grid_k = tiles(p.Hkv, split_k ? 64 : 128);
+    if (grid_q * 256 > 0xffffffffll || grid_k * 256 > 0xffffffffll) return -1;  // beyond what a launch holds
+    AttnBwdParams q = p;
+    q.T = (p.N + rows_q - 1) / rows_q;
+    const void* const dq = split_q ? (const void*)attn_bwd_dq_kernel<D, CAUSAL, 2> : (const void*)attn_bwd_dq_kernel<D, CAUSAL, 1>;
+    void* args[] = {&q};
+    if (hipLaunchKernel(dq, dim3((unsigned)grid_q), dim3(256), args, 0, stream) != hipSuccess) {
+      const int err = (int)hipGetLastError();
+      return err ? err : -1;  // (dK/dV would read rows that nothing has written)
+    }
+    if (split_k) hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 2>), dim3((unsigned)grid_k), dim3(256), 0, stream, q);
+    else hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<D, CAUSAL, 1>), dim3((unsigned)grid_k), dim3(256), 0, stream, q);
+    return (int)hipGetLastError();
   };
-  auto by_causal = [&](auto dtag) {
-    if (p.causal) launch(dtag, std::true_type{});
-    else launch(dtag, std::false_type{});
-  };
-  if (d == 128) by_causal(ic<128>{});
-  else if (d == 64) by_causal(ic<64>{});
-  else return -1;
-  return (int)hipGetLastError();
+  auto by_causal = [&](auto dtag) { return p.causal ? launch(dtag, std::true_type{}) : launch(dtag, std::false_type{}); };
+  return d == 128 ? by_causal(ic<128>{}) : d == 64 ? by_causal(ic<64>{}) : -1;
 }

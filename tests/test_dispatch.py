@@ -58,6 +58,18 @@ def _form_calls():
     return calls
 
 
+def test_a_backward_too_large_for_a_launch_launches_nothing():
+    """The dQ grid counts workgroups of 128 query rows, so that heads of 129 have two: what does not fit is refused before anything is enqueued."""
+    calls = [dict(op=op, H=H, Hkv=Hkv, N=N, d=d) for op, H, Hkv, N, d in (("bwd", 2 ** 30 + 8, 1, 129, 64), ("bwd", 2 ** 24, 1, 128, 64), ("bwd", 2 ** 24, 2 ** 24, 128, 128),
+                                                                         ("bwd", 2 ** 23, 2 ** 23, 256, 128), ("bwd", 2 ** 31 - 1, 1, 1, 64))]
+    fits = [dict(op="bwd", H=2 ** 23 - 8, Hkv=8, N=N, d=d, causal=c) for N in (1, 128, 129, 256) for d in (64, 128) for c in (False, True)]
+    got, _ = routes(calls + fits)
+    for c, (st, launches) in zip(calls, got):
+        assert st != 0 and not launches, (c, st, launches)
+    for c, (st, launches) in zip(fits, got[len(calls):]):
+        assert st == 0 and len(launches) == 2, (c, st, launches)
+
+
 def test_every_kernel_is_launched_by_a_case_that_a_gpu_test_runs():
     """The rows of kernel_cases.py, and every variant of gemm_bf16_nt_variant, which the GEMM's tests run one by one."""
     got, kernels = routes([c for _, c in kc.ATTENTION + kc.NN + kc.SPLITK] + _variant_calls())
