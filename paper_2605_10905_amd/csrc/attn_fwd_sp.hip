@@ -665,10 +665,16 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
     hand_on();
   };
   if constexpr (FORM != kWhole) {
-    // (from the queue: next_tile_index() holds the barrier behind which no wave reads the finished tile's ring; nothing of the next tile
-    // is requested before it, the workgroups beside this one fill the seam)
-    for (int wg = MODE == 1 ? next_tile_index() : (int)blockIdx.x; wg >= 0; wg = MODE == 1 ? next_tile_index() : -1) {
-      set_tile(wg);
+    for (;;) {
+      if constexpr (MODE == 1) {
+        // (holds the barrier behind which no wave reads the finished tile's ring; nothing of the next tile is requested before it, the
+        // workgroups beside this one fill the seam)
+        const int wg = next_tile_index();
+        if (wg < 0) return;
+        set_tile(wg);
+      } else {
+        set_tile((int)blockIdx.x);
+      }
       if constexpr (FORM == kPair) {
         const char* src = qhead + (size_t)min(qrow, N - 1) * INB + h * 16;
 #pragma unroll
@@ -761,7 +767,8 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
           if (h == 0) p.lse[row] = (m_ref + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
           attn_store_packed_o<NCB>(out, (char*)p.o + row * ROWB + h * 16);
         }
-        continue;
+        if constexpr (MODE == 1) continue;
+        else return;
       }
       // ---- merge: each of the two waves gives away the columns the other one finishes ------------------
       float l = attn_sum_halves(l_run);
@@ -816,8 +823,8 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
         if (kg == 0 && h == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f;
         attn_store_packed_o<NH>(out, (char*)p.o + row * ROWB + kg * NH * 64 + h * 16);
       }
+      return;
     }
-    return;
   }
 
   // ---- the tiles of this workgroup -----------------------------------------------------------------
