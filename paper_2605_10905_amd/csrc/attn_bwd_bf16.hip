@@ -446,6 +446,190 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dq_kernel(const AttnBwdParams
   }
 }
 
+// The same in workgroups of 256 queries: eight waves, two per SIMD, that work block by block without the pipeline.  K and V
+// are read half as often, and launches of few short tiles take half the rounds over the CUs.
+template <int D_>
+struct DqWide {
+  static constexpr int D = D_, BN = 64, NWAVES = 8, BM = NWAVES * 32, NT = NWAVES * 64;
+  static constexpr int NKK = D / 16, NCB = D / 32, ROWB = D * 2, NCH = ROWB / 16;
+  static constexpr int TILEB = BN * ROWB, SUBB = 32 * ROWB, NSLOT = 3;
+  static constexpr int T2BASE = NSLOT * TILEB;  // V's slots
+  static constexpr int NLD = BN * NCH / NT;
+};
+
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(512, 2) attn_bwd_dq_wide_kernel(const AttnBwdParams p) {
+  using C = DqWide<D>;
+  constexpr int NKK = C::NKK, NCB = C::NCB, ROWB = C::ROWB, NCH = C::NCH, TILEB = C::TILEB, SUBB = C::SUBB, NSLOT = C::NSLOT;
+  constexpr int NLD = C::NLD, NT = C::NT, BN = C::BN, BM = C::BM;
+
+  __shared__ __attribute__((aligned(1024))) char smem_raw[2 * NSLOT * TILEB];
+  LDS_AS char* const smem = (LDS_AS char*)smem_raw;
+
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int qi = lane & 31, h = lane >> 5;
+
+  const AttnTileCoord tc = attn_tile_coord_impl(blockIdx.x, p.B, p.Hq, p.Hkv, p.T, CAUSAL ? 1 : 0);
+  const int N = p.N;
+  const int hk = tc.hq / (p.Hq / p.Hkv);
+  const int q0 = tc.t * BM;
+  const int wq0 = q0 + w * 32;
+  const bool wave_valid = wq0 < N;
+  const int qrow = wq0 + qi;
+
+  const size_t qoff = ((size_t)(tc.b * p.Hq + tc.hq) * N) * ROWB;
+  const char* const khead = (const char*)p.k + ((size_t)(tc.b * p.Hkv + hk) * N) * ROWB;
+  const char* const vhead = (const char*)p.v + ((size_t)(tc.b * p.Hkv + hk) * N) * ROWB;
+
+  const int kv_end = CAUSAL ? min(N, q0 + BM) : N;
+  const int nt = (kv_end + BN - 1) / BN;
+
+  // ---- producer role ------------------------------------------------------------------------------
+  int ld_row[NLD];
+  uint32_t ld_off[NLD];
+#pragma unroll
+  for (int it = 0; it < NLD; ++it) {
+    const int s = it * NT + tid;
+    const int r = s / NCH, c = s % NCH;
+    ld_row[it] = r;
+    ld_off[it] = r * ROWB + ((c ^ swz_rt<ROWB>(r)) << 4);
+  }
+  const uint32_t lds_wave = (uint32_t)(uintptr_t)smem + w * 1024;
+  auto issue_tile = [&](int j, int slot) __attribute__((always_inline)) {
+    const char* const kb = khead + (size_t)j * TILEB;
+    const char* const vb = vhead + (size_t)j * TILEB;
+#pragma unroll
+    for (int it = 0; it < NLD; ++it) {
+      const uint32_t over = (uint32_t)max(0, j * BN + ld_row[it] - (N - 1)) * ROWB;  // rows past N-1 re-read row N-1
+      attn_lds_dma16(kb, ld_off[it] - over, lds_wave + slot * TILEB + it * NT * 16);
+      attn_lds_dma16(vb, ld_off[it] - over, lds_wave + C::T2BASE + slot * TILEB + it * NT * 16);
+    }
+  };
+  issue_tile(0, 0);
+
+  // ---- stationary operands: Q and dO rows of this lane's query; delta from dO and O ---------------
+  bf16x8 qf[NKK], dof[NKK];
+  float delta;
+  {
+    const int row = min(qrow, N - 1);
+    const char* qs = (const char*)p.q + qoff + (size_t)row * ROWB + h * 16;
+    const char* ds = (const char*)p.dout + qoff + (size_t)row * ROWB + h * 16;
+    const char* os = (const char*)p.o + qoff + (size_t)row * ROWB + h * 16;
+    float acc = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      qf[kk] = *(const bf16x8*)(qs + kk * 32);
+      dof[kk] = *(const bf16x8*)(ds + kk * 32);
+      const bf16x8 ov = *(const bf16x8*)(os + kk * 32);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc += (float)dof[kk][e] * (float)ov[e];
+    }
+    delta = attn_sum_halves(acc);
+  }
+  const float lse2 = p.lse[(size_t)(tc.b * p.Hq + tc.hq) * N + min(qrow, N - 1)] * kLog2e;
+  if (h == 0 && qrow < p.Npad) {
+    float* const wsrow = p.ws + (size_t)(tc.b * p.Hq + tc.hq) * 2 * p.Npad;
+    wsrow[qrow] = qrow < N ? lse2 : INFINITY;
+    wsrow[p.Npad + qrow] = qrow < N ? -delta : 0.f;
+  }
+  if (nt > 1) issue_tile(1, 1);
+
+  // ---- LDS read addresses (slot 0, first 32-row block) --------------------------------------------
+  uint32_t raddr[NKK];  // row-wise operand: row qi, chunk 2kk + h
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) raddr[kk] = qi * ROWB + (((2 * kk + h) ^ swz_rt<ROWB>(qi)) << 4);
+  uint32_t taddr[NCB][2];  // transposed operand through the transposing load
+  {
+    const int s = lane & 15, chalf = (lane >> 4) & 1;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int key = 8 * e + 4 * h + (s >> 2);
+        const int chunk = cb * 4 + chalf * 2 + ((s & 3) >> 1);
+        taddr[cb][e] = key * ROWB + ((chunk ^ swz_rt<ROWB>(key)) << 4) + ((s & 1) << 3);
+      }
+  }
+  auto row_operand = [&](int base, int kk) __attribute__((always_inline)) { return *(LDS_AS bf16x8*)(smem + raddr[kk] + base); };
+  auto tr_operand = [&](int base, int cb, int kc) __attribute__((always_inline)) {
+    const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(smem + taddr[cb][0] + base + kc * 16 * ROWB));
+    const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(smem + taddr[cb][1] + base + kc * 16 * ROWB));
+    s16x8 av;
+    av[0] = v0[0]; av[1] = v0[1]; av[2] = v0[2]; av[3] = v0[3];
+    av[4] = v1[0]; av[5] = v1[1]; av[6] = v1[2]; av[7] = v1[3];
+    return __builtin_bit_cast(bf16x8, av);
+  };
+
+  f32x16 acc[NCB];  // dQ^T
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
+  const float c = p.scale_log2;
+  const int limit = CAUSAL ? min(qrow, N - 1) : (N - 1);
+  const int wlast = wq0 + 31;
+
+  // one 32-key block: `base` = byte offset of the block inside the K slots (V: + T2BASE)
+  auto block = [&](int key0, int base) __attribute__((always_inline)) {
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(base, kk), qf[kk], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_operand(base + C::T2BASE, kk), dof[kk], dp, 0, 0, 0);
+    }
+    // invisible keys (causal diagonal, ragged tail): a score of -inf gives P = 0 and dS = 0.  The
+    // compare / select work sits behind a wave-uniform branch, the common case carries none of it.
+    if ((CAUSAL && key0 + 31 > wq0) || key0 + 31 >= N) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (key0 + 4 * h + 8 * (r >> 2) + (r & 3) > limit) s[r] = -INFINITY;
+    }
+    u32x4 dsk[2];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      float e[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int r = 2 * u + t;
+        const float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -lse2));
+        e[t] = pr * (dp[r] - delta);
+      }
+      dsk[u >> 2][u & 3] = pack_bf16(e[0], e[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * NCB; ++i) {
+      const int cb = i % NCB, kc = i / NCB;
+      acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_operand(base, cb, kc), __builtin_bit_cast(bf16x8, dsk[kc]), acc[cb], 0, 0, 0);
+    }
+  };
+
+  if (nt > 1) ATTN_WAIT_VMCNT(2 * NLD);
+  else ATTN_WAIT_VMCNT(0);
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) asm volatile("" ::"v"(qf[kk]), "v"(dof[kk]));  // stationary operands are in registers
+  attn_wg_barrier();
+
+  int slot = 0;
+  for (int j = 0; j < nt; ++j) {
+    const int pslot = slot == 0 ? NSLOT - 1 : slot - 1;  // slot of tile j+2 = slot of tile j-1
+    if (j + 2 < nt) issue_tile(j + 2, pslot);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int key0 = j * BN + i * 32;
+      if (wave_valid && key0 < kv_end && (!CAUSAL || key0 <= wlast)) block(key0, slot * TILEB + i * SUBB);
+    }
+    if (j + 2 < nt) ATTN_WAIT_VMCNT(2 * NLD);  // tile j+1 has landed; the loads of tile j+2 stay in flight
+    else ATTN_WAIT_VMCNT(0);
+    attn_wg_barrier();
+    slot = slot == NSLOT - 1 ? 0 : slot + 1;
+  }
+
+  store_transposed<NCB>(acc, p.scale, (char*)p.dq + qoff + (size_t)min(qrow, N - 1) * ROWB, h, qrow < N);
+}
+
 // =====================================================================================================
 // dK and dV in one kernel (S and dP computed once for both).  The accumulators of both gradients
 // (128 registers per 32 keys) beside the stationary K and V rows (64) leave no room for two waves
@@ -905,11 +1089,16 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
 
 }  // namespace
 
-// Both kernels split where the launch has few tiles; d = 64 dK/dV nearly always.  Whole backward passes in which only that
-// kernel changes, us, unsplit -> split, heads x N (both forms of 1380 random shapes were timed, N 60 .. 6000, up to 1600 tiles; the
-// choice is 0.1 % (d = 128) to 0.6 % (d = 64) slower than the faster form on average, and at worst 3 % and 8 %):
-//   dQ     d = 128  2 x 656 causal 41 -> 38; 20 x 3220 405 -> 381; 128 x 369 causal 52 -> 57; 64 x 2048 causal 260 -> 297
-//          d = 64   8 x 2919 causal 68 -> 59; 32 x 1000 40 -> 43; 64 x 8192 3532 -> 3669
+// The forms, and which of them a launch takes: for dQ the cheapest by what attn_equal_us (not causal) and attn_causal_us make of the
+// fitted costs below.  Whole backward passes in which only that kernel changes, us, heads x N (2953 random shapes, N 20 .. 6000, all forms of
+// each timed in turn):
+//   dQ, 128 / 64 / 256 rows: the wide form is ahead where it saves a round over the CUs or where K and V weigh more than the chain
+//     d = 128  144/36 x 146 46.0 / 42.4 / 38.0; 256/128 x 133 38.2 / 43.8 / 31.9; causal 20 x 3449 327 / 304 / 309; 60/30 x 2179 364 / 396 / 421;
+//              2 x 656 41 / 38 / 49
+//     d = 64   80 x 22 9.1 / 9.2 / 8.7; causal 512/128 x 132 34.1 / 38.9 / 30.7; 128/64 x 522 48.3 / 47.0 / 41.8; 384/192 x 23 13.4 / 13.4 / 14.2 (no fewer
+//              workgroups, and more than the CUs: not wide)
+//     the choice is 0.1 % slower than the fastest form on average, at worst 3 % (non-causal), 7 % (causal); without the wide form
+//     0.6 - 1.2 % and 21 %
 //   dK/dV  d = 128  12 x 1000 75 -> 67; 16 x 2048 140 -> 151; 64 x 2048 causal 260 -> 292; 256/32 x 4096 causal 3491 -> 3687
 //          d = 64   64 x 8192 3532 -> 3446, causal 1911 -> 1833; 256/32 x 4096 causal 1924 -> 1852; 96/12 x 413 causal 93 -> 76;
 //                   64 x 597 causal 31 -> 35
@@ -918,11 +1107,30 @@ int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
     constexpr int D = decltype(dtag)::value;
     constexpr bool CAUSAL = decltype(causal_tag)::value;
     const double blocks = (p.N + 31) / 32;  // 32-row blocks of a head
+    const int G = p.Hq / p.Hkv;
     auto tiles = [&](int heads, int rows) { return (long long)p.B * heads * ((p.N + rows - 1) / rows); };
-    const AttnSplitCost cost_q = D == 128 ? (CAUSAL ? AttnSplitCost{13.2, 14.5, 1.14, 0.46, 2.8} : AttnSplitCost{20.3, 18.6, 1.12, 0.63, 4.4})
-                                          : (CAUSAL ? AttnSplitCost{6.5, 6.1, 0.3, 0.74, 2.7} : AttnSplitCost{6.9, 7.7, 1.03, 0.45, 4.5});
-    const bool split_q = attn_split_pays(CAUSAL, tiles(p.Hq, 128), tiles(p.Hq, 64), (p.N + 63) / 64, blocks, cost_q);
-    const double steps_k = blocks * (p.Hq / p.Hkv);
+    // workgroups of `rows` queries / keys, of whose blocks a wave takes `part`
+    auto us_q = [&](const AttnFormCost& c, int rows, int slots, double part) {
+      const long long n = tiles(p.Hq, rows);
+      if (!CAUSAL) return attn_equal_us(c, n, slots, part * blocks);
+      const int T = (p.N + rows - 1) / rows;
+      const double tile = part * (rows / 32);
+      return attn_causal_us(c, attn_tile_map_make(p.B, p.Hq, p.Hkv, T, 1), n, slots, T * tile, tile, part * blocks);
+    };
+    // ---- dQ: workgroups of 128 queries, of 64 with split keys, or wide ones of 256
+    static constexpr AttnFormCost cost_q[2][2][3] = {  // [d = 128][causal][128, 64, 256 rows]
+        {{{-0.04, 1.84, 0.276, 0.250, 0.49}, {-0.80, 3.22, 0.229, 0.410, 0.61}, {0.53, 0.66, 0.605, 0.570, 0.42}},
+         {{0.22, 3.14, 0.177, 0.049, 0.0}, {0.16, 3.52, 0.117, 0.156, 0.0}, {-0.30, 3.23, 0.476, 0.000, 0.0}}},
+        {{{-0.01, 3.85, 0.517, 0.268, 1.04}, {0.02, 4.52, 0.685, 0.299, 1.32}, {0.08, 3.16, 1.056, 0.425, 0.96}},
+         {{-0.06, 5.50, 0.415, 0.246, 0.0}, {0.30, 5.69, 0.550, 0.359, 0.0}, {0.10, 4.83, 0.906, 0.445, 0.0}}}};
+    const AttnFormCost* const cq = cost_q[D == 128][CAUSAL];
+    constexpr int slots = D == 128 ? 1 : 2;
+    const double us_128 = us_q(cq[0], 128, slots, 1.0);
+    const double us_64 = tiles(p.Hq, 64) <= 131072 ? us_q(cq[1], 64, slots, 0.5) : INFINITY;
+    double us_256 = us_q(cq[2], 256, slots, 1.0);
+    if (D == 64 && CAUSAL && p.N <= 128 && tiles(p.Hq, 256) > 256) us_256 = INFINITY;
+    const int rows_q = us_256 < us_128 && us_256 < us_64 ? 256 : us_64 < us_128 ? 64 : 128;
+    const double steps_k = blocks * G;
     const long long whole_k = tiles(p.Hkv, 128);
     bool split_k;
     if constexpr (D == 128) {
@@ -932,14 +1140,16 @@ int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
       // (two of the split form's workgroups fit a CU, one of the whole form's: only where those fill the CUs once is it ahead)
       split_k = whole_k <= 65536 && steps_k >= (CAUSAL ? 3 : 5) && !(whole_k > 224 && whole_k <= (CAUSAL ? 448 : 288));
     }
-    const int rows_q = split_q ? 64 : 128;
     const long long grid_q = tiles(p.Hq, rows_q), grid_k = tiles(p.Hkv, split_k ? 64 : 128);
-    if (grid_q * 256 > 0xffffffffll || grid_k * 256 > 0xffffffffll) return -1;  // beyond what a launch holds
+    const int threads_q = rows_q == 256 ? 512 : 256;
+    if (grid_q * threads_q > 0xffffffffll || grid_k * 256 > 0xffffffffll) return -1;  // beyond what a launch holds
     AttnBwdParams q = p;
     q.T = (p.N + rows_q - 1) / rows_q;
-    const void* const dq = split_q ? (const void*)attn_bwd_dq_kernel<D, CAUSAL, 2> : (const void*)attn_bwd_dq_kernel<D, CAUSAL, 1>;
+    const void* const dq = rows_q == 256  ? (const void*)attn_bwd_dq_wide_kernel<D, CAUSAL>
+                           : rows_q == 64 ? (const void*)attn_bwd_dq_kernel<D, CAUSAL, 2>
+                                          : (const void*)attn_bwd_dq_kernel<D, CAUSAL, 1>;
     void* args[] = {&q};
-    if (hipLaunchKernel(dq, dim3((unsigned)grid_q), dim3(256), args, 0, stream) != hipSuccess) {
+    if (hipLaunchKernel(dq, dim3((unsigned)grid_q), dim3(threads_q), args, 0, stream) != hipSuccess) {
       const int err = (int)hipGetLastError();
       return err ? err : -1;  // (dK/dV would read rows that nothing has written)
     }

@@ -14,8 +14,10 @@ def _fwd(d, causal, mode, form, **size):
 
 
 def _bwd(d, causal, q, k, **size):
+    """q: 1 and 2 for dQ workgroups of 128 and 64 queries, "wide" for 256; k: 1 and 2 for dK/dV workgroups of 128 and 64 keys."""
     c = str(causal).lower()
-    return [f"attn_bwd_dq_kernel<{d}, {c}, {q}>", f"attn_bwd_dkv_pipe_kernel<{d}, {c}, {k}>"], dict(op="bwd", d=d, causal=causal, **size)
+    dq = f"attn_bwd_dq_wide_kernel<{d}, {c}>" if q == "wide" else f"attn_bwd_dq_kernel<{d}, {c}, {q}>"
+    return [dq, f"attn_bwd_dkv_pipe_kernel<{d}, {c}, {k}>"], dict(op="bwd", d=d, causal=causal, **size)
 
 
 ATTENTION = []
@@ -33,14 +35,15 @@ for _d in (64, 128):
         _fwd(_d, False, 1, 1, op="persistent", H=64, Hkv=32, N=600), _fwd(_d, True, 1, 1, op="persistent", H=70, Hkv=35, N=513),
         _fwd(_d, False, 0, 2 if _d == 64 else 3, op="persistent", H=5, N=300), _fwd(_d, True, 0, 2, op="persistent", H=5, N=300),
         _fwd(_d, False, 0, 2, op="persistent", H=5, N=517), _fwd(_d, False, 0, 3, op="persistent", H=130, Hkv=65, N=257),
-        _bwd(_d, False, 2, 2, H=6, Hkv=3, N=517), _bwd(_d, True, 2, 2, H=6, Hkv=2, N=517),
-        _bwd(_d, False, 1, 2, H=140, Hkv=20, N=513), _bwd(_d, True, 1, 1, H=180, Hkv=90, N=300),
+        _bwd(_d, False, 2, 2, H=6, Hkv=3, N=517), _bwd(_d, True, 2, 2, H=6, Hkv=2, N=517), _bwd(_d, False, 1, 2, H=140, Hkv=20, N=513),
     ]
-# backward, the dK/dV launches whose form depends on the head dimension
+# backward, the launches whose form depends on the head dimension
 ATTENTION += [
-    _bwd(128, False, 1, 1, H=70, N=513), _bwd(128, False, 1, 1, H=70, Hkv=35, N=513), _bwd(128, True, 1, 1, H=90, N=513), _bwd(128, True, 1, 2, H=90, Hkv=45, N=513),
-    _bwd(64, False, 1, 2, H=70, N=513), _bwd(64, False, 1, 2, H=70, Hkv=35, N=513), _bwd(64, True, 1, 2, H=90, N=513), _bwd(64, True, 1, 1, H=90, Hkv=45, N=513),
-    _bwd(64, False, 1, 1, H=46, N=513),
+    _bwd(128, False, "wide", 1, H=70, N=513), _bwd(128, False, "wide", 1, H=70, Hkv=35, N=513), _bwd(128, False, "wide", 2, H=144, Hkv=72, N=133), _bwd(128, False, 1, 1, H=90, N=513),
+    _bwd(128, True, 1, 1, H=90, N=513), _bwd(128, True, "wide", 1, H=180, Hkv=90, N=300), _bwd(128, True, 1, 2, H=90, Hkv=45, N=513), _bwd(128, True, "wide", 2, H=144, Hkv=72, N=133),
+    _bwd(64, False, 1, 2, H=70, N=513), _bwd(64, False, 1, 2, H=70, Hkv=35, N=513), _bwd(64, False, 1, 1, H=46, N=513), _bwd(64, False, "wide", 2, H=192, Hkv=48, N=162),
+    _bwd(64, False, "wide", 2, H=234, Hkv=117, N=390), _bwd(64, True, 1, 2, H=90, N=513), _bwd(64, True, "wide", 1, H=180, Hkv=90, N=300), _bwd(64, True, 1, 1, H=90, Hkv=45, N=513),
+    _bwd(64, True, "wide", 2, H=300, Hkv=75, N=133), _bwd(64, True, 1, 1, H=60, N=513),
 ]
 ATTENTION += [
     _fwd(128, False, 0, 1, op="fp8", H=4, Hkv=2, N=517), _fwd(128, True, 0, 1, op="fp8", H=4, Hkv=2, N=517),

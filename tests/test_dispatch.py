@@ -1,6 +1,7 @@
 """Routes of the public calls, without a GPU: which kernels a call launches, and that no size which fits a
 launch is refused."""
 import ctypes
+import heapq
 import math
 import os
 import random
@@ -124,6 +125,37 @@ def test_split_tile_map_is_a_bijection_and_keeps_an_xcd_on_few_slices(tmp_path, 
     assert seen == {(s, i, j) for s in range(splits) for i in range(tiles_m) for j in range(tiles_n)}
     share = -(-total // 8)  # entries of the list an XCD takes
     assert all(max(s) - min(s) + 1 == len(s) <= (share - 1 + tiles_m * tiles_n - 1) // (tiles_m * tiles_n) + 1 for s in slices.values())
+
+
+
+def test_causal_launch_model_against_a_plain_queue_of_workgroups(tmp_path):
+    """attn_causal_us, by which the causal forms are weighed, keeps places that come free at the same time together; here every
+    workgroup is handed out by itself, in the order that attn_tile_coord gives, to the place that is free first."""
+    (tmp_path / "hip").mkdir()
+    (tmp_path / "hip" / "hip_runtime.h").write_text("#pragma once\ntypedef void* hipStream_t;\n")
+    src, lib = tmp_path / "model.cpp", tmp_path / "model.so"
+    src.write_text('#define ATTN_HD\n#include "attn_kernels.h"\nextern "C" double model(int B, int Hq, int Hkv, int T, int slots, double P, double a, double b, double heaviest, double less, double top) {\n'
+                   "  return attn_causal_us(AttnFormCost{0.5, P, a, b, 0.0}, attn_tile_map_make(B, Hq, Hkv, T, 1), (long long)B * Hq * T, slots, heaviest, less, top);\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", str(tmp_path), "-I", os.path.join(ROOT, "paper_2605_10905_amd", "csrc"), str(src), "-o", str(lib)], check=True)
+    model = ctypes.CDLL(str(lib)).model
+    model.restype, model.argtypes = ctypes.c_double, [ctypes.c_int] * 5 + [ctypes.c_double] * 6
+    rng = random.Random(7)
+    b, hq, t = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    for _ in range(60):
+        B, Hkv, G, T, slots = rng.randint(1, 6), rng.choice((1, 3, 8, 12, 16)), rng.choice((1, 2, 4)), rng.randint(1, 12), rng.randint(1, 3)
+        n, P, a, share, less = B * Hkv * G * T, rng.uniform(2, 8), rng.uniform(0.2, 1), rng.uniform(0, 0.4), rng.choice((2.0, 4.0, 8.0))
+        heaviest = T * less - rng.choice((0.0, 1.0))
+        top = heaviest - rng.choice((0.0, 1.5))
+        step = a + share * (min(-(-n // 256), slots) - 1)
+        lists = 8 if B * Hkv % 8 == 0 else 1
+        places = [[0.0] * (256 * slots // lists) for _ in range(lists)]
+        for wg in range(n):
+            assert A.lib.attn_tile_coord(wg, B, Hkv * G, Hkv, T * 256, 256, 1, ctypes.byref(b), ctypes.byref(hq), ctypes.byref(t)) == 0
+            heapq.heapreplace(places[wg % lists], places[wg % lists][0] + P + min(heaviest - (T - 1 - t.value) * less, top) * step)
+        want = 0.5 + max(max(x) for x in places)
+        got = model(B, Hkv * G, Hkv, T, slots, P, a, share, heaviest, less, top)
+        assert abs(got - want) < 1e-6 * want, (B, Hkv, G, T, slots, got, want)
+    assert 0 < model(8, 64, 64, 1000, 2, 5.0, 0.5, 0.2, 1000.0, 1.0, 1000.0) < 1e6  # (more ranks than are followed)
 
 
 # Sizes at which a form of the bf16 forward was measured at least 4 % faster than another, us (w: whole tiles, s: split keys, p:
