@@ -1089,8 +1089,8 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
 
 }  // namespace
 
-// The forms, and which of them a launch takes: for dQ the cheapest by what attn_equal_us (not causal) and attn_causal_us make of the
-// fitted costs below.  Whole backward passes in which only that kernel changes, us, heads x N (2953 random shapes, N 20 .. 6000, all forms of
+// The forms, and which of them a launch takes: the cheapest by what attn_equal_us (not causal) and attn_causal_us make of the fitted
+// costs below.  Whole backward passes in which only that kernel changes, us, heads x N (2953 random shapes, N 20 .. 6000, all forms of
 // each timed in turn):
 //   dQ, 128 / 64 / 256 rows: the wide form is ahead where it saves a round over the CUs or where K and V weigh more than the chain
 //     d = 128  144/36 x 146 46.0 / 42.4 / 38.0; 256/128 x 133 38.2 / 43.8 / 31.9; causal 20 x 3449 327 / 304 / 309; 60/30 x 2179 364 / 396 / 421;
@@ -1099,9 +1099,10 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
 //              workgroups, and more than the CUs: not wide)
 //     the choice is 0.1 % slower than the fastest form on average, at worst 3 % (non-causal), 7 % (causal); without the wide form
 //     0.6 - 1.2 % and 21 %
-//   dK/dV  d = 128  12 x 1000 75 -> 67; 16 x 2048 140 -> 151; 64 x 2048 causal 260 -> 292; 256/32 x 4096 causal 3491 -> 3687
-//          d = 64   64 x 8192 3532 -> 3446, causal 1911 -> 1833; 256/32 x 4096 causal 1924 -> 1852; 96/12 x 413 causal 93 -> 76;
-//                   64 x 597 causal 31 -> 35
+//   dK/dV, 128 / 64 keys (at d = 64 two of the split form's workgroups share a CU, one of the whole form's)
+//     d = 128  12 x 1000 75 / 67; 16 x 2048 140 / 151; causal 64 x 2048 260 / 292; 60/30 x 2179 364 / 311; 256/32 x 4096 3491 / 3687
+//     d = 64   384/96 x 297 72.1 / 53.9; 36/18 x 1994 198 / 165; causal 24/12 x 2412 112 / 90; 36 x 925 37.1 / 45.6; 72 x 490 26.3 / 29.8; 1 x 59 9.8 / 10.2
+//     the choice is 0.1 % slower than the faster form on average, at worst 4 %
 int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
   auto launch = [&](auto dtag, auto causal_tag) {
     constexpr int D = decltype(dtag)::value;
@@ -1117,6 +1118,12 @@ int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
       const double tile = part * (rows / 32);
       return attn_causal_us(c, attn_tile_map_make(p.B, p.Hq, p.Hkv, T, 1), n, slots, T * tile, tile, part * blocks);
     };
+    auto us_k = [&](const AttnFormCost& c, int rows, int slots, double part) {
+      const long long n = tiles(p.Hkv, rows);
+      const double all = part * G * blocks;
+      if (!CAUSAL) return attn_equal_us(c, n, slots, all);
+      return attn_causal_us(c, attn_tile_map_make(p.B, p.Hkv, p.Hkv, (p.N + rows - 1) / rows, 1), n, slots, all, part * G * (rows / 32), all);
+    };
     // ---- dQ: workgroups of 128 queries, of 64 with split keys, or wide ones of 256
     static constexpr AttnFormCost cost_q[2][2][3] = {  // [d = 128][causal][128, 64, 256 rows]
         {{{-0.04, 1.84, 0.276, 0.250, 0.49}, {-0.80, 3.22, 0.229, 0.410, 0.61}, {0.53, 0.66, 0.605, 0.570, 0.42}},
@@ -1130,15 +1137,15 @@ int attn_bwd_launch_bf16(const AttnBwdParams& p, int d, hipStream_t stream) {
     double us_256 = us_q(cq[2], 256, slots, 1.0);
     if (D == 64 && CAUSAL && p.N <= 128 && tiles(p.Hq, 256) > 256) us_256 = INFINITY;
     const int rows_q = us_256 < us_128 && us_256 < us_64 ? 256 : us_64 < us_128 ? 64 : 128;
+    // ---- dK/dV: workgroups of 128 keys, or of 64 with split queries (which a head of two blocks or fewer gains nothing from)
+    bool split_k = false;
     const double steps_k = blocks * G;
-    const long long whole_k = tiles(p.Hkv, 128);
-    bool split_k;
-    if constexpr (D == 128) {
-      const AttnSplitCost cost_k = CAUSAL ? AttnSplitCost{6.5, 7.5, 0.88, 0.51, 4.0} : AttnSplitCost{10.3, 8.7, 1.09, 0.82, 4.0};
-      split_k = attn_split_pays(CAUSAL, whole_k, tiles(p.Hkv, 64), (p.N + 63) / 64, steps_k, cost_k);
-    } else {
-      // (two of the split form's workgroups fit a CU, one of the whole form's: only where those fill the CUs once is it ahead)
-      split_k = whole_k <= 65536 && steps_k >= (CAUSAL ? 3 : 5) && !(whole_k > 224 && whole_k <= (CAUSAL ? 448 : 288));
+    if (tiles(p.Hkv, 128) <= 65536 && (D == 64 || CAUSAL || steps_k >= 4.0) && !(CAUSAL && steps_k < 3.0 && G == 1)) {
+      static constexpr AttnFormCost cost_k[2][2][2] = {  // [d = 128][causal][128, 64 keys]
+          {{{-0.09, 2.99, 0.420, 0.162, 0.93}, {0.26, 3.38, 0.446, 0.348, 0.35}}, {{1.30, 5.24, 0.437, 0.159, 0.0}, {-1.52, 7.62, 0.477, 0.131, 0.0}}},
+          {{{-0.13, 4.19, 0.634, 0.288, 0.99}, {0.05, 5.11, 0.688, 0.292, 1.12}}, {{-0.17, 5.88, 0.618, 0.278, 0.0}, {0.02, 6.25, 0.697, 0.287, 0.0}}}};
+      const AttnFormCost* const ck = cost_k[D == 128][CAUSAL];
+      split_k = us_k(ck[1], 64, D == 64 ? 2 : 1, 0.5) < us_k(ck[0], 128, 1, 1.0);
     }
     const long long grid_q = tiles(p.Hq, rows_q), grid_k = tiles(p.Hkv, split_k ? 64 : 128);
     const int threads_q = rows_q == 256 ? 512 : 256;

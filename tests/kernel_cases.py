@@ -42,7 +42,7 @@ ATTENTION += [
     _bwd(128, False, "wide", 1, H=70, N=513), _bwd(128, False, "wide", 1, H=70, Hkv=35, N=513), _bwd(128, False, "wide", 2, H=144, Hkv=72, N=133), _bwd(128, False, 1, 1, H=90, N=513),
     _bwd(128, True, 1, 1, H=90, N=513), _bwd(128, True, "wide", 1, H=180, Hkv=90, N=300), _bwd(128, True, 1, 2, H=90, Hkv=45, N=513), _bwd(128, True, "wide", 2, H=144, Hkv=72, N=133),
     _bwd(64, False, 1, 2, H=70, N=513), _bwd(64, False, 1, 2, H=70, Hkv=35, N=513), _bwd(64, False, 1, 1, H=46, N=513), _bwd(64, False, "wide", 2, H=192, Hkv=48, N=162),
-    _bwd(64, False, "wide", 2, H=234, Hkv=117, N=390), _bwd(64, True, 1, 2, H=90, N=513), _bwd(64, True, "wide", 1, H=180, Hkv=90, N=300), _bwd(64, True, 1, 1, H=90, Hkv=45, N=513),
+    _bwd(64, False, "wide", 2, H=234, Hkv=117, N=390), _bwd(64, True, 1, 2, H=90, N=513), _bwd(64, True, "wide", 2, H=180, Hkv=90, N=300), _bwd(64, True, 1, 2, H=90, Hkv=45, N=513),
     _bwd(64, True, "wide", 2, H=300, Hkv=75, N=133), _bwd(64, True, 1, 1, H=60, N=513),
 ]
 ATTENTION += [

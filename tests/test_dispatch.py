@@ -191,3 +191,45 @@ def test_the_forward_takes_the_faster_form(op):
     got, _ = routes([dict(op=op, H=h, N=n, causal=c, d=d) for h, n, c, d, _ in _FORMS])
     wrong = [(f, launches) for f, (st, launches) in zip(_FORMS, got) if st != 0 or "wsp"[int(launches[-1][0][-2]) - 1] not in f[4]]
     assert not wrong, wrong
+
+
+# Backward passes in which only the form of dK/dV changes, us, keys 128 a workgroup -> 64 (heads, K/V heads, N, causal, d, 64 is right)
+_DKV = [(384, 96, 297, False, 64, True),     # 72.1 -> 53.9
+        (192, 96, 263, False, 64, True),     # 44.2 -> 34.2
+        (36, 18, 1994, False, 64, True),     # 198 -> 165
+        (120, 30, 1144, False, 64, True),    # 213 -> 179
+        (24, 12, 2412, True, 64, True),      # 112 -> 90
+        (384, 48, 547, True, 64, True),      # 123 -> 100
+        (36, 36, 925, True, 64, False),      # 37.1 -> 45.6
+        (72, 72, 490, True, 64, False),      # 26.3 -> 29.8
+        (1, 1, 59, True, 64, False),         # 9.8 -> 10.2
+        (60, 30, 2179, True, 128, True),     # 364 -> 311
+        (12, 12, 1000, False, 128, True),    # 75 -> 67
+        (16, 16, 2048, False, 128, False)]   # 140 -> 151
+
+
+def test_the_backward_takes_the_faster_form_of_dkv():
+    got, _ = routes([dict(op="bwd", H=h, Hkv=g, N=n, causal=c, d=d) for h, g, n, c, d, _ in _DKV])
+    wrong = [(r, launches) for r, (st, launches) in zip(_DKV, got) if st != 0 or (launches[1][0][-2] == "2") != r[5]]
+    assert not wrong, wrong
+
+
+# The same for dQ, 128 / 64 / 256 queries a workgroup (..., the forms within 4 % of the fastest)
+_DQ = [(256, 128, 133, False, 128, "w"),     # 38.2 / 43.8 / 31.9
+       (144, 36, 146, False, 128, "w"),      # 46.0 / 42.4 / 38.0
+       (160, 160, 152, True, 128, "w"),      # 31.9 / 31.3 / 27.9
+       (60, 30, 2179, True, 128, "1"),       # 364 / 396 / 421
+       (20, 20, 3449, True, 128, "2w"),      # 327 / 304 / 309
+       (80, 80, 22, False, 64, "w"),         # 9.1 / 9.2 / 8.7
+       (320, 160, 130, False, 64, "w"),      # 35.9 / 35.5 / 32.5
+       (512, 128, 132, True, 64, "w"),       # 34.1 / 38.9 / 30.7
+       (128, 64, 522, True, 64, "w"),        # 48.3 / 47.0 / 41.8
+       (384, 192, 23, True, 64, "12"),       # 13.4 / 13.4 / 14.2
+       (2, 2, 656, True, 128, "2")]          # 41 / 38 / 49
+
+
+def test_the_backward_takes_the_faster_form_of_dq():
+    got, _ = routes([dict(op="bwd", H=h, Hkv=g, N=n, causal=c, d=d) for h, g, n, c, d, _ in _DQ])
+    form = [("w" if "wide" in launches[0][0] else launches[0][0][-2]) for _, launches in got]
+    wrong = [(r, f) for r, f in zip(_DQ, form) if f not in r[5]]
+    assert not wrong, wrong
