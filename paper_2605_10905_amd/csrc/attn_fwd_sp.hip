@@ -1009,12 +1009,14 @@ double form_us(const FormCost& c, bool causal, double n, int slots, double longe
 }
 
 // Paired workgroups (kPair) against the form that the launch would take otherwise.  The numbers are fits to 1609 random launches (heads
-// 1 .. 2000, N 60 .. 5000), all forms of each timed: on average over them the choice is 2 - 7 % faster than the choice without
-// this form, in 1 % of them slower, at worst by 6 %.  It pays where the launch has more tiles than CUs and short to middling
+// 1 .. 2000, N 60 .. 5000), all forms of each timed.  Over 5616 other launches (N from 20) the choice is 4 - 5 % faster than the choice without this
+// form, causal at d = 128 2.4 %; 7 of them are more than 3 % slower, at worst 9 % (1792/224 causal heads x 245), and up to 2.4 % more could
+// be had.  It pays where the launch has more tiles than CUs and short to middling
 // chains, whose first loads, first block and stores then run beside another workgroup's steps; us, otherwise -> paired:
 // d = 64 causal 192 heads x 327 16.0 -> 10.9, 512 x 903 110 -> 86; few tiles (32 heads x 1000, keys split) 13.6 -> 15.6;
 // d = 128 384 x 400 47.2 -> 48.9, 96 x 1962 causal 105.1 -> 110.7, and long launches
-// up to 8 % slower (every workgroup reads K and V for 128 queries instead of 256): those keep their form.
+// up to 8 % slower (every workgroup reads K and V for 128 queries instead of 256): those keep their form, as do causal launches like
+// 128/64 x 568 25.6 -> 29.8, d = 64 72/36 x 1050 24.1 -> 28.0.
 bool pair_pays(const AttnParams& p, int d, bool split) {
   static const FormCost cost[2][2][3] = {  // [d = 128][causal][whole, split, paired]
       {{{0.98, 3.44, 0.469, 0.100, 1.00}, {0.85, 4.00, 0.496, 0.300, 1.00}, {0.67, 3.89, 0.319, 0.220, 0.24}},
@@ -1030,8 +1032,11 @@ bool pair_pays(const AttnParams& p, int d, bool split) {
   };
   const double n = heads * ((p.N + 127) / 128);
   if (n > (1 << 22) || (p.causal && n <= 256.0) || steps > (d == 64 ? 128 : 64)) return false;
-  const double other = split ? us(c[1], 128, 1, 0.5) : us(c[0], 256, 1, 1.0);
-  return us(c[2], 128, d == 64 ? kPairSlots<64> : kPairSlots<128>, 1.0) < (!p.causal ? 0.97 : d == 64 ? 0.94 : 0.95) * other;
+  const double other = split ? us(c[1], 128, 1, 0.5) : us(c[0], 256, 1, 1.0), whole = heads * ((p.N + 255) / 256);
+  // (a causal launch of 1.35 - 2 rounds of whole tiles is better than the model says: the light tiles of the second round
+  // fill up behind the heavy ones of the first)
+  const double margin = !p.causal ? 0.97 : whole > 345.0 && whole <= 512.0 ? 0.90 : d == 64 ? 0.94 : 0.95;
+  return us(c[2], 128, d == 64 ? kPairSlots<64> : kPairSlots<128>, 1.0) < margin * other;
 }
 
 // the launch in tiles of 128 queries

@@ -182,6 +182,8 @@ _FORMS = [(32, 1000, False, 128, "s"),    # w 25.8, s 20.3
           (34, 2048, False, 64, "sp"), (24, 2048, False, 64, "w"), (128, 2048, False, 64, "wp"),
           (192, 327, True, 64, "p"),      # w 16.0, s 18.3, p 10.9
           (512, 903, True, 64, "p"),      # w 109.7, s 130.2, p 86.1
+          (128, 568, True, 128, "w"),     # w 25.6, s 33.4, p 29.8
+          (72, 1050, True, 64, "w"),      # w 24.1, s 32.4, p 28.0
           (64, 8192, True, 128, "w"),     # w 905, s 1017, p 981
           (64, 8192, False, 128, "w")]    # w 1750, s 1913, p 1864
 
