@@ -975,9 +975,40 @@ int resident_workgroups() {
 
 // Launches with at least three tiles per CU walk static tile lists (mode 2): the seams
 // between a workgroup's tiles hide part of what a workgroup pays per tile outside its main loop
-// (measured: causal +0.5 .. +4.5 %; with two tiles per CU the plain launch is 1 % faster; non-causal, 81 launches of three tiles per CU
-// and more, d = 64 and 128: 0.92 - 0.95 of the plain launch's time on average, at worst 1.04; fp8, us: 512 heads x 513 90.7 -> 82.0,
-// 768 x 257 58.7 -> 51.8, 192 x 1500 184 -> 175, 64 x 8192 1380 / 1378).
+// (measured: causal +0.5 .. +4.5 %; with two tiles per CU the plain launch is 1 % faster; non-causal 0.93 - 0.97 of the plain launch's time on
+// average, fp8, us: 512 heads x 513 90.7 -> 82.0, 768 x 257 58.7 -> 51.8, 192 x 1500 184 -> 175, 64 x 8192 1380 / 1378).
+// A non-causal list is dealt as if its tiles were equal, but a ragged head's last tile is light (its waves past the end do nothing), which
+// tiles handed out one by one level out.  Up to eight rounds, beyond which that drowns, both are followed on the host (1 - 6 us; a light tile
+// takes 0.35, and 0.65 of the waves it uses), and lists are walked if they end earlier with the 5 % that their seams save.  us, lists / one by
+// one: 160 heads x 1138 128.1 / 119.0, 60 x 3080 at d = 64 192.9 / 180.3, fp8 72 x 2620 222.5 / 204.7, 160 x 1130 104.9 / 93.0.  Over 429 launches
+// this is 0.2 % slower than the faster way on average, at worst 6 %, where lists always are 0.5 % and 9 %, never 3.5 % and 29 %.
+bool lists_pay(const AttnParams& p, int tiles, int resident) {
+  if (tiles < 3 * resident) return false;
+  const int waves = (p.N - 1) % 256 / 32 + 1;  // of a head's last tile
+  if (p.causal || waves == 8 || tiles > 8 * resident || resident > 256) return true;
+  const double weight[2] = {1.0, 0.35 + 0.65 * waves / 8.0};
+  const int lists = p.map.lists, per = resident / lists, n = tiles / lists, full = p.map.G * (p.map.T - 1);
+  double dealt[256] = {}, free_at[2][256];  // per workgroup; when the workgroups that run a full / a light tile come free, in order
+  int first[2] = {0, 0}, count[2] = {per, 0};
+  for (int s = 0; s < per; ++s) free_at[0][s] = 0.0;
+  double most_dealt = 0.0, most = 0.0;
+  for (int rank = 0, inner = 0, s = 0, down = 0; rank < n; ++rank) {
+    const int light = inner >= full;
+    if (++inner == p.map.W) inner = 0;
+    dealt[s] += weight[light];
+    if (dealt[s] > most_dealt) most_dealt = dealt[s];
+    if (down ? s == 0 : s == per - 1) down ^= 1;
+    else s += down ? -1 : 1;
+    const int from = count[1] && (!count[0] || free_at[1][first[1]] < free_at[0][first[0]]);
+    const double end = free_at[from][first[from]] + weight[light];
+    first[from] = (first[from] + 1) & 255;
+    --count[from];
+    free_at[light][(first[light] + count[light]++) & 255] = end;
+    if (end > most) most = end;
+  }
+  return 0.95 * most_dealt < most;
+}
+
 // bf16 launches of few tiles (`tiles` of 256 queries) split the keys (KS = 2); the plain and the queue
 // launch follow the same rule, so that both give the same bytes.  us, whole tiles -> split keys, d = 128, heads x N:
 //   non-causal  32 x 1000 25.8 -> 20.3; 16 x 2048 42.0 -> 34.2; 34 x 2048 100.4 -> 92.0; 22 x 4096 186.1 -> 172.7;
@@ -1060,7 +1091,7 @@ int launch_128(const AttnParams& p, int, hipStream_t stream) {
 template <int D, bool FP8>
 int launch_whole(const AttnParams& p, int grid, hipStream_t stream) {
   const int resident = resident_workgroups();
-  if (resident >= 8 && grid >= 3 * resident) {
+  if (resident >= 8 && lists_pay(p, grid, resident)) {
     AttnParams q = p;
     q.total = grid;
     if (p.causal) hipLaunchKernelGGL((attn_fwd_sp_kernel<D, true, 2, FP8>), dim3(resident), dim3(512), 0, stream, q);

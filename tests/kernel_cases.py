@@ -48,6 +48,8 @@ ATTENTION += [
 ATTENTION += [
     _fwd(128, False, 0, 1, op="fp8", H=4, Hkv=2, N=517), _fwd(128, True, 0, 1, op="fp8", H=4, Hkv=2, N=517),
     _fwd(128, True, 2, 1, op="fp8", H=800, Hkv=400, N=201), _fwd(128, False, 2, 1, op="fp8", H=800, Hkv=400, N=201),
+    # more than three rounds of tiles, a fifth of them light: non-causal lists would be dealt unevenly
+    _fwd(128, False, 0, 1, op="fp8", B=5, H=32, Hkv=16, N=1130),
     # four tiles and more for each resident workgroup of the queue
     _fwd(128, False, 1, 1, op="persistent", H=1000, Hkv=500, N=250), _fwd(128, True, 1, 1, op="persistent", H=800, Hkv=400, N=201),
     (["attn_fwd_fp8_kernel<128, false>"], dict(op="fp8_variant", variant=3, H=4, Hkv=2, N=517, d=128, causal=False)),

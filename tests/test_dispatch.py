@@ -195,6 +195,25 @@ def test_the_forward_takes_the_faster_form(op):
     assert not wrong, wrong
 
 
+# Non-causal launches of three and more 256-row tiles per CU, us, lists / one tile per workgroup (heads, K/V heads, N, d or "fp8", lists are right)
+_LISTS = [(160, 160, 1138, 128, False),      # 128.1 / 119.0: 3.1 rounds, a fifth of the tiles light
+          (60, 15, 3080, 64, False),         # 192.9 / 180.3
+          (384, 48, 577, 128, False),        # 92.2 / 87.0
+          (72, 36, 2620, "fp8", False),      # 222.5 / 204.7
+          (160, 80, 1130, "fp8", False),     # 104.9 / 93.0
+          (512, 512, 513, "fp8", True),      # 82.0 / 90.7
+          (768, 768, 257, "fp8", True),      # 51.8 / 58.7
+          (192, 192, 1500, "fp8", True),     # 175 / 184
+          (64, 64, 8192, 128, True)]         # no light tiles
+
+
+def test_lists_of_uneven_tiles_are_not_walked():
+    call = lambda h, g, n, d: dict(op="fp8", H=h, Hkv=g, N=n) if d == "fp8" else dict(op="fwd_variant", variant=4 if d == 128 else 5, H=h, Hkv=g, N=n, d=d)
+    got, _ = routes([call(h, g, n, d) for h, g, n, d, _ in _LISTS])
+    wrong = [(r, launches) for r, (st, launches) in zip(_LISTS, got) if st != 0 or (", 2, " in launches[0][0]) != r[4]]
+    assert not wrong, wrong
+
+
 # Backward passes in which only the form of dK/dV changes, us, keys 128 a workgroup -> 64 (heads, K/V heads, N, causal, d, 64 is right)
 _DKV = [(384, 96, 297, False, 64, True),     # 72.1 -> 53.9
         (192, 96, 263, False, 64, True),     # 44.2 -> 34.2
