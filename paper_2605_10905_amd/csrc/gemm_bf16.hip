@@ -426,9 +426,8 @@ __global__ void __launch_bounds__(256, 1) gemm_bf16_nt_m16_kernel(const GemmPara
   // into the XCD's L2, not for what comes from memory.  So the workgroups that share a panel fetch it into the L2 four stages
   // ahead between them: per stage one load of one line per lane and wave (waves 0, 1 half of the A panel's rows, waves 2, 3 of
   // B's, which half by the tile's place; written into LDS that the ring leaves over and never read).  It goes out
-  // behind the stage's own loads, so that a wait for those leaves it in flight.  Split-K always; otherwise by
-  // launch_m16_by_size.  Measured, without -> with, buffers changing from call to call: split-K 2304 x 1024 x 65536
-  // 298 -> 258 us, x 65600 262 -> 244, 3000 x 1000 x 20480 122 -> 116.
+  // behind the stage's own loads, so that a wait for those leaves it in flight.  Where: see the launches.  Measured, without -> with,
+  // buffers changing from call to call: split-K 2304 x 1024 x 65536 298 -> 258 us, x 65600 262 -> 244, 3000 x 1000 x 20480 122 -> 116.
   constexpr int DIST = 4;
   static_assert(!AHEAD || (NSTAGE == 2 && C::LDS_BYTES >= NSTAGE * STAGEB + 4096), "room for what is fetched ahead");
   const char* const pf_tile = w < 2 ? a_tile : b_tile;
@@ -606,6 +605,9 @@ int launch_m16(const GemmParams& p, hipStream_t stream) {
 // 4000 x 4000 x 9984 237 -> 231, 4096 x 4096 x 16384 413 -> 399, 8192 x 8192 x 16384 1634 -> 1610, 4096 x 4096 x 65536 1882 -> 1582,
 // 1000 x 15000 x 16384 405 -> 392; 512 x 30000 x 16384 (two tile rows) 403 -> 421, 8192 x 8192 x 4096 370 -> 385,
 // 3000 x 30000 x 2752 393 -> 400.  (One kernel with a branch instead: 0.5 % slower on the launches that do not fetch ahead.)
+// What it gives depends on where the operands are.  Either side of the line, from memory / from the memory-side cache: 1003 x 2609 x 7552
+// 163 -> 147 / 131 -> 132, 6197 x 4606 x 7936 377 -> 349 / 332 -> 351, 1439 x 1708 x 8192 171 -> 149 / 140 -> 142, 6108 x 4303 x 8192 361 -> 348 /
+// 329 -> 338, 7714 x 4385 x 8640 525 -> 522 / 510 -> 519.  So for operands from memory the line could lie lower (1585 x 1960 x 4096 88 -> 78 / 74 -> 75).
 int launch_m16_by_size(const GemmParams& p, hipStream_t stream) {
   return p.K >= 8192 && p.tiles_m >= 4 && p.tiles_n >= 4 ? launch_m16<64, 2, true>(p, stream) : launch_m16<64, 2>(p, stream);
 }
@@ -654,7 +656,13 @@ int launch(const GemmParams& p, hipStream_t stream) {
 }  // namespace
 
 int gemm_bf16_nt_splitk_launch(const GemmParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true, true>), dim3(p.tiles_m * p.tiles_n * p.splits), dim3(256), 0, stream, p);
+  // Fetched ahead unless there is but one row or column of tiles, whose operand nobody shares and of which only half of the other is
+  // fetched.  Time with over without, 782 random launches, operands from memory / all of them in the memory-side cache: one row or
+  // column 1.01 / 1.01 (105 x 4127 x 27520 69 -> 75 us, 3223 x 200 x 50240 99 -> 106), two 0.98 / 1.00, four and more 0.98
+  // (up to 64 stages a slice) to 0.90 (from 192) / 1.01 to 0.93.
+  const dim3 grid(p.tiles_m * p.tiles_n * p.splits);
+  if (p.tiles_m > 1 && p.tiles_n > 1) hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true, true>), grid, dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true, false>), grid, dim3(256), 0, stream, p);
   return (int)hipGetLastError();
 }
 

@@ -94,6 +94,7 @@ def _sk(kernel, vec, M, N, K, splits):
 SPLITK = [
     _sk("gemm_bf16_nt_m16_kernel<64, 2, true, true>", "false", 1413, 758, 11008, 13), _sk("gemm_bf16_nt_m16_kernel<64, 2, true, true>", "true", 2052, 523, 17856, 11),
     _sk("gemm_bf16_nt_m16_kernel<64, 2, true, true>", "true", 1413, 760, 11072, 13),
+    _sk("gemm_bf16_nt_m16_kernel<64, 2, true, false>", "false", 2757, 143, 15808, 13), _sk("gemm_bf16_nt_m16_kernel<64, 2, true, false>", "true", 196, 2323, 19328, 13),
     _sk("gemm_wavek_kernel<1, 1, 4, 4, false, true>", "false", 1, 1, 6848, 11), _sk("gemm_wavek_kernel<1, 1, 4, 4, false, true>", "false", 35, 37, 9152, 13),
     _sk("gemm_wavek_kernel<1, 1, 4, 4, false, true>", "true", 21, 52, 7104, 9),
     _sk("gemm_wavek_kernel<2, 2, 4, 2, false, true>", "false", 561, 1, 15744, 13), _sk("gemm_wavek_kernel<2, 2, 4, 2, false, true>", "true", 2, 706, 8512, 9),
