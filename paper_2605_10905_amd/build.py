@@ -14,7 +14,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-Wno-inline-asm"]
-# the one-wave-per-SIMD backward kernel keeps its score accumulators in ordinary registers, where the vector work reads them
+# the one-wave-per-SIMD backward kernel keeps its score accumulators in ordinary registers, where the vector work reads them.
+# (An internal switch of the compiler: known to the clang 22 of ROCm 7.2.0, with which all figures were taken.  A compiler that does not know
+# it refuses the build; without it the kernels' register plan does not hold, and the listing has to be read anew for the wait states.)
 SOURCE_FLAGS = {"attn_bwd_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 

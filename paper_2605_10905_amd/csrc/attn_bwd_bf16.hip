@@ -843,10 +843,12 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_dkv_pipe_kernel(const AttnBwd
   auto grad_operand = [&](int off, int i) __attribute__((always_inline)) { return tr_operand((i & 1) ? 0 : 1, off, (i >> 1) % NCB, (i >> 1) / NCB); };
   // operand of score product i of the block at `off`: S += Q K^T (even i), dP += dO V^T (odd i)
   auto score_operand = [&](int off, int i) __attribute__((always_inline)) { return row_operand(i & 1, off, i >> 1); };
-  // The gradients are accumulated by assembly statements that pin them to accumulation registers , which
-  // the compiler's wait-state insertion does not look into.  In a step the packed P and dS are written a whole step before
-  // they are read here and nothing but these products touches the accumulators; behind the loop, `copied`
-  // covers operands that were just moved (2 wait states) and grads_settled() the readers of the result (8 passes: 12).
+  // The gradients are accumulated by assembly statements that pin them to accumulation registers, which
+  // the compiler's wait-state insertion does not look into.  A step packs its last P and dS in its last slot and the next step
+  // reads them two slots (d = 64) or more into it: behind at least two products and their operand reads, also over the back edge of the
+  // loop, where the compiler must place no move of them (a test reads the listing).  Nothing but these products touches the
+  // accumulators in a step; behind the loop, `copied` covers operands that were just moved (2 wait states) and grads_settled()
+  // the readers of the result (8 passes: 12).
   auto grad_mfma = [&](int i, u32x4 o, const u32x4 (&pp)[2], const u32x4 (&pd)[2], auto copied) __attribute__((always_inline)) {
     const int cb = (i >> 1) % NCB, kc = (i >> 1) / NCB;
     if constexpr (decltype(copied)::value) {
