@@ -656,12 +656,13 @@ int launch(const GemmParams& p, hipStream_t stream) {
 }  // namespace
 
 int gemm_bf16_nt_splitk_launch(const GemmParams& p, hipStream_t stream) {
-  // Fetched ahead unless there is but one row or column of tiles, whose operand nobody shares and of which only half of the other is
-  // fetched.  Time with over without, 782 random launches, operands from memory / all of them in the memory-side cache: one row or
-  // column 1.01 / 1.01 (105 x 4127 x 27520 69 -> 75 us, 3223 x 200 x 50240 99 -> 106), two 0.98 / 1.00, four and more 0.98
-  // (up to 64 stages a slice) to 0.90 (from 192) / 1.01 to 0.93.
+  // Fetched ahead from three rows and columns of tiles on.  Of one row or column nobody shares the panel and of the other operand only half
+  // is fetched; with two, what is fetched for some twenty panels of which each has two users can outgrow an XCD's L2.  Time with over without, 2532
+  // launches, operands from memory / all of them in the memory-side cache, geometric means (worst): one 1.01 / 1.01 (1.08 / 1.10: 105 x 4127 x
+  // 27520 69 -> 75 us), two 0.98 / 1.00 (1.15 / 1.48: 5140 x 281 x 49344 240 -> 355, 321 x 5342 x 48960 240 -> 274), three 0.96 / 0.99 (1.04 / 1.09),
+  // four and more 0.95 / 0.98 (1.03 / 1.14).
   const dim3 grid(p.tiles_m * p.tiles_n * p.splits);
-  if (p.tiles_m > 1 && p.tiles_n > 1) hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true, true>), grid, dim3(256), 0, stream, p);
+  if (p.tiles_m > 2 && p.tiles_n > 2) hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true, true>), grid, dim3(256), 0, stream, p);
   else hipLaunchKernelGGL((gemm_bf16_nt_m16_kernel<64, 2, true, false>), grid, dim3(256), 0, stream, p);
   return (int)hipGetLastError();
 }
