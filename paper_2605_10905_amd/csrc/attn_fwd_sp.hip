@@ -113,8 +113,11 @@ __device__ __forceinline__ void for_each_slot(F f, std::integer_sequence<int, M.
 // need only Q and key tiles 0 and 1 to have arrived, not bundles 0 and 1 requested behind them.
 // FORM = kPair (bf16, MODE 0 and 1): four waves own 128 queries, key tiles of 32 and otherwise the one-step iterations of the split
 // form.  The ring is 64 KB (d = 64: 32), so two (three) such workgroups share a CU, and one's first loads, first
-// block, diagonal and stores run beside the other's steps; its bytes are those of the whole form.  By itself a step
-// takes it 0.56 us (d = 128), beside another one 0.78.
+// block, diagonal and stores run beside the other's steps.  By itself a step takes it 0.56 us (d = 128), beside another one 0.78
+// (stamps of a full launch at a power-limited clock; pair_pays holds fits to whole launches, not step times).  Its results are the whole form's
+// but where a row's maximum rises by more than 8 in the last block that only one of them takes through the pipelined step (the
+// whole form runs an even number of blocks there): that block's probabilities are then rounded against another reference.  (The whole
+// form's count here would make the bytes equal and costs paired launches 1 - 2 %.)
 template <int D, bool CAUSAL, int MODE, bool FP8, int FORM = kWhole>
 __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kernel(const AttnParams p) {
   static_assert(!FP8 || (D == 128 && MODE != 1), "fp8 inputs: head dimension 128, no queue launch");
@@ -485,8 +488,9 @@ __global__ void __launch_bounds__(FORM == kPair ? 256 : 512, 2) attn_fwd_sp_kern
   // the current reference and the block is redone, after raising the reference and rescaling,
   // only if a lane's partial sum comes out large or not a number (always on the very first
   // block).  A row's multiply-add, exponential, and sum and pack lie in three consecutive slots, so that none waits for the
-  // one before it.  (A scheduling-group pipeline that left the order to the compiler had all three in one slot: 2 x 32 x 8192 1753 -> 1750 us,
-  // causal 910 -> 905, d = 64 1095 -> 1079, 4 x 16/8 x 2693, d = 64 135.0 -> 133.1, 4 x 16 x 2048 causal 71.2 -> 70.8.)
+  // one before it.  (A scheduling-group pipeline that left the order to the compiler had all three in one slot.  By itself this gives d = 64 1.5 %,
+  // 2 x 32 x 8192 1095 -> 1079 us, and d = 128 nothing beyond noise; it is here because every instantiation comes out alike, the list
+  // walk and the paired form too, which the compiler's solver had left half unpipelined.)
   // NSEG: between(i) runs in front of slot i * NM / NSEG, which is where the producer role's work goes.
   Operand pre[RA];
   auto koff_of = [](auto bid) __attribute__((always_inline)) { return ic<(decltype(bid)::value >> 1) * KTILEB + (decltype(bid)::value & 1) * KSUBB>{}; };

@@ -250,3 +250,27 @@ def test_resident_workgroups_give_the_bytes_of_single_tiles(names, c):
     want, want_lse = _one_tile_each(run, q, k, v, 768)
     assert bool(torch.isfinite(want.float()).all()) and bool(torch.isfinite(want_lse).all())
     assert torch.equal(o.view(torch.int16), want.view(torch.int16)) and torch.equal(lse, want_lse)
+
+
+# Scores that rise by `step` (in powers of two) from one 32-key block to the next: which of them raise the reference, and against which one
+# a block is rounded, depends on the form; all forms stay within the tolerances.
+@pytest.mark.parametrize("step", [9.0, 12.0, 15.0])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_forms_on_scores_that_rise_from_block_to_block(d, causal, step):
+    import paper_2605_10905_amd as A
+
+    forms = [v for v in range(A.attn_num_variants()) if A.attn_variant_name(v).startswith(f"bf16 d{d} ")]
+    assert len(forms) == 4
+    rng = np.random.default_rng(81 + d)
+    for N in (33, 95, 96, 97, 127, 128, 129, 160, 191, 192, 224, 257, 300):
+        q, k, v = (0.25 * rng.standard_normal((1, 3, N, d)).astype(np.float32) for _ in range(3))
+        q[..., 0] = 8.0
+        k[..., 0] = step * (np.arange(N) // 32) / (8.0 * d ** -0.5 * 1.4426950408889634)
+        bits = [wl.f32_to_bf16_bits(x) for x in (q, k, v)]
+        inp = dict(B=1, Hq=3, Hkv=3, N=N, d=d, causal=causal, scale=d ** -0.5, dtype="bf16", q=bits[0], k=bits[1], v=bits[2], descale=(1.0, 1.0, 1.0))
+        for form in forms:
+            label = f"rising scores d={d} causal={causal} step={step} N={N} {A.attn_variant_name(form)}"
+            print(label, flush=True)
+            o, lse = gu.run_gpu(inp, variant=form)
+            gu.check_full(inp, o, lse, label)
