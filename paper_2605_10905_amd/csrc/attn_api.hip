@@ -63,7 +63,7 @@ int validate(const void* q, const void* k, const void* v, void* o, float* lse, i
 }
 
 // Default choice: the first listed variant for (dtype, d).  (The bf16 defaults choose by themselves between the
-// two forms that attn_sp_forms lists one by one.)
+// three forms that attn_sp_forms lists one by one.)
 int choose_variant(int dtype, int B, int Hq, int N, int d) {
   (void)B; (void)Hq; (void)N;
   for (int i = 0; i < total_variants(); ++i) {

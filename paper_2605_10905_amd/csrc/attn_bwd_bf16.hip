@@ -11,8 +11,8 @@
 // Two kernels, neither of which uses atomics or a reduction across workgroups, so the result is
 // deterministic and no gradient needs an fp32 accumulation buffer in memory:
 //
-//   * attn_bwd_dq_kernel: a workgroup owns 128 query rows (64 when the launch is small; Q and dO rows stationary in
-//     registers as MFMA B operands, one query per lane, exactly the forward layout) and streams K/V tiles:
+//   * attn_bwd_dq_kernel: a workgroup owns 128 query rows (64 when the launch is small, 256 in attn_bwd_dq_wide_kernel, which some launches
+//     take; Q and dO rows stationary in registers as MFMA B operands, one query per lane, exactly the forward layout) and streams K/V tiles:
 //     S^T = K Q^T, dP^T = V dO^T, dS^T in registers, dQ^T += K^T dS^T.  It also writes the two
 //     per-row vectors the other kernel needs, -delta and lse * log2(e), into the workspace.
 //   * attn_bwd_dkv_pipe_kernel: a workgroup owns 128 keys (64 when the launch is small; K and V rows stationary, one key per

@@ -1026,19 +1026,13 @@ bool split_pays(const AttnParams& p, long long tiles) {
   return attn_split_pays(p.causal != 0, tiles, (long long)p.B * p.Hq * per_head, per_head, (p.N + 31) / 32, cost);
 }
 
-// What a launch of one form takes, us: n workgroups of `slots` per CU, the longest and the mean of their chains in 32-key
-// steps.  A step takes a + b (k - 1) where k workgroups share the CU, a workgroup P beside its chain, the launch F; it lasts as
-// long as the longest workgroup, or as all of them take: equal workgroups in whole rounds, the last one at t of a round if it is
-// nearly empty; causal ones, longest first, their share and half of t more.
-struct FormCost {
-  double F, P, a, b, t;
-};
-double form_us(const FormCost& c, bool causal, double n, int slots, double longest, double mean) {
-  const long long groups = (long long)n, cap = 256ll * slots, before = (groups - 1) / cap;
-  const double rounds = (double)((groups + 255) / 256), k = rounds < slots ? rounds : slots;
-  const double step = c.a + c.b * (k - 1.0), chain = c.P + longest * step;
-  double work = rounds;  // workgroups one after the other on a CU, each at its share of it
-  if (groups > cap) work = causal ? n / 256.0 + 0.5 * c.t : slots * ((double)before + c.t + (1.0 - c.t) * (n - (double)(before * cap)) / (double)cap);
+// What a launch of one form takes, us (see AttnFormCost): n workgroups, the longest and the mean of their chains in 32-key steps.  A causal
+// launch, longest first, lasts as long as its longest workgroup, or as all of them take evenly spread and half of t workgroups more.
+double form_us(const AttnFormCost& c, bool causal, double n, int slots, double longest, double mean) {
+  const long long groups = (long long)n, rounds = (groups + 255) / 256;
+  if (!causal) return attn_equal_us(c, groups, slots, longest);
+  const double step = attn_shared_step(c, groups, slots), k = (double)(rounds < slots ? rounds : slots);
+  const double chain = c.P + longest * step, work = groups > 256ll * slots ? n / 256.0 + 0.5 * c.t : (double)rounds;
   const double all = work * (c.P + mean * step) / k;
   return c.F + (chain > all ? chain : all);
 }
@@ -1053,14 +1047,14 @@ double form_us(const FormCost& c, bool causal, double n, int slots, double longe
 // up to 8 % slower (every workgroup reads K and V for 128 queries instead of 256): those keep their form, as do causal launches like
 // 128/64 x 568 25.6 -> 29.8, d = 64 72/36 x 1050 24.1 -> 28.0.
 bool pair_pays(const AttnParams& p, int d, bool split) {
-  static const FormCost cost[2][2][3] = {  // [d = 128][causal][whole, split, paired]
+  static const AttnFormCost cost[2][2][3] = {  // [d = 128][causal][whole, split, paired]
       {{{0.98, 3.44, 0.469, 0.100, 1.00}, {0.85, 4.00, 0.496, 0.300, 1.00}, {0.67, 3.89, 0.319, 0.220, 0.24}},
        {{1.70, 3.01, 0.433, 0.300, 1.13}, {1.16, 3.98, 0.466, 0.200, 0.94}, {1.51, 3.39, 0.316, 0.140, 4.44}}},
       {{{0.36, 4.88, 0.730, 0.200, 1.00}, {0.00, 6.01, 0.762, 0.300, 1.00}, {0.33, 5.35, 0.413, 0.420, 0.38}},
        {{0.18, 5.60, 0.628, 0.300, 1.08}, {0.00, 6.58, 0.651, 0.093, 1.08}, {0.00, 6.05, 0.406, 0.182, 3.44}}}};
-  const FormCost* const c = cost[d == 128][p.causal != 0];
+  const AttnFormCost* const c = cost[d == 128][p.causal != 0];
   const double heads = (double)p.B * p.Hq, steps = (p.N + 31) / 32;
-  auto us = [&](const FormCost& f, int bm, int slots, double part) {
+  auto us = [&](const AttnFormCost& f, int bm, int slots, double part) {
     const double T = (p.N + bm - 1) / bm;
     const double mean = p.causal ? ((T - 1.0) * 0.5 * (bm / 32) + steps / T) : steps;
     return form_us(f, p.causal != 0, heads * T, slots, part < 1.0 ? 0.5 * (steps + 1.0) : steps, part * mean);

@@ -29,9 +29,8 @@ struct AttnParams {
 //     third round then has to pay for its fixed cost.
 //   causal: only up to 256 whole tiles, where the longest of them sets the time.  The split tiles, longest
 //     first, take their mean over the CUs, and `last` of a mean tile longer where they do not all start at once.
-// The callers' numbers are fits to 908 launches of the forward and 1380 of the
-// backward (d = 64 and 128, N = 20 .. 6000, grouped heads among them, both forms of each timed
-// in turn); what the choice costs against the better form stands at the callers.
+// The caller's numbers are fits to 908 launches of the forward (d = 64 and 128, N = 20 .. 6000, grouped heads among them, both forms of
+// each timed in turn); what the choice costs against the better form stands there.
 struct AttnSplitCost {
   double fixed, fixed_split, slower, last;
   double least;  // steps below which the split form saves nothing: its tiles are then as many, each with a merge
